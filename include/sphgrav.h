@@ -88,13 +88,20 @@ typedef enum {
  *   grav_tile: sources per LDS tile of the gravity kernels (128, 256 or
  *   512; 0 = automatic: 256 for SG_FP32C, 512 for SG_FP64).  None of the
  *   three changes results beyond summation order.
- * grav_variant: 0 = automatic.  FP64 form: 1 = pair differences, reciprocal
+ * grav_variant: 0 = automatic: from 12288 particles on, in both forms, the
+ *   symmetric kernel, which meets each pair once and credits both particles
+ *   (grav_ipl = targets per lane, grav_split = parts of a block's source
+ *   list, grav_tile unused; its sums are fixed-point, so results do not
+ *   depend on grav_split), and below, or where those sums cannot hold the
+ *   input (extent / eps beyond 2^19 in the FP64 form, 2^30 in FP32C, or
+ *   magnitudes near the ends of the floating-point range), FP64 variant 4 or
+ *   FP32C variant 1.  FP64 form: 1 = pair differences, reciprocal
  *   square root seeded in FP32 and refined in FP64 (needs eps^2 >=
  *   1.2e-38), 2 = pair differences, seeded in FP64 (both refined to FP64
  *   rounding level); 3 (FP32 seed, needs eps^2 >= 1.2e-38) and 4 (FP64
  *   seed) = Morton-ordered particles with the far field expanded about a
- *   per-workgroup anchor, as the FP32C kernel does, in FP64 (4 is the
- *   automatic choice).  FP32C form: 1 (the only kernel).
+ *   per-workgroup anchor, as the FP32C kernel does, in FP64.  FP32C form:
+ *   1 = the one-sided kernel.
  * cell_scale_log2: side of the neighbour-search cells relative to the
  *   default rule, as a power of two (-1, 0 or +1; 0 = default).  Each gas
  *   particle keeps its level (the first l with L0 * 2^l >= (2 + 2^-9) h_i,

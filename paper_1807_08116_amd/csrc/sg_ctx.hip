@@ -36,6 +36,13 @@ inline int resolved_tile(const sg_params& p) {
     return p.precision == SG_FP64 ? 512 : 256;
 }
 
+// Smallest N of the symmetric gravity kernel: below, its launches have too
+// few workgroups (4096 particles: FP32C 33 us one-sided against 41, FP64 45
+// against 37 but with 7 us more preparation; 8192: equal; 20011: FP32C 204
+// against 162, FP64 362 against 222).
+constexpr int64_t kSymMin = 12288;
+constexpr int64_t kSymPartsMax = 128;
+
 constexpr size_t kAlign = 256;
 inline size_t al(size_t v) { return (v + kAlign - 1) & ~(kAlign - 1); }
 
@@ -102,7 +109,8 @@ layout make_layout(const sg_params* p, const sg_caps* c) {
     L.gorder = take(mort ? 4 * n : 0);
     L.morton = take(mort ? sg_morton_tmp_bytes(n) : 0);
     L.gsorted = take(mort ? sg_grav_sorted_bytes(n) : 0);
-    L.part = take(8 * 4 * (size_t)part_cap_elems(n));
+    L.part = take(std::max(8 * 4 * (size_t)part_cap_elems(n),
+                           mort && p->grav_variant == 0 ? sg_grav_sym_bytes(n) : 0));
     L.vtx = take(8 * n);
     L.vty = take(8 * n);
     L.vtz = take(8 * n);
@@ -314,6 +322,39 @@ void grav_shape(const sg_ctx* c, int* ipl, int* split) {
     *split = s;
 }
 
+// Symmetric gravity launch (each pair once): targets per lane, 0 for the
+// one-sided kernel.
+int sym_lanes(const sg_params& p, int64_t n, int ipl) {
+    if (p.grav_variant != 0 || n < kSymMin) return 0;
+    if (ipl != 0) return ipl;
+    if (p.precision == SG_FP32C) return n >= 65536 ? 4 : (n >= 24576 ? 2 : 1);
+    return n >= 131072 ? 4 : 2;
+}
+
+// Tiles per workgroup by the automatic rule; it is also the period at which
+// the target-side sums are rounded, so it follows from n and the targets per
+// lane alone.  About 16384 workgroups, and at most 32 tiles (8192 sources)
+// each up to kSymPartsMax parts: workgroups differ by the near runs they
+// meet, and more, shorter ones end closer together (FP32C at 786432
+// particles, T = 4: 150 ms with 2 parts a block, 128 with 8, 121 with 16,
+// 118 with 32; at 262144: 18.5 with 8, 15.1 with 32, 14.4 with 48).
+int64_t sym_period(int64_t n, int t) {
+    const int64_t B = 256 * (int64_t)t, nb = (n + B - 1) / B, tiles = sg_sym_tiles(n, t);
+    int64_t s = (16384 + nb - 1) / nb;
+    if (s < tiles / 32) s = tiles / 32;
+    if (s > kSymPartsMax) s = kSymPartsMax;
+    return s < tiles ? (tiles + s - 1) / s : 1;
+}
+
+// Tiles per workgroup: the automatic ones, or grav_split parts a block,
+// rounded up to whole periods (so results do not depend on the parts).
+int64_t sym_chunk(const sg_params& p, int64_t n, int t) {
+    const int64_t period = sym_period(n, t);
+    if (p.grav_split == 0) return period;
+    const int64_t tiles = sg_sym_tiles(n, t), c = (tiles + p.grav_split - 1) / p.grav_split;
+    return (c + period - 1) / period * period;
+}
+
 sg_status do_build(sg_ctx* c) {
     const int64_t ng = c->ng;
     if (ng == 0) {
@@ -394,6 +435,10 @@ void grav_args(sg_ctx* c, bool pot, sg_grav_args& a) {
     a.gz = c->at<double>(c->L.gz);
     a.gpot = c->s.pot ? c->s.pot : c->at<double>(c->L.gpot);
     a.part = c->at<double>(c->L.part);
+    a.sym = sym_lanes(c->prm, c->n, c->prm.grav_ipl);
+    a.sym_period = a.sym ? sym_period(c->n, a.sym) : 1;
+    a.sym_chunk = a.sym ? sym_chunk(c->prm, c->n, a.sym) : 1;
+    a.g = c->grid();
     a.err = &c->grid()->err;
 }
 
@@ -1027,9 +1072,11 @@ struct sg_ens {
     hipEvent_t cev[2];
     sg_ens_sys* d_sys;
     sg_ens_task* d_tasks;
-    int32_t* d_counter;
-    int32_t ntasks;
+    sg_sym_task* d_sym;
+    int32_t* d_counter;          // [2]: one-sided, symmetric
+    int32_t ntasks, nsym;
     int nblocks, ipl, tile;
+    int sym_blocks;              // workgroups of the symmetric launch
     double eps, G;
     sg_seg seg;                  // segmented launches over all systems
     char msg[256];
@@ -1050,16 +1097,22 @@ extern "C++" {
 namespace {
 
 struct ens_offsets {
-    size_t tasks, counter, seg, pfx, total;
+    size_t tasks, sym, counter, seg, pfx, total;
 };
 
-ens_offsets ens_layout(int32_t nsys, int64_t ntasks) {
+// Symmetric tasks of an ensemble are at most kSymPartsMax for each block of
+// at least 256 particles.
+int64_t ens_sym_cap(int32_t nsys, int64_t total) { return kSymPartsMax * (total / 256 + nsys); }
+
+ens_offsets ens_layout(int32_t nsys, int64_t ntasks, int64_t nsym) {
     ens_offsets o;
     size_t at = al(sizeof(sg_ens_sys) * (size_t)nsys);
     o.tasks = at;
     at += al(sizeof(sg_ens_task) * (size_t)(ntasks > 0 ? ntasks : 1));
+    o.sym = at;
+    at += al(sizeof(sg_sym_task) * (size_t)(nsym > 0 ? nsym : 1));
     o.counter = at;
-    at += al(sizeof(int32_t));
+    at += al(2 * sizeof(int32_t));
     o.seg = at;
     at += al(sizeof(sg_seg_sys) * (size_t)nsys);
     o.pfx = at;
@@ -1101,8 +1154,11 @@ sg_status ens_grav_launch(sg_ens* e, bool pot, hipStream_t st) {
     hipStream_t own = c0->st;
     c0->st = st;
     c0->begin(SG_ST_GRAV);
+    sg_launch_grav_ensemble_sym(e->d_sys, e->d_sym, e->nsym, e->d_counter, pot ? 1 : 0, e->eps,
+                                e->ipl, e->sym_blocks, st);
     sg_launch_grav_ensemble(e->d_sys, e->d_tasks, e->ntasks, e->d_counter, pot ? 1 : 0, e->eps,
                             e->G, e->ipl, e->tile, e->nblocks, st);
+    if (e->nsym > 0) sg_seg_launch_grav_finish(e->seg, pot ? 1 : 0, e->G, e->eps, st);
     c0->end();
     c0->st = own;
     hipError_t err = hipGetLastError();
@@ -1251,7 +1307,7 @@ sg_status ens_step(sg_ens* e, double dt, uint32_t flags) {
 
 size_t sg_ensemble_bytes(int32_t nsys, int64_t total_particles) {
     if (nsys < 1 || total_particles < 1) return 0;
-    return ens_layout(nsys, total_particles / 64 + nsys).total;
+    return ens_layout(nsys, total_particles / 64 + nsys, ens_sym_cap(nsys, total_particles)).total;
 }
 
 sg_status sg_ensemble_create(sg_ctx* const* ctxs, int32_t nsys, void* d_ws, size_t ws_bytes,
@@ -1265,6 +1321,7 @@ sg_status sg_ensemble_create(sg_ctx* const* ctxs, int32_t nsys, void* d_ws, size
     std::vector<sg_seg_sys> seg((size_t)nsys);
     std::vector<int64_t> pfx((size_t)SG_SEG_NPFX * (nsys + 1), 0);
     std::vector<std::pair<int64_t, sg_ens_task>> tasks;
+    std::vector<std::pair<int64_t, sg_sym_task>> stasks;
     int64_t total = 0;
     int gas_passes = 1;
     // launch shape of the first context: 256 * ipl targets per task.  Unset
@@ -1294,6 +1351,19 @@ sg_status sg_ensemble_create(sg_ctx* const* ctxs, int32_t nsys, void* d_ws, size
         S.gp = c->s.pot ? c->s.pot : c->at<double>(c->L.gpot);
         const int64_t nb = (c->n + per - 1) / per;
         for (int64_t b = 0; b < nb; ++b) tasks.push_back({c->n, sg_ens_task{k, (int32_t)b}});
+        S.g = c->grid();
+        S.acc = c->at<long long>(c->L.part);
+        S.sym = sym_lanes(c->prm, c->n, ipl) != 0 ? 1 : 0;
+        S.sym_period = 1;
+        if (S.sym) {
+            const int64_t B = 256 * (int64_t)ipl, nsb = (c->n + B - 1) / B;
+            const int64_t tiles = sg_sym_tiles(c->n, ipl), chunk = sym_period(c->n, ipl);
+            S.sym_period = (int32_t)chunk;
+            for (int64_t t0 = 0; t0 < tiles; t0 += chunk)
+                for (int64_t b = 0; b < nsb; ++b)
+                    stasks.push_back({c->n, sg_sym_task{k, (int32_t)b, (int32_t)t0,
+                                                        (int32_t)(t0 + chunk)}});
+        }
         total += c->n;
         // the segmented launches' view of the same system
         sg_seg_sys& Q = seg[(size_t)k];
@@ -1333,6 +1403,9 @@ sg_status sg_ensemble_create(sg_ctx* const* ctxs, int32_t nsys, void* d_ws, size
         Q.gx = S.gx;
         Q.gy = S.gy;
         Q.gz = S.gz;
+        Q.gp = S.gp;
+        Q.acc = S.acc;
+        Q.sym = S.sym;
         Q.sph = c->sph();
         Q.g = c->grid();
         sg_morton_ptrs(c->at<void>(c->L.morton), c->n, &Q.mk0, &Q.mk1, &Q.mv0, &Q.mv1, &Q.mhist,
@@ -1369,8 +1442,15 @@ sg_status sg_ensemble_create(sg_ctx* const* ctxs, int32_t nsys, void* d_ws, size
     std::stable_sort(tasks.begin(), tasks.end(),
                      [](const std::pair<int64_t, sg_ens_task>& a,
                         const std::pair<int64_t, sg_ens_task>& b) { return a.first > b.first; });
-    const ens_offsets o = ens_layout(nsys, (int64_t)tasks.size());
-    if (ws_bytes < o.total || (int64_t)tasks.size() > total / 64 + nsys) return SG_EINVAL;
+    std::stable_sort(stasks.begin(), stasks.end(),
+                     [](const std::pair<int64_t, sg_sym_task>& a,
+                        const std::pair<int64_t, sg_sym_task>& b) { return a.first > b.first; });
+    const ens_offsets o = ens_layout(nsys, (int64_t)tasks.size(), (int64_t)stasks.size());
+    if (ws_bytes < o.total || (int64_t)tasks.size() > total / 64 + nsys ||
+        (int64_t)stasks.size() > ens_sym_cap(nsys, total))
+        return SG_EINVAL;
+    std::vector<sg_sym_task> stk(stasks.size());
+    for (size_t i = 0; i < stasks.size(); ++i) stk[i] = stasks[i].second;
     std::vector<sg_ens_task> tk(tasks.size());
     for (size_t i = 0; i < tasks.size(); ++i) tk[i] = tasks[i].second;
     sg_ens* e = new (std::nothrow) sg_ens();
@@ -1381,7 +1461,9 @@ sg_status sg_ensemble_create(sg_ctx* const* ctxs, int32_t nsys, void* d_ws, size
     e->d_sys = (sg_ens_sys*)ws;
     e->d_tasks = (sg_ens_task*)(ws + o.tasks);
     e->d_counter = (int32_t*)(ws + o.counter);
+    e->d_sym = (sg_sym_task*)(ws + o.sym);
     e->ntasks = (int32_t)tk.size();
+    e->nsym = (int32_t)stk.size();
     e->ipl = ipl;
     e->tile = tile;
     e->eps = ctxs[0]->prm.eps;
@@ -1390,6 +1472,8 @@ sg_status sg_ensemble_create(sg_ctx* const* ctxs, int32_t nsys, void* d_ws, size
     e->seg.pfx = (const int64_t*)(ws + o.pfx);
     e->seg.nsys = nsys;
     e->seg.gas_passes = gas_passes;
+    e->seg.sym = e->nsym > 0 ? 1 : 0;
+    e->seg.eps = e->eps;
     for (int q = 0; q < SG_SEG_NPFX; ++q) e->seg.nblk[q] = pfx[(size_t)q * (nsys + 1) + nsys];
     e->msg[0] = 0;
     int dev = 0, cus = 256;
@@ -1424,10 +1508,16 @@ sg_status sg_ensemble_create(sg_ctx* const* ctxs, int32_t nsys, void* d_ws, size
     (void)hipGetLastError();
     e->nblocks = per_cu * (cus > 0 ? cus : 256);
     if (e->nblocks > e->ntasks) e->nblocks = e->ntasks;
+    e->sym_blocks = sg_grav_sym_blocks_per_cu(ipl) * (cus > 0 ? cus : 256);
+    (void)hipGetLastError();
+    if (e->sym_blocks > e->nsym) e->sym_blocks = e->nsym;
     if (hipMemcpyAsync(e->d_sys, sys.data(), sizeof(sg_ens_sys) * sys.size(), hipMemcpyHostToDevice,
                        e->st) != hipSuccess ||
         hipMemcpyAsync(e->d_tasks, tk.data(), sizeof(sg_ens_task) * tk.size(),
                        hipMemcpyHostToDevice, e->st) != hipSuccess ||
+        (!stk.empty() &&
+         hipMemcpyAsync(e->d_sym, stk.data(), sizeof(sg_sym_task) * stk.size(),
+                        hipMemcpyHostToDevice, e->st) != hipSuccess) ||
         hipMemcpyAsync(ws + o.seg, seg.data(), sizeof(sg_seg_sys) * seg.size(),
                        hipMemcpyHostToDevice, e->st) != hipSuccess ||
         hipMemcpyAsync(ws + o.pfx, pfx.data(), sizeof(int64_t) * pfx.size(), hipMemcpyHostToDevice,

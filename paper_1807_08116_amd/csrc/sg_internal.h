@@ -82,6 +82,10 @@ struct sg_grid_dev {
     int64_t M;
     // gravity-order bounding box over all N (order-preserving u64 images)
     unsigned long long glo[3], ghi[3];
+    // gravity preparation: scales (powers of two) of the fixed-point sums of
+    // the symmetric kernel, and whether it may run (else the one-sided one)
+    double grav_S, grav_Sp;
+    int32_t grav_sym, pad2;
     // status
     uint32_t err, pad1;
     int64_t need_cells, need_nnz;
@@ -204,16 +208,31 @@ struct sg_grav_args {
     const double *xs, *ys, *zs, *ms;    // (set by the launcher) sorted copies
     const void* sbox;                   // (set by the launcher) sub-tile boxes
     double *gx, *gy, *gz, *gpot;        // outputs [n], particle order
-    double* part;                       // split partials [4][split][n] when split > 1
+    double* part;                       // split partials [4][split][n] when split > 1; the
+                                        // symmetric kernel's fixed-point sums (sg_grav_sym_bytes)
+    int sym;                            // symmetric kernel: targets per lane (1, 2 or 4), 0 = the
+                                        // one-sided kernel alone
+    int64_t sym_chunk, sym_period;      // tiles per workgroup (a multiple of the period), tiles
+                                        // per rounding of the target-side sums
+    sg_grid_dev* g;                     // scales and the device's choice (sym != 0)
     uint32_t* err;                      // device error word (non-finite positions)
 };
 size_t sg_grav_sorted_bytes(int64_t n);
+size_t sg_grav_sym_bytes(int64_t n);
 // FP32C: Morton-ordered copies of x, y, z, m and the boxes of their
 // 64-particle runs (needs a.order and a.sorted); a non-finite position
 // sets SGE_GNONFINITE in *a.err.
 // Both return -1 (and launch nothing) when a required pointer is missing.
 int sg_launch_grav_sorted(const sg_grav_args& a, hipStream_t st);
 int sg_launch_gravity(const sg_grav_args& a, hipStream_t st);
+
+// Symmetric kernel: 256-source tiles of the longest block list (its own
+// block, (nb - 1) / 2 others, one more for half of the blocks when their
+// number nb is even), t targets per lane.
+inline int64_t sg_sym_tiles(int64_t n, int t) {
+    const int64_t B = 256 * (int64_t)t, nb = (n + B - 1) / B;
+    return t * (1 + nb / 2);
+}
 
 // Ensembles: one persistent launch over (system, block of 256*ipl targets)
 // tasks of several systems in the FP32C form.
@@ -223,12 +242,26 @@ struct sg_ens_sys {
     const int32_t* order;
     int64_t n;
     double *gx, *gy, *gz, *gp;          // outputs, particle order
+    sg_grid_dev* g;
+    long long* acc;                     // the symmetric kernel's sums (sg_grav_sym_bytes)
+    int32_t sym, sym_period;            // the symmetric kernel serves this system (where the
+                                        // device's choice, g->grav_sym, allows it)
 };
 struct sg_ens_task {
     int32_t sys, blk;
 };
+struct sg_sym_task {
+    int32_t sys, blk, t0, t1;           // tiles [t0, t1) of the block's source list
+};
 void sg_grav_sorted_ptrs(void* sorted, int64_t n, const double** xs, const double** ys,
                          const double** zs, const double** ms, const void** sbox);
+// The symmetric launch over its tasks (it resets both task counters first:
+// d_counter[0] belongs to the one-sided launch, which follows it and takes
+// the systems that the symmetric kernel does not serve).
+void sg_launch_grav_ensemble_sym(const sg_ens_sys* d_sys, const sg_sym_task* d_tasks,
+                                 int32_t ntasks, int32_t* d_counter, int with_pot, double eps,
+                                 int t, int nblocks, hipStream_t st);
+int sg_grav_sym_blocks_per_cu(int t);
 void sg_launch_grav_ensemble(const sg_ens_sys* d_sys, const sg_ens_task* d_tasks, int32_t ntasks,
                              int32_t* d_counter, int with_pot, double eps, double G, int ipl,
                              int tile, int nblocks, hipStream_t st);
@@ -252,7 +285,9 @@ struct sg_seg_sys {
     // workspace: predictor values, SPH and gravity parts
     double *vtx, *vty, *vtz, *et;
     double *asx, *asy, *asz;
-    double *gx, *gy, *gz;
+    double *gx, *gy, *gz, *gp;
+    long long* acc;                  // as in sg_ens_sys
+    int32_t sym, pad;
     sg_sph_bufs sph;
     sg_grid_dev* g;
     // Morton order: key/value ping-pong buffers, digit histograms and
@@ -295,6 +330,8 @@ struct sg_seg {
     const sg_seg_sys* sys;           // [nsys], device
     const int64_t* pfx;              // [SG_SEG_NPFX][nsys + 1] block prefixes, device
     int32_t nsys;
+    int32_t sym;                     // some system is served by the symmetric gravity
+    double eps;
     int32_t gas_passes;              // radix passes of the cell keys (largest over systems)
     int64_t nblk[SG_SEG_NPFX];       // totals of the prefixes (host)
 };
@@ -311,6 +348,8 @@ void sg_seg_launch_predict(const sg_seg& s, double dt, hipStream_t st);
 void sg_seg_launch_correct(const sg_seg& s, double dt, hipStream_t st);
 void sg_seg_launch_morton_order(const sg_seg& s, hipStream_t st);
 void sg_seg_launch_grav_sorted(const sg_seg& s, hipStream_t st);
+void sg_seg_launch_grav_finish(const sg_seg& s, int with_pot, double G, double eps,
+                               hipStream_t st);
 // The neighbour build of every system, in the order of the per-system
 // launches: the gas sort (grid rule, keys and counts, cell offsets, stable
 // reorder and gather), the search, the scan of the neighbour counts into
