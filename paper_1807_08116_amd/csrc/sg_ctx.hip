@@ -1332,6 +1332,11 @@ sg_status sg_ensemble_create(sg_ctx* const* ctxs, int32_t nsys, void* d_ws, size
     const int ipl = ctxs[0]->prm.grav_ipl != 0 ? ctxs[0]->prm.grav_ipl : 2;
     const int tile = ctxs[0]->prm.grav_tile != 0 ? ctxs[0]->prm.grav_tile : 512;
     const int64_t per = 256 * (int64_t)ipl;
+    // one search launch for all systems: as many targets per wavefront as
+    // their gas together asks for
+    int64_t gas_total = 0;
+    for (int32_t k = 0; k < nsys; ++k) gas_total += ctxs[k] && ctxs[k]->bound ? ctxs[k]->ng : 0;
+    const int nbr_targets = sg_nbr_targets(gas_total);
     for (int32_t k = 0; k < nsys; ++k) {
         sg_ctx* c = ctxs[k];
         if (!c || !c->bound) return SG_EINVAL;
@@ -1432,7 +1437,7 @@ sg_status sg_ensemble_create(sg_ctx* const* ctxs, int32_t nsys, void* d_ws, size
                                           sg_compact_blocks(c->ng),
                                           gas ? Q.gntiles : 0,
                                           sg_sph_blocks(c->ng),
-                                          sg_nbr_blocks(c->ng)};
+                                          sg_nbr_blocks(c->ng, nbr_targets)};
         if (gas && sg_gas_radix_passes(c->caps.cell_cap) > gas_passes)
             gas_passes = sg_gas_radix_passes(c->caps.cell_cap);
         for (int q = 0; q < SG_SEG_NPFX; ++q)
@@ -1471,6 +1476,7 @@ sg_status sg_ensemble_create(sg_ctx* const* ctxs, int32_t nsys, void* d_ws, size
     e->seg.sys = (const sg_seg_sys*)(ws + o.seg);
     e->seg.pfx = (const int64_t*)(ws + o.pfx);
     e->seg.nsys = nsys;
+    e->seg.nbr_targets = nbr_targets;
     e->seg.gas_passes = gas_passes;
     e->seg.sym = e->nsym > 0 ? 1 : 0;
     e->seg.eps = e->eps;

@@ -332,6 +332,7 @@ struct sg_seg {
     int32_t nsys;
     int32_t sym;                     // some system is served by the symmetric gravity
     double eps;
+    int32_t nbr_targets;             // targets per wavefront of the neighbour search
     int32_t gas_passes;              // radix passes of the cell keys (largest over systems)
     int64_t nblk[SG_SEG_NPFX];       // totals of the prefixes (host)
 };
@@ -361,7 +362,8 @@ void sg_seg_launch_nbr_finish(const sg_seg& s, hipStream_t st);
 // Density, and the EOS records + FP32C forces on the predicted state
 // (predicted != 0: vt, et) or the current one.
 int64_t sg_sph_blocks(int64_t ng);
-int64_t sg_nbr_blocks(int64_t ng);
+int sg_nbr_targets(int64_t ng);                // targets per wavefront of the search
+int64_t sg_nbr_blocks(int64_t ng, int nt);
 int64_t sg_compact_blocks(int64_t ng);
 void sg_seg_launch_density(const sg_seg& s, hipStream_t st);
 void sg_seg_launch_sph_state(const sg_seg& s, int predicted, hipStream_t st);

@@ -10,7 +10,7 @@
 // contiguous slot range, and visiting levels, then z, y, x in ascending
 // order yields candidates in ascending slot order: rows need no sort.
 //
-// Cell-staged search (k_nbr_search).  One wavefront takes 32 consecutive
+// Cell-staged search (k_nbr_search).  One wavefront takes 1 to 32 consecutive
 // target slots and walks them cell by cell: the targets that share a cell
 // key form a run, and the run's search region is the union (per level) of
 // its targets' boxes.  The rows of that region are flattened into one
@@ -33,22 +33,17 @@
 //
 // Built with -ffp-contract=off: the FP32 predicate must round exactly as
 // specified (each product and fma rounded once).
+#include <type_traits>
+
 #include "sg_internal.h"
 
 namespace {
 
 constexpr int kBlock = 256;
 constexpr int kWaves = kBlock / 64;
-// Targets per wavefront of the search (lanes 0 .. kTargets-1 hold them;
-// all 64 lanes hold candidates).  The search is bound by the vector-ALU
-// work of its pair tests (busy 85 % of the kernel at 2M particles),
-// and the wavefronts' work varies widely (runs of 1 to 64 targets, union
-// boxes over 1 to 5 levels), so shorter wavefronts pack the SIMDs better
-// at the end of the launch: the search stage took 1.62 ms with 64 targets
-// per wavefront, 1.53 ms with 32 and 1.57 ms with 16 (each run cut at a
-// wavefront boundary repeats its boxes' setup and candidate loads); with
-// the set-up as it is now, 0.98-0.99, 0.96-0.97 and 1.00 ms.
-constexpr int kTargets = 32;
+// Targets per wavefront of the search, NT (lanes 0 .. NT-1 hold them; all
+// 64 lanes hold candidates): 32 at a million targets, down to 1 for a few
+// thousand, by the number of targets (sg_nbr_targets below has the times).
 // Candidate batches held in registers per target pass: each target's data
 // is read and its hit count fetched once per kHold batches instead of once
 // per batch.  Search stage at 2M particles when the target data were lane
@@ -206,7 +201,8 @@ __device__ inline int32_t wave_incl_sum(int32_t v) {
     return v;
 }
 
-// The search of wavefront w (target slots kTargets w onward); w is uniform.
+// The search of wavefront w (target slots NT w onward); w is uniform.
+template <int NT>
 __device__ __attribute__((always_inline)) inline void nbr_search_wave(
     const sg_grid_dev* __restrict__ g, int64_t ng, const double* __restrict__ xs,
     const double* __restrict__ ys, const double* __restrict__ zs, const double* __restrict__ hs,
@@ -215,10 +211,10 @@ __device__ __attribute__((always_inline)) inline void nbr_search_wave(
     int32_t w) {
     if (g->err & SGE_SORT_FATAL) return;
     const unsigned lane = threadIdx.x & 63;
-    const int64_t g0 = (int64_t)w * kTargets;
+    const int64_t g0 = (int64_t)w * NT;
     if (g0 >= ng) return;
     const int64_t s = g0 + lane;
-    const bool live = lane < (unsigned)kTargets && s < ng;
+    const bool live = lane < (unsigned)NT && s < ng;
     double p[3] = {0.0, 0.0, 0.0}, h = 0.0;
     int32_t k = -1;
     if (live) {
@@ -237,9 +233,9 @@ __device__ __attribute__((always_inline)) inline void nbr_search_wave(
     // 1.096 ms); 4 KB per workgroup, which still fits beside the gravity
     // kernel's workgroups on a compute unit
     struct target_rec { double x, y, z; float h, pad; };
-    __shared__ target_rec tp[kWaves][kTargets];
+    __shared__ target_rec tp[kWaves][NT];
     target_rec* const mytp = tp[threadIdx.x >> 6];
-    if (lane < (unsigned)kTargets) mytp[lane] = target_rec{p[0], p[1], p[2], hif, 0.0f};
+    if (lane < (unsigned)NT) mytp[lane] = target_rec{p[0], p[1], p[2], hif, 0.0f};
     __builtin_amdgcn_wave_barrier();
     int32_t mine = 0;                          // hits of target g0 + lane so far
     const int nlev = g->nlev;
@@ -386,6 +382,7 @@ __device__ __attribute__((always_inline)) inline void nbr_search_wave(
     if (live) cnt[s] = mine;
 }
 
+template <int NT>
 __global__ __launch_bounds__(kBlock) void k_nbr_search(
     const sg_grid_dev* __restrict__ g, int64_t ng, const double* __restrict__ xs,
     const double* __restrict__ ys, const double* __restrict__ zs, const double* __restrict__ hs,
@@ -400,7 +397,7 @@ __global__ __launch_bounds__(kBlock) void k_nbr_search(
     // (1.5x the fetched bytes of chunks of 16, at the same time).
     const int32_t w = __builtin_amdgcn_readfirstlane(
         (int32_t)(xcd_chunk_block(blockIdx.x, gridDim.x, 16) * kWaves + (threadIdx.x >> 6)));
-    nbr_search_wave(g, ng, xs, ys, zs, hs, off, perm, key, cnt, slots, w);
+    nbr_search_wave<NT>(g, ng, xs, ys, zs, hs, off, perm, key, cnt, slots, w);
 }
 
 // Move every target's slot to its CSR row (or search again into the row
@@ -483,6 +480,7 @@ __global__ void k_nbr_check(sg_grid_dev* g, const int64_t* __restrict__ nbr_off,
 // ----------------------------------------------------- all systems at once --
 // (see sg_seg in sg_internal.h)
 
+template <int NT>
 __global__ __launch_bounds__(kBlock) void k_seg_nbr_search(const sg_seg_sys* __restrict__ sys,
                                                            const int64_t* __restrict__ pfx,
                                                            int nsys) {
@@ -490,7 +488,8 @@ __global__ __launch_bounds__(kBlock) void k_seg_nbr_search(const sg_seg_sys* __r
     const sg_seg_sys& S = sys[sg_seg_find(pfx, nsys, blockIdx.x, &lb)];
     const int32_t w = __builtin_amdgcn_readfirstlane((int32_t)(lb * kWaves + (threadIdx.x >> 6)));
     const sg_sph_bufs& b = S.sph;
-    nbr_search_wave(S.g, S.ng, b.xs, b.ys, b.zs, b.hs, S.off, b.perm, S.key, S.ncnt, S.slots, w);
+    nbr_search_wave<NT>(S.g, S.ng, b.xs, b.ys, b.zs, b.hs, S.off, b.perm, S.key, S.ncnt, S.slots,
+                        w);
 }
 
 __global__ void k_seg_nbr_check(const sg_seg_sys* __restrict__ sys, int nsys) {
@@ -515,10 +514,46 @@ inline unsigned waves_grid(int64_t n) {
 
 }  // namespace
 
+// Targets per wavefront.  Few targets per wavefront give many short
+// wavefronts: at a few thousand targets the stage is the latency of one
+// wavefront's serial walk over its targets' levels, rows and passes.  Many
+// share the set-up of a run's boxes and each candidate load among its
+// targets, which is what counts once the wavefronts fill the chip.  Stage
+// (search, scan, check, copy) in us with 32 / 16 / 8 / 4 / 2 / 1 targets: 1009
+// targets 153 / 116 / 86 / 61 / 42 / 30; 4096: 179 / 116 / 79 / 61 / 48 / 39;
+// 9001: 217 / 129 / 86 / 72 / 57 / 56; 30011: 191 / 128 / 100 / 98 / 101 /
+// 123; 65536: 204 / 157 / 133 / 139 / 168 / 219; 131071: 222 / 197 / 195 /
+// 218 / 281; 262144: 328 / 307 / 330 / 390; 524288: 541 / 544 / 602; 1048576:
+// 953 / 991 / 1123.
+int sg_nbr_targets(int64_t ng) {
+    if (ng >= 450000) return 32;
+    if (ng >= 150000) return 16;
+    if (ng >= 45000) return 8;
+    if (ng >= 22000) return 4;
+    return ng >= 9500 ? 2 : 1;
+}
+
+namespace {
+template <typename F>
+void with_targets(int nt, F&& f) {
+    switch (nt) {
+        case 1: f(std::integral_constant<int, 1>()); break;
+        case 2: f(std::integral_constant<int, 2>()); break;
+        case 4: f(std::integral_constant<int, 4>()); break;
+        case 8: f(std::integral_constant<int, 8>()); break;
+        case 16: f(std::integral_constant<int, 16>()); break;
+        default: f(std::integral_constant<int, 32>()); break;
+    }
+}
+}  // namespace
+
 void sg_seg_launch_nbr_search(const sg_seg& s, hipStream_t st) {
-    if (s.nblk[SG_SEG_NBR] > 0)
-        hipLaunchKernelGGL(k_seg_nbr_search, dim3((unsigned)s.nblk[SG_SEG_NBR]), dim3(kBlock), 0, st,
-                           s.sys, s.pfx + SG_SEG_NBR * (s.nsys + 1), s.nsys);
+    if (s.nblk[SG_SEG_NBR] == 0) return;
+    with_targets(s.nbr_targets, [&](auto nt) {
+        hipLaunchKernelGGL((k_seg_nbr_search<decltype(nt)::value>),
+                           dim3((unsigned)s.nblk[SG_SEG_NBR]), dim3(kBlock), 0, st, s.sys,
+                           s.pfx + SG_SEG_NBR * (s.nsys + 1), s.nsys);
+    });
 }
 
 void sg_seg_launch_nbr_finish(const sg_seg& s, hipStream_t st) {
@@ -533,8 +568,8 @@ int64_t sg_compact_blocks(int64_t ng) {
     return (ng + per - 1) / per;
 }
 
-int64_t sg_nbr_blocks(int64_t ng) {
-    const int64_t per = (int64_t)kWaves * kTargets;
+int64_t sg_nbr_blocks(int64_t ng, int nt) {
+    const int64_t per = (int64_t)kWaves * nt;
     return (ng + per - 1) / per;
 }
 
@@ -544,9 +579,12 @@ void sg_launch_nbr_search(const sg_grid_dev* g, int64_t ng, const double* xs, co
                           const double* zs, const double* hs, const int64_t* off,
                           const int32_t* perm, const int32_t* key, int32_t* cnt, int32_t* slots,
                           hipStream_t st) {
-    // one wavefront per kTargets target slots
-    hipLaunchKernelGGL(k_nbr_search, dim3(waves_grid((ng + kTargets - 1) / kTargets)), dim3(kBlock), 0, st, g, ng,
-                       xs, ys, zs, hs, off, perm, key, cnt, slots);
+    const int targets = sg_nbr_targets(ng);
+    with_targets(targets, [&](auto nt) {
+        hipLaunchKernelGGL((k_nbr_search<decltype(nt)::value>),
+                           dim3(waves_grid((ng + targets - 1) / targets)), dim3(kBlock), 0, st, g,
+                           ng, xs, ys, zs, hs, off, perm, key, cnt, slots);
+    });
 }
 
 void sg_launch_nbr_check(sg_grid_dev* g, const int64_t* nbr_off, int64_t ng, int64_t nnz_cap,
