@@ -372,28 +372,29 @@ sg_status do_build(sg_ctx* c) {
     void* scan = c->at<void>(c->L.scan);
     sg_sph_bufs b = c->sph();
     c->begin(SG_ST_SORT);
-    sg_launch_grid_reset(g, st);
-    sg_launch_grid_reduce(s.x, s.y, s.z, s.h, ng, g, st);
-    sg_launch_grid_finish(g, C, c->prm.cell_scale_log2, st);
-    sg_launch_cells_clear(g, count, hmax, C, st);
+    sg_launch_grid(s.x, s.y, s.z, s.h, ng, g, count, hmax, C, c->prm.cell_scale_log2, st);
     // the FP64 force records are rebuilt before every use (record builds
     // precede each force and time-step pass), so the sort borrows their
     // buffer for the particle-order records the gather reads
     sg_prec* pin = reinterpret_cast<sg_prec*>(b.f64);
     sg_launch_keys_count(s.x, s.y, s.z, s.h, s.m, ng, g, key, count, hmax, pin, st);
-    sg_launch_scan(count, off, 0, &g->M, C, scan, st);
-    sg_launch_gas_order(key, ng, C, c->at<void>(c->L.gsort), c->at<int32_t>(c->L.perm), st);
-    sg_launch_gather_gas(b.perm, ng, g, pin, b.xs, b.ys, b.zs, b.hs, b.ms, b.prec, st);
+    const uint32_t* sorted =
+        sg_launch_gas_order(key, ng, C, c->at<void>(c->L.gsort), c->at<int32_t>(c->L.perm), st);
+    if (sg_offsets_by_bisection(ng, C)) {
+        sg_launch_gather_gas_off(b.perm, ng, g, pin, b.xs, b.ys, b.zs, b.hs, b.ms, b.prec, sorted,
+                                 off, C, st);
+    } else {
+        sg_launch_scan(count, off, 0, &g->M, C, scan, st);
+        sg_launch_gather_gas(b.perm, ng, g, pin, b.xs, b.ys, b.zs, b.hs, b.ms, b.prec, st);
+    }
     c->end();
     c->begin(SG_ST_NBR);
     int32_t* ncnt = c->at<int32_t>(c->L.ncnt);
     int64_t* nbr_off = c->at<int64_t>(c->L.nbr_off);
     int32_t* slots = c->at<int32_t>(c->L.nbr_slots);
     sg_launch_nbr_search(g, ng, b.xs, b.ys, b.zs, b.hs, off, b.perm, key, ncnt, slots, st);
-    sg_launch_scan(ncnt, nbr_off, ng, nullptr, ng, scan, st);
-    sg_launch_nbr_check(g, nbr_off, ng, c->caps.nnz_cap, st);
-    sg_launch_nbr_compact(g, ng, b.xs, b.ys, b.zs, b.hs, off, ncnt, slots, nbr_off,
-                          c->at<int32_t>(c->L.nbr_idx), st);
+    sg_launch_nbr_finish(g, ng, b.xs, b.ys, b.zs, b.hs, off, ncnt, slots, c->caps.nnz_cap, scan,
+                         nbr_off, c->at<int32_t>(c->L.nbr_idx), st);
     c->end();
     sg_status r = c->check_launch("neighbour build");
     if (r != SG_OK) return r;
@@ -439,7 +440,6 @@ void grav_args(sg_ctx* c, bool pot, sg_grav_args& a) {
     a.sym_period = a.sym ? sym_period(c->n, a.sym) : 1;
     a.sym_chunk = a.sym ? sym_chunk(c->prm, c->n, a.sym) : 1;
     a.g = c->grid();
-    a.err = &c->grid()->err;
 }
 
 // Gravity preparations per Morton sort (1 when the kernel uses no order).
@@ -508,16 +508,22 @@ sg_status do_sph(sg_ctx* c) {
     return SG_OK;
 }
 
+// The parts of the total acceleration that exist (null: none).
+sg_acc_parts acc_parts(const sg_ctx* c) {
+    const bool sph = c->have_sph && c->ng > 0, grav = c->have_grav;
+    sg_acc_parts p;
+    p.asx = sph ? c->at<double>(c->L.asx) : nullptr;
+    p.asy = sph ? c->at<double>(c->L.asy) : nullptr;
+    p.asz = sph ? c->at<double>(c->L.asz) : nullptr;
+    p.gx = grav ? c->at<double>(c->L.gx) : nullptr;
+    p.gy = grav ? c->at<double>(c->L.gy) : nullptr;
+    p.gz = grav ? c->at<double>(c->L.gz) : nullptr;
+    return p;
+}
+
 void do_combine(sg_ctx* c) {
-    const bool sph = c->have_sph && c->ng > 0;
     c->begin(SG_ST_UPDATE);
-    sg_launch_combine(c->n, c->ng, sph ? c->at<double>(c->L.asx) : nullptr,
-                      sph ? c->at<double>(c->L.asy) : nullptr,
-                      sph ? c->at<double>(c->L.asz) : nullptr,
-                      c->have_grav ? c->at<double>(c->L.gx) : nullptr,
-                      c->have_grav ? c->at<double>(c->L.gy) : nullptr,
-                      c->have_grav ? c->at<double>(c->L.gz) : nullptr, c->s.ax, c->s.ay, c->s.az,
-                      c->st);
+    sg_launch_combine(c->n, c->ng, acc_parts(c), c->s.ax, c->s.ay, c->s.az, c->st);
     c->end();
 }
 
@@ -536,20 +542,22 @@ sg_status do_accel(sg_ctx* c, uint32_t flags) {
     return c->check_launch("combine");
 }
 
-sg_status do_kick_drift(sg_ctx* c, double dt, int phase) {
+// fused: the total acceleration is formed from its parts in the same pass.
+sg_status do_kick_drift(sg_ctx* c, double dt, int phase, bool fused = false) {
     if (!__builtin_isfinite(dt)) return c->fail(SG_EINVAL, "dt must be finite");
     const sg_state& s = c->s;
     double* vtx = c->at<double>(c->L.vtx);
     double* vty = c->at<double>(c->L.vty);
     double* vtz = c->at<double>(c->L.vtz);
     double* et = c->at<double>(c->L.et);
+    const sg_acc_parts parts = acc_parts(c);
     if (phase == SG_PREDICT) {
         if (c->predicted) return c->fail(SG_ESTATE, "SG_PREDICT twice without SG_CORRECT");
         if (!c->have_grav || !(c->have_sph || c->ng == 0))
             return c->fail(SG_ESTATE, "SG_PREDICT needs gravity and SPH forces at the current state");
         c->begin(SG_ST_UPDATE);
         sg_launch_predict(c->n, c->ng, dt, s.x, s.y, s.z, s.vx, s.vy, s.vz, s.e, s.ax, s.ay, s.az,
-                          s.dedt, vtx, vty, vtz, et, c->st);
+                          s.dedt, vtx, vty, vtz, et, fused ? &parts : nullptr, c->st);
         c->end();
         c->invalidate_positions();
         c->predicted = true;
@@ -560,7 +568,7 @@ sg_status do_kick_drift(sg_ctx* c, double dt, int phase) {
             return c->fail(SG_ESTATE, "SG_CORRECT needs gravity and SPH forces after SG_PREDICT");
         c->begin(SG_ST_UPDATE);
         sg_launch_correct(c->n, c->ng, dt, s.vx, s.vy, s.vz, s.e, vtx, vty, vtz, et, s.ax, s.ay,
-                          s.az, s.dedt, c->st);
+                          s.az, s.dedt, fused ? &parts : nullptr, c->st);
         c->end();
         c->predicted = false;
         c->have_sph = false;       // the SPH part was evaluated with the predicted velocities
@@ -576,7 +584,6 @@ sg_status do_step(sg_ctx* c, double dt, uint32_t flags) {
     if (flags & ~SG_POT) return c->fail(SG_EINVAL, "steps accept only SG_POT");
     if (!__builtin_isfinite(dt)) return c->fail(SG_EINVAL, "dt must be finite");
     if (c->predicted) return c->fail(SG_ESTATE, "step inside a predict/correct pair");
-    const uint32_t gflags = SG_GRAV | (flags & SG_POT);
     // forces at r(t): neighbours and density are reused from the previous
     // step's corrector (positions unchanged since), gravity likewise.
     if (!c->have_nbr && (r = do_build(c)) != SG_OK) return r;
@@ -584,8 +591,7 @@ sg_status do_step(sg_ctx* c, double dt, uint32_t flags) {
     if (!c->have_grav || ((flags & SG_POT) && !c->have_pot))
         if ((r = do_gravity(c, (flags & SG_POT) != 0)) != SG_OK) return r;
     if ((r = do_sph(c)) != SG_OK) return r;                 // predictor right-hand side
-    do_combine(c);
-    if ((r = do_kick_drift(c, dt, SG_PREDICT)) != SG_OK) return r;
+    if ((r = do_kick_drift(c, dt, SG_PREDICT, true)) != SG_OK) return r;
     // corrector right-hand side.  Gravity at the predicted positions and the
     // neighbour build -> density -> SPH forces chain are independent: with a
     // second stream, the chain runs there (forked from the context's stream
@@ -599,8 +605,10 @@ sg_status do_step(sg_ctx* c, double dt, uint32_t flags) {
     if (!c->st2 || c->prm.step_serial) {
         if ((r = do_build(c)) != SG_OK) return r;
         if ((r = do_density(c)) != SG_OK) return r;
-        if ((r = do_accel(c, gflags | SG_SPH)) != SG_OK) return r;
-        return do_kick_drift(c, dt, SG_CORRECT);
+        if ((r = do_gravity(c, (flags & SG_POT) != 0)) != SG_OK) return r;
+        if ((r = do_sph(c)) != SG_OK) return r;
+        c->accel_after_predict = true;
+        return do_kick_drift(c, dt, SG_CORRECT, true);
     }
     if (hipEventRecord(c->ev_fork, c->st) != hipSuccess ||
         hipStreamWaitEvent(c->st2, c->ev_fork, 0) != hipSuccess)
@@ -617,10 +625,8 @@ sg_status do_step(sg_ctx* c, double dt, uint32_t flags) {
          hipStreamWaitEvent(c->st, c->ev_join, 0) != hipSuccess) && rs == SG_OK)
         rs = c->fail(SG_EDEVICE, "step: join of the second stream failed");
     if (rs != SG_OK) return rs;
-    do_combine(c);
     c->accel_after_predict = true;
-    if ((r = c->check_launch("combine")) != SG_OK) return r;
-    return do_kick_drift(c, dt, SG_CORRECT);
+    return do_kick_drift(c, dt, SG_CORRECT, true);
 }
 
 sg_status do_diag(sg_ctx* c, double* d_out10) {
@@ -659,8 +665,7 @@ sg_status init_ctx(sg_ctx* c, const sg_params* prm, const sg_caps* caps, const l
         c->prof_n[k] = 0;
     }
     (void)hipGetLastError();            // drop a stale error of an earlier call
-    sg_launch_status_clear(c->grid(), c->st);
-    sg_launch_grid_reset(c->grid(), c->st);
+    sg_launch_status_clear(c->grid(), true, c->st);
     return c->check_launch("create");
 }
 
@@ -835,7 +840,7 @@ sg_status sg_bind_state(sg_ctx* c, int64_t n_gas, int64_t n_halo, const sg_state
     c->have_order = false;
     c->predicted = false;
     c->accel_after_predict = false;
-    sg_launch_status_clear(c->grid(), c->st);
+    sg_launch_status_clear(c->grid(), true, c->st);
     return c->check_launch("bind");
 }
 
@@ -1045,7 +1050,7 @@ sg_status sg_status_sync(sg_ctx* c, int64_t need[2]) {
         need[1] = g.need_nnz;
     }
     if (g.err == 0) return SG_OK;
-    sg_launch_status_clear(c->grid(), c->st);
+    sg_launch_status_clear(c->grid(), false, c->st);
     (void)hipStreamSynchronize(c->st);
     c->invalidate_positions();
     if (g.err & (SGE_NONFINITE | SGE_GNONFINITE))
@@ -1244,7 +1249,6 @@ sg_status ens_step(sg_ens* e, double dt, uint32_t flags) {
     sg_seg_launch_sph_state(e->seg, 0, e->st);
     c0->end();
     c0->begin(SG_ST_UPDATE);
-    sg_seg_launch_combine(e->seg, e->st);
     sg_seg_launch_predict(e->seg, dt, e->st);
     c0->end();
     if ((r = ens_launched(e, "predictor")) != SG_OK) return r;
@@ -1291,7 +1295,6 @@ sg_status ens_step(sg_ens* e, double dt, uint32_t flags) {
     }
     // corrector update, one launch each for all systems
     c0->begin(SG_ST_UPDATE);
-    sg_seg_launch_combine(e->seg, e->st);
     sg_seg_launch_correct(e->seg, dt, e->st);
     c0->end();
     for (sg_ctx* c : e->c) {

@@ -69,7 +69,8 @@ struct sg_grid_dev {
     unsigned long long lo[SG_MAXLEV][3];
     unsigned long long hi[SG_MAXLEV][3];
     unsigned long long hmax_bits[SG_MAXLEV];
-    unsigned long long npart[SG_MAXLEV];
+    unsigned long long cnt[SG_MAXLEV];
+    uint32_t ticket, pad3;             // workgroups that have ended their part
     // finished grid
     double L0;
     double L[SG_MAXLEV], invL[SG_MAXLEV];
@@ -77,6 +78,7 @@ struct sg_grid_dev {
     int64_t dim[SG_MAXLEV][3];
     int64_t base[SG_MAXLEV];
     int64_t ncell[SG_MAXLEV];
+    unsigned long long npart[SG_MAXLEV];
     double hmaxlev[SG_MAXLEV];
     int32_t nlev, pad0;
     int64_t M;
@@ -111,13 +113,14 @@ void sg_launch_scan(const int32_t* in, int64_t* out, int64_t n_host, const int64
                     int64_t cap, void* tmp, hipStream_t st);
 
 // Gas sort chain.
-void sg_launch_grid_reset(sg_grid_dev* g, hipStream_t st);   // keeps the error word
-void sg_launch_status_clear(sg_grid_dev* g, hipStream_t st);
-void sg_launch_grid_reduce(const double* x, const double* y, const double* z, const double* h,
-                           int64_t ng, sg_grid_dev* g, hipStream_t st);
-void sg_launch_grid_finish(sg_grid_dev* g, int64_t cell_cap, int cell_scale_log2, hipStream_t st);
-void sg_launch_cells_clear(sg_grid_dev* g, int32_t* count, unsigned long long* hmax,
-                           int64_t cell_cap, hipStream_t st);
+// Clear the error word; record: also the grid record and the reduction
+// inputs (a newly bound state).
+void sg_launch_status_clear(sg_grid_dev* g, bool record, hipStream_t st);
+// Grid rule (minimum h, level bounds, cell sides and offsets) and cleared
+// cell counts and maxima.
+void sg_launch_grid(const double* x, const double* y, const double* z, const double* h, int64_t ng,
+                    sg_grid_dev* g, int32_t* count, unsigned long long* hmax, int64_t cell_cap,
+                    int cell_scale_log2, hipStream_t st);
 // Cell keys, per-cell counts and max h; also each particle's record
 // (x, y, z, h, m) in particle order into pin [ng] (scratch the gather reads).
 struct sg_prec;
@@ -129,11 +132,19 @@ void sg_launch_keys_count(const double* x, const double* y, const double* z, con
 // radix sort of the keys with 10-bit digits, enough passes for keys below
 // cell_cap; tmp: sg_morton_tmp_bytes(ng) bytes.
 int sg_gas_radix_passes(int64_t cell_cap);
-void sg_launch_gas_order(const int32_t* key, int64_t ng, int64_t cell_cap, void* tmp,
+// Returns the keys in sorted order (in tmp).
+const uint32_t* sg_launch_gas_order(const int32_t* key, int64_t ng, int64_t cell_cap, void* tmp,
                          int32_t* perm, hipStream_t st);
 void sg_launch_gather_gas(const int32_t* perm, int64_t ng, const sg_grid_dev* g,
                           const sg_prec* pin, double* xs, double* ys, double* zs, double* hs,
                           double* ms, sg_prec* prec, hipStream_t st);
+// The gather with the cell offsets from the sorted keys beside it, for sizes
+// where that beats the scan of the counts.
+bool sg_offsets_by_bisection(int64_t ng, int64_t cell_cap);
+void sg_launch_gather_gas_off(const int32_t* perm, int64_t ng, const sg_grid_dev* g,
+                              const sg_prec* pin, double* xs, double* ys, double* zs, double* hs,
+                              double* ms, sg_prec* prec, const uint32_t* keys, int64_t* off,
+                              int64_t cell_cap, hipStream_t st);
 
 // Neighbour lists.
 // Neighbour search: per-target slots of fixed length (sg_nbr_slot_bytes),
@@ -143,12 +154,12 @@ void sg_launch_nbr_search(const sg_grid_dev* g, int64_t ng, const double* xs, co
                           const double* zs, const double* hs, const int64_t* off,
                           const int32_t* perm, const int32_t* key, int32_t* cnt, int32_t* slots,
                           hipStream_t st);
-void sg_launch_nbr_check(sg_grid_dev* g, const int64_t* nbr_off, int64_t ng, int64_t nnz_cap,
-                         hipStream_t st);
-void sg_launch_nbr_compact(const sg_grid_dev* g, int64_t ng, const double* xs, const double* ys,
-                           const double* zs, const double* hs, const int64_t* off,
-                           const int32_t* cnt, const int32_t* slots, const int64_t* nbr_off,
-                           int32_t* nbr_idx, hipStream_t st);
+// CSR offsets from the counts, the capacity check and the copy into the rows
+// (scan: scratch of sg_scan_tmp_bytes(ng)).
+void sg_launch_nbr_finish(sg_grid_dev* g, int64_t ng, const double* xs, const double* ys,
+                          const double* zs, const double* hs, const int64_t* off,
+                          const int32_t* cnt, const int32_t* slots, int64_t nnz_cap, void* scan,
+                          int64_t* nbr_off, int32_t* nbr_idx, hipStream_t st);
 
 // SPH.  Per-particle data in sorted-slot order is packed into one record
 // per particle, so a neighbour gather touches one or two cache lines.
@@ -214,14 +225,14 @@ struct sg_grav_args {
                                         // one-sided kernel alone
     int64_t sym_chunk, sym_period;      // tiles per workgroup (a multiple of the period), tiles
                                         // per rounding of the target-side sums
-    sg_grid_dev* g;                     // scales and the device's choice (sym != 0)
-    uint32_t* err;                      // device error word (non-finite positions)
+    sg_grid_dev* g;                     // error word (non-finite positions), scales and choice
 };
 size_t sg_grav_sorted_bytes(int64_t n);
 size_t sg_grav_sym_bytes(int64_t n);
 // FP32C: Morton-ordered copies of x, y, z, m and the boxes of their
 // 64-particle runs (needs a.order and a.sorted); a non-finite position
-// sets SGE_GNONFINITE in *a.err.
+// sets SGE_GNONFINITE in a.g's error word, and the Morton box is reset for
+// the next order.
 // Both return -1 (and launch nothing) when a required pointer is missing.
 int sg_launch_grav_sorted(const sg_grav_args& a, hipStream_t st);
 int sg_launch_gravity(const sg_grav_args& a, hipStream_t st);
@@ -343,8 +354,7 @@ int64_t sg_radix_tiles(int64_t n);
 int64_t sg_scan_tiles(int64_t cap);          // blocks of one sg_launch_scan pass
 int64_t sg_cells_clear_blocks(int64_t cell_cap);
 // Stages (each one launch, or a few, for all systems).
-
-void sg_seg_launch_combine(const sg_seg& s, hipStream_t st);
+// (predictor and corrector also form the total acceleration from its parts)
 void sg_seg_launch_predict(const sg_seg& s, double dt, hipStream_t st);
 void sg_seg_launch_correct(const sg_seg& s, double dt, hipStream_t st);
 void sg_seg_launch_morton_order(const sg_seg& s, hipStream_t st);
@@ -368,18 +378,23 @@ int64_t sg_compact_blocks(int64_t ng);
 void sg_seg_launch_density(const sg_seg& s, hipStream_t st);
 void sg_seg_launch_sph_state(const sg_seg& s, int predicted, hipStream_t st);
 
-// Update and diagnostics.
+// Update and diagnostics.  Parts of the total acceleration (null: that part
+// does not exist); predictor and corrector given them also write their sum
+// to ax, ay, az, as sg_launch_combine does.
+struct sg_acc_parts {
+    const double *asx, *asy, *asz, *gx, *gy, *gz;
+};
 void sg_launch_predict(int64_t n, int64_t ng, double dt, double* x, double* y, double* z,
                        const double* vx, const double* vy, const double* vz, const double* e,
-                       const double* ax, const double* ay, const double* az, const double* dedt,
-                       double* vtx, double* vty, double* vtz, double* et, hipStream_t st);
+                       double* ax, double* ay, double* az, const double* dedt, double* vtx,
+                       double* vty, double* vtz, double* et, const sg_acc_parts* parts,
+                       hipStream_t st);
 void sg_launch_correct(int64_t n, int64_t ng, double dt, double* vx, double* vy, double* vz,
                        double* e, const double* vtx, const double* vty, const double* vtz,
-                       const double* et, const double* ax, const double* ay, const double* az,
-                       const double* dedt, hipStream_t st);
-void sg_launch_combine(int64_t n, int64_t ng, const double* asx, const double* asy,
-                       const double* asz, const double* gx, const double* gy, const double* gz,
-                       double* ax, double* ay, double* az, hipStream_t st);
+                       const double* et, double* ax, double* ay, double* az, const double* dedt,
+                       const sg_acc_parts* parts, hipStream_t st);
+void sg_launch_combine(int64_t n, int64_t ng, const sg_acc_parts& parts, double* ax, double* ay,
+                       double* az, hipStream_t st);
 size_t sg_diag_tmp_bytes();
 void sg_launch_diagnostics(int64_t n, int64_t ng, const double* x, const double* y,
                            const double* z, const double* vx, const double* vy,

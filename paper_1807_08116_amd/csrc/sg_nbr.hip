@@ -400,22 +400,22 @@ __global__ __launch_bounds__(kBlock) void k_nbr_search(
     nbr_search_wave<NT>(g, ng, xs, ys, zs, hs, off, perm, key, cnt, slots, w);
 }
 
-// Move every target's slot to its CSR row (or search again into the row
-// when the slot was too short).  Wavefront w takes targets
-// kCompact w .. kCompact w + kCompact - 1, 64 / kCompact lanes each; a target
-// with more than kSlot hits is searched again by the whole wavefront.
+// Move every target's slot to its CSR row, which starts at nbr_off[s - off0]
+// (or search again into the row when the slot was too short).  Wavefront w
+// takes targets kCompact w .. kCompact w + kCompact - 1, 64 / kCompact lanes
+// each; a target with more than kSlot hits is searched again by the whole
+// wavefront.
 // Targets per wavefront at 1M gas (about 41 hits each), neighbour stage:
 // 2: 1.23 ms, 4: 1.17-1.19, 8: 1.14-1.16, 16: 1.18, 32: 1.31.
 constexpr int kCompact = 8;
 constexpr int kCompactLanes = 64 / kCompact;
 
-__device__ __attribute__((always_inline)) inline void nbr_compact_wave(
+__device__ __attribute__((always_inline)) inline void nbr_copy_wave(
     const sg_grid_dev* __restrict__ g, int64_t ng, const double* __restrict__ xs,
     const double* __restrict__ ys, const double* __restrict__ zs, const double* __restrict__ hs,
     const int64_t* __restrict__ off, const int32_t* __restrict__ cnt,
-    const int32_t* __restrict__ slots, const int64_t* __restrict__ nbr_off,
+    const int32_t* __restrict__ slots, const int64_t* nbr_off, int64_t off0,
     int32_t* __restrict__ nbr_idx, int64_t w) {
-    if (g->err & (SGE_SORT_FATAL | SGE_NNZ)) return;
     const unsigned lane = threadIdx.x & 63;
     const int64_t s0 = w * kCompact;
     if (s0 >= ng) return;
@@ -423,7 +423,7 @@ __device__ __attribute__((always_inline)) inline void nbr_compact_wave(
     const int64_t c = s < ng ? cnt[s] : 0;
     if (c <= kSlot) {
         const int32_t* mine = slots + s * kSlot;
-        const int64_t to = nbr_off[s < ng ? s : 0];
+        const int64_t to = nbr_off[(s < ng ? s : s0) - off0];
         // four entries in flight per lane, then the rest
         int64_t k = lane % kCompactLanes;
         for (; k + 3 * kCompactLanes < c; k += 4 * kCompactLanes) {
@@ -439,7 +439,7 @@ __device__ __attribute__((always_inline)) inline void nbr_compact_wave(
     for (int j = 0; j < kCompact; ++j) {
         const int64_t sj = s0 + j;
         if (sj >= ng) break;
-        const int64_t to = nbr_off[sj];
+        const int64_t to = nbr_off[sj - off0];
         if (cnt[sj] <= kSlot) continue;
         int64_t q = 0;
         nbr_scan(g, ng, sj, lane, xs, ys, zs, hs, off,
@@ -450,19 +450,81 @@ __device__ __attribute__((always_inline)) inline void nbr_compact_wave(
     }
 }
 
+// Up to this many targets, a workgroup of the copy adds up the counts before
+// its own targets itself (at most 64 KB from L2) and writes their offsets:
+// no scan and no check of their own (three launches and one).  Stage: 1009
+// targets 31 -> 23 us, 4096 39 -> 33, 9001 56 -> 54.
+constexpr int64_t kOwnScan = 16384;
+
+__global__ __launch_bounds__(kBlock) void k_nbr_compact_own(
+    sg_grid_dev* __restrict__ g, int64_t ng, const double* __restrict__ xs,
+    const double* __restrict__ ys, const double* __restrict__ zs, const double* __restrict__ hs,
+    const int64_t* __restrict__ off, const int32_t* __restrict__ cnt,
+    const int32_t* __restrict__ slots, int64_t nnz_cap, int64_t* __restrict__ nbr_off,
+    int32_t* __restrict__ nbr_idx) {
+    constexpr int kPer = kWaves * kCompact;        // targets of a workgroup
+    __shared__ int64_t s_off[kPer + 1];
+    __shared__ int64_t s_w[kWaves];
+    if (g->err & SGE_SORT_FATAL) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) g->nnz = 0;
+        return;
+    }
+    const int tid = threadIdx.x;
+    const unsigned lane = tid & 63;
+    const int first = blockIdx.x * kPer;
+    int64_t sum = 0;
+    for (int k = tid; k < first; k += kBlock) sum += cnt[k];
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    if (lane == 0) s_w[tid >> 6] = sum;
+    __syncthreads();
+    if (tid < 64) {
+        int64_t base = 0;
+        for (int w = 0; w < kWaves; ++w) base += s_w[w];
+        const int64_t c = (int)lane < kPer && first + (int)lane < ng ? cnt[first + lane] : 0;
+        int64_t incl = c;
+        for (int o = 1; o < kPer; o <<= 1) {
+            const int64_t t = __shfl_up(incl, o, 64);
+            if ((int)lane >= o) incl += t;
+        }
+        if ((int)lane < kPer) {
+            s_off[lane] = base + incl - c;
+            if (first + (int)lane < ng) nbr_off[first + lane] = base + incl - c;
+            if ((int)lane == kPer - 1) s_off[kPer] = base + incl;
+        }
+    }
+    __syncthreads();
+    const int64_t end = s_off[kPer];
+    // the last workgroup knows the total
+    if (blockIdx.x == gridDim.x - 1 && tid == 0) {
+        nbr_off[ng] = end;
+        g->nnz = end;
+        if (end > nnz_cap) {
+            atomicOr(&g->err, SGE_NNZ);
+            g->need_nnz = end;
+        }
+    }
+    if (end > nnz_cap) return;                     // rows past the capacity are not written
+    nbr_copy_wave(g, ng, xs, ys, zs, hs, off, cnt, slots, s_off, first, nbr_idx,
+                  (int64_t)blockIdx.x * kWaves + (tid >> 6));
+}
+
 __global__ __launch_bounds__(kBlock) void k_nbr_compact(
     const sg_grid_dev* __restrict__ g, int64_t ng, const double* __restrict__ xs,
     const double* __restrict__ ys, const double* __restrict__ zs, const double* __restrict__ hs,
     const int64_t* __restrict__ off, const int32_t* __restrict__ cnt,
     const int32_t* __restrict__ slots, const int64_t* __restrict__ nbr_off,
     int32_t* __restrict__ nbr_idx) {
+    if (g->err & (SGE_SORT_FATAL | SGE_NNZ)) return;
     const int64_t w = (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6);
-    nbr_compact_wave(g, ng, xs, ys, zs, hs, off, cnt, slots, nbr_off, nbr_idx, w);
+    nbr_copy_wave(g, ng, xs, ys, zs, hs, off, cnt, slots, nbr_off, 0, nbr_idx, w);
 }
 
 __device__ inline void nbr_check_one(sg_grid_dev* g, const int64_t* __restrict__ nbr_off,
                                      int64_t ng, int64_t nnz_cap) {
-    if (g->err & SGE_SORT_FATAL) return;
+    if (g->err & SGE_SORT_FATAL) {
+        g->nnz = 0;
+        return;
+    }
     const int64_t nnz = nbr_off[ng];
     g->nnz = nnz;
     if (nnz > nnz_cap) {
@@ -503,8 +565,9 @@ __global__ __launch_bounds__(kBlock) void k_seg_nbr_compact(const sg_seg_sys* __
     int64_t lb;
     const sg_seg_sys& S = sys[sg_seg_find(pfx, nsys, blockIdx.x, &lb)];
     const sg_sph_bufs& b = S.sph;
-    nbr_compact_wave(S.g, S.ng, b.xs, b.ys, b.zs, b.hs, S.off, S.ncnt, S.slots, b.nbr_off,
-                     const_cast<int32_t*>(b.nbr_idx), lb * kWaves + (threadIdx.x >> 6));
+    if (S.g->err & (SGE_SORT_FATAL | SGE_NNZ)) return;
+    nbr_copy_wave(S.g, S.ng, b.xs, b.ys, b.zs, b.hs, S.off, S.ncnt, S.slots, b.nbr_off, 0,
+                  const_cast<int32_t*>(b.nbr_idx), lb * kWaves + (threadIdx.x >> 6));
 }
 
 inline unsigned waves_grid(int64_t n) {
@@ -587,16 +650,18 @@ void sg_launch_nbr_search(const sg_grid_dev* g, int64_t ng, const double* xs, co
     });
 }
 
-void sg_launch_nbr_check(sg_grid_dev* g, const int64_t* nbr_off, int64_t ng, int64_t nnz_cap,
-                         hipStream_t st) {
+void sg_launch_nbr_finish(sg_grid_dev* g, int64_t ng, const double* xs, const double* ys,
+                          const double* zs, const double* hs, const int64_t* off,
+                          const int32_t* cnt, const int32_t* slots, int64_t nnz_cap, void* scan,
+                          int64_t* nbr_off, int32_t* nbr_idx, hipStream_t st) {
+    const unsigned nb = waves_grid((ng + kCompact - 1) / kCompact);
+    if (ng <= kOwnScan) {
+        hipLaunchKernelGGL(k_nbr_compact_own, dim3(nb), dim3(kBlock), 0, st, g, ng, xs, ys, zs, hs,
+                           off, cnt, slots, nnz_cap, nbr_off, nbr_idx);
+        return;
+    }
+    sg_launch_scan(cnt, nbr_off, ng, nullptr, ng, scan, st);
     hipLaunchKernelGGL(k_nbr_check, dim3(1), dim3(64), 0, st, g, nbr_off, ng, nnz_cap);
-}
-
-void sg_launch_nbr_compact(const sg_grid_dev* g, int64_t ng, const double* xs, const double* ys,
-                           const double* zs, const double* hs, const int64_t* off,
-                           const int32_t* cnt, const int32_t* slots, const int64_t* nbr_off,
-                           int32_t* nbr_idx, hipStream_t st) {
-    hipLaunchKernelGGL(k_nbr_compact, dim3(waves_grid((ng + kCompact - 1) / kCompact)), dim3(kBlock),
-                       0, st, g, ng, xs, ys, zs,
-                       hs, off, cnt, slots, nbr_off, nbr_idx);
+    hipLaunchKernelGGL(k_nbr_compact, dim3(nb), dim3(kBlock), 0, st, g, ng, xs, ys, zs, hs, off,
+                       cnt, slots, nbr_off, nbr_idx);
 }

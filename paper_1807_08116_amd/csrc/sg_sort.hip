@@ -6,6 +6,8 @@
 //
 // Built with -ffp-contract=off: the key arithmetic must round exactly like
 // the plain FP64 definition of the grid.
+#include <type_traits>
+
 #include "sg_internal.h"
 
 namespace {
@@ -198,35 +200,46 @@ __device__ inline int level_of(double h, double L0) {
     return l;
 }
 
-__global__ void k_status_clear(sg_grid_dev* g) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
+// The grid's reduction inputs (lane l < SG_MAXLEV of a wavefront: level l).
+// They are reset when a state is bound, and by the pass that consumes them
+// (grid_finish_wave) for the next build, so a build needs no launch for it;
+// the gravity-order box likewise (gbox_reset_lane, after the Morton keys).
+__device__ inline void grid_inputs_reset(sg_grid_dev* g, int l) {
+    if (l == 0) g->hmin_bits = ~0ull;
+    if (l < SG_MAXLEV) {
+        for (int d = 0; d < 3; ++d) {
+            g->lo[l][d] = ~0ull;
+            g->hi[l][d] = 0ull;
+        }
+        g->hmax_bits[l] = 0ull;
+        g->cnt[l] = 0ull;
+    }
+}
+
+__global__ void k_status_clear(sg_grid_dev* g, int record) {
+    const int t = threadIdx.x;
+    if (t == 0) {
         g->err = 0;
         g->need_cells = 0;
         g->need_nnz = 0;
     }
-}
-
-__device__ inline void grid_reset_one(sg_grid_dev* g) {
-    int t = threadIdx.x;
+    if (!record) return;
     if (t == 0) {
-        g->hmin_bits = ~0ull;
         g->nnz = 0;
         g->M = 0;
         g->nlev = 0;
+        g->ticket = 0;
     }
     if (t < SG_MAXLEV) {
-        for (int d = 0; d < 3; ++d) {
-            g->lo[t][d] = ~0ull;
-            g->hi[t][d] = 0ull;
-        }
-        g->hmax_bits[t] = 0ull;
-        g->npart[t] = 0ull;
         g->ncell[t] = 0;
+        g->npart[t] = 0;
     }
-    // glo / ghi belong to the gravity preparation, which resets them itself
+    grid_inputs_reset(g, t);
+    if (t < 3) {
+        g->glo[t] = ~0ull;
+        g->ghi[t] = 0ull;
+    }
 }
-
-__global__ void k_grid_reset(sg_grid_dev* g) { grid_reset_one(g); }
 
 // Minimum h and validity of the gas state: a thread's items, then the
 // wavefront and workgroup minimum, one global atomic per workgroup.
@@ -258,12 +271,19 @@ __global__ __launch_bounds__(kBlock) void k_grid_hmin(const double* __restrict__
                                                       const double* __restrict__ y,
                                                       const double* __restrict__ z,
                                                       const double* __restrict__ h, int64_t ng,
-                                                      sg_grid_dev* g) {
+                                                      sg_grid_dev* g, int32_t* __restrict__ count,
+                                                      unsigned long long* __restrict__ hmax,
+                                                      int64_t nclear) {
     unsigned long long mn = ~0ull;
     bool bad = false;
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < ng;
-         i += (int64_t)gridDim.x * kBlock)
-        hmin_item(x, y, z, h, i, mn, bad);
+    const int64_t i0 = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int64_t stride = (int64_t)gridDim.x * kBlock;
+    for (int64_t i = i0; i < ng; i += stride) hmin_item(x, y, z, h, i, mn, bad);
+    // small cell tables are cleared whole here, before their size is known
+    for (int64_t k = i0; k < nclear; k += stride) {
+        count[k] = 0;
+        hmax[k] = 0ull;
+    }
     hmin_fold(mn, bad, g);
 }
 
@@ -329,86 +349,119 @@ __device__ inline void grid_levels_block(const double* __restrict__ x,
             atomicMax(&g->hi[t][d], s_hi[t][d]);
         }
         atomicMax(&g->hmax_bits[t], s_hmax[t]);
-        atomicAdd(&g->npart[t], s_cnt[t]);
+        atomicAdd(&g->cnt[t], s_cnt[t]);
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_grid_levels(const double* __restrict__ x,
-                                                        const double* __restrict__ y,
-                                                        const double* __restrict__ z,
-                                                        const double* __restrict__ h,
-                                                        int64_t ng, sg_grid_dev* g) {
-    const int64_t stride = (int64_t)gridDim.x * kBlock;
-    grid_levels_block(x, y, z, h, ng, g, (int64_t)blockIdx.x * kBlock, stride,
-                      (ng + stride - 1) / stride);
+// A value that other workgroups wrote by device-scope atomics.
+__device__ inline unsigned long long seen(unsigned long long* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Cell sides L[l] = L0 2^(l + cell_scale_log2) (powers of two); the level of
-// a particle depends on L0 only.
-__device__ inline void grid_finish_one(sg_grid_dev* g, int64_t cell_cap, double cell_scale) {
-    if (g->err & (SGE_NONFINITE | SGE_LEVELS)) {
-        g->M = 0;
+// a particle depends on L0 only.  One wavefront, lane l level l (the levels
+// one after the other on one thread took 7-12 us).
+__device__ inline void grid_finish_wave(sg_grid_dev* g, int64_t cell_cap, double cell_scale) {
+    const int l = threadIdx.x & 63;
+    const uint32_t err = __hip_atomic_load(&g->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const double hmin = sg_unord(seen(&g->hmin_bits));
+    const bool mine = l < SG_MAXLEV;
+    unsigned long long np = 0, hb = 0, lo[3] = {0, 0, 0}, hi[3] = {0, 0, 0};
+    if (mine) {
+        np = seen(&g->cnt[l]);
+        hb = seen(&g->hmax_bits[l]);
+        for (int d = 0; d < 3; ++d) {
+            lo[d] = seen(&g->lo[l][d]);
+            hi[d] = seen(&g->hi[l][d]);
+        }
+    }
+    grid_inputs_reset(g, l);
+    if (err & (SGE_NONFINITE | SGE_LEVELS)) {
+        if (mine) {
+            g->ncell[l] = 0;
+            g->npart[l] = 0;
+        }
+        if (l == 0) {
+            g->M = 0;
+            g->nlev = 0;
+        }
         return;
     }
-    const double hmin = sg_unord(g->hmin_bits);
     const double L0 = pow2_ceil(hmin * (2.0 + 0x1p-9));
-    g->L0 = L0;
-    int nlev = 0;
-    for (int l = 0; l < SG_MAXLEV; ++l)
-        if (g->npart[l]) nlev = l + 1;
-    g->nlev = nlev;
-    int64_t M = 0;
     double L = L0 * cell_scale;        // exact: cell_scale is 1/2, 1 or 2
-    for (int l = 0; l < SG_MAXLEV; ++l, L *= 2.0) {
-        g->L[l] = L;
-        g->invL[l] = 1.0 / L;          // exact: L is a power of two
-        g->base[l] = M;
-        g->hmaxlev[l] = g->npart[l] ? sg_unord(g->hmax_bits[l]) : 0.0;
-        if (l >= nlev || g->npart[l] == 0) {
-            g->ncell[l] = 0;
-            for (int d = 0; d < 3; ++d) {
-                g->dim[l][d] = 0;
-                g->org[l][d] = 0.0;
+    for (int k = 0; k < l && k < SG_MAXLEV; ++k) L *= 2.0;
+    const double inv = 1.0 / L;        // exact: L is a power of two
+    int64_t nc = np ? 1 : 0, dim[3] = {0, 0, 0};
+    double org[3] = {0.0, 0.0, 0.0};
+    bool bad = false;
+    if (np) {
+        for (int d = 0; d < 3 && !bad; ++d) {
+            const double plo = sg_unord(lo[d]), phi = sg_unord(hi[d]);
+            org[d] = floor(plo * inv) * L;
+            const double span = floor((phi - org[d]) * inv);
+            bad = !(span < 2147483646.0);
+            if (!bad) {
+                dim[d] = (int64_t)span + 1;
+                nc *= dim[d];
+                bad = nc > 2147483647ll;
             }
-            continue;
-        }
-        int64_t nc = 1;
-        for (int d = 0; d < 3; ++d) {
-            double lo = sg_unord(g->lo[l][d]), hi = sg_unord(g->hi[l][d]);
-            double o = floor(lo * g->invL[l]) * L;
-            g->org[l][d] = o;
-            double span = floor((hi - o) * g->invL[l]);
-            if (!(span < 2147483646.0)) {
-                atomicOr(&g->err, SGE_GRID);
-                g->M = 0;
-                return;
-            }
-            g->dim[l][d] = (int64_t)span + 1;
-            nc *= g->dim[l][d];
-            if (nc > 2147483647ll) {
-                atomicOr(&g->err, SGE_GRID);
-                g->M = 0;
-                return;
-            }
-        }
-        g->ncell[l] = nc;
-        M += nc;
-        if (M > 2147483647ll) {
-            atomicOr(&g->err, SGE_GRID);
-            g->M = 0;
-            return;
         }
     }
-    g->M = M;
+    const unsigned long long full = __ballot(np != 0);
+    if (__ballot(bad)) nc = 0;
+    int64_t incl = nc;
+    for (int o = 1; o < SG_MAXLEV; o <<= 1) {
+        const int64_t t = __shfl_up(incl, o, 64);
+        if (l >= o) incl += t;
+    }
+    const int64_t M = __shfl(incl, SG_MAXLEV - 1, 64);
+    if (mine) {
+        g->L[l] = L;
+        g->invL[l] = inv;
+        g->base[l] = incl - nc;
+        g->hmaxlev[l] = np ? sg_unord(hb) : 0.0;
+        g->npart[l] = np;
+        g->ncell[l] = nc;
+        for (int d = 0; d < 3; ++d) {
+            g->dim[l][d] = dim[d];
+            g->org[l][d] = org[d];
+        }
+    }
+    const bool none = __ballot(bad) != 0ull || M > 2147483647ll;
+    if (l != 0) return;
+    g->L0 = L0;
+    g->nlev = full ? 64 - __builtin_clzll(full) : 0;
+    g->M = none ? 0 : M;
+    if (none) {
+        atomicOr(&g->err, SGE_GRID);
+        return;
+    }
     if (M > cell_cap) {
         atomicOr(&g->err, SGE_CELLS);
         g->need_cells = M;
     }
 }
 
-__global__ void k_grid_finish(sg_grid_dev* g, int64_t cell_cap, double cell_scale) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    grid_finish_one(g, cell_cap, cell_scale);
+// Level bounds; the workgroup that ends last turns them into the grid.
+__global__ __launch_bounds__(kBlock) void k_grid_levels(const double* __restrict__ x,
+                                                        const double* __restrict__ y,
+                                                        const double* __restrict__ z,
+                                                        const double* __restrict__ h,
+                                                        int64_t ng, sg_grid_dev* g,
+                                                        int64_t cell_cap, double cell_scale) {
+    __shared__ int s_last;
+    const int64_t stride = (int64_t)gridDim.x * kBlock;
+    grid_levels_block(x, y, z, h, ng, g, (int64_t)blockIdx.x * kBlock, stride,
+                      (ng + stride - 1) / stride);
+    // this workgroup's atomics (the only data handed over) have reached
+    // memory before it draws its ticket
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) s_last = atomicAdd(&g->ticket, 1u) == gridDim.x - 1;
+    __syncthreads();
+    if (!s_last || threadIdx.x >= 64) return;
+    if (threadIdx.x == 0) atomicExch(&g->ticket, 0u);
+    grid_finish_wave(g, cell_cap, cell_scale);
 }
 
 __device__ inline void cells_clear_block(const sg_grid_dev* g, int32_t* __restrict__ count,
@@ -529,17 +582,39 @@ __global__ __launch_bounds__(kBlock) void k_gather_gas(
     gather_one(perm, s, pin, xs, ys, zs, hs, ms, prec);
 }
 
+// The same, and in the workgroups after the first nbg the cell offsets, by
+// bisection in the sorted keys (off[c] = particles with a key below c: what
+// the scan of the counts gives) beside the gather instead of in three
+// launches of a scan.
+__global__ __launch_bounds__(kBlock) void k_gather_gas_off(
+    const int32_t* __restrict__ perm, int64_t ng, const sg_grid_dev* g,
+    const sg_prec* __restrict__ pin, double* __restrict__ xs, double* __restrict__ ys,
+    double* __restrict__ zs, double* __restrict__ hs, double* __restrict__ ms,
+    sg_prec* __restrict__ prec, int nbg, const uint32_t* __restrict__ keys,
+    int64_t* __restrict__ off) {
+    if (g->err & SGE_SORT_FATAL) return;
+    if ((int)blockIdx.x < nbg) {
+        const int64_t s = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+        if (s < ng) gather_one(perm, s, pin, xs, ys, zs, hs, ms, prec);
+        return;
+    }
+    const int64_t M = g->M;
+    for (int64_t c = (int64_t)(blockIdx.x - nbg) * kBlock + threadIdx.x; c <= M;
+         c += (int64_t)(gridDim.x - nbg) * kBlock) {
+        int32_t lo = 0, hi = (int32_t)ng;
+        while (lo < hi) {
+            const int32_t mid = (int32_t)(((uint32_t)lo + (uint32_t)hi) >> 1);
+            if ((int64_t)keys[mid] < c) lo = mid + 1;
+            else hi = mid;
+        }
+        off[c] = lo;
+    }
+}
+
 // ------------------------------------------------------ Morton ordering --
 
 constexpr int kRadixItems = 16;
 constexpr int kRadixTile = kBlock * kRadixItems;
-
-__global__ void k_gbox_reset(sg_grid_dev* g) {
-    if (threadIdx.x < 3) {
-        g->glo[threadIdx.x] = ~0ull;
-        g->ghi[threadIdx.x] = 0ull;
-    }
-}
 
 // Fold one thread's bounds into the grid record: wavefront, then
 // workgroup, then one global atomic per bound and workgroup (same-address
@@ -608,8 +683,7 @@ __device__ inline uint32_t spread3(uint32_t v) {   // 10 bits -> every third bit
 
 __device__ inline void morton_key_one(const double* __restrict__ x, const double* __restrict__ y,
                                       const double* __restrict__ z, int64_t i,
-                                      const sg_grid_dev* g, uint32_t* __restrict__ keys,
-                                      int32_t* __restrict__ vals) {
+                                      const sg_grid_dev* g, uint32_t* __restrict__ keys) {
     double lo[3], ext = 0.0;
     for (int d = 0; d < 3; ++d) {
         lo[d] = sg_unord(g->glo[d]);
@@ -625,18 +699,16 @@ __device__ inline void morton_key_one(const double* __restrict__ x, const double
         c[d] = (uint32_t)v;
     }
     keys[i] = spread3(c[0]) | (spread3(c[1]) << 1) | (spread3(c[2]) << 2);
-    vals[i] = (int32_t)i;
 }
 
 __global__ __launch_bounds__(kBlock) void k_morton_keys(const double* __restrict__ x,
                                                         const double* __restrict__ y,
                                                         const double* __restrict__ z, int64_t n,
                                                         const sg_grid_dev* g,
-                                                        uint32_t* __restrict__ keys,
-                                                        int32_t* __restrict__ vals) {
+                                                        uint32_t* __restrict__ keys) {
     int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i >= n) return;
-    morton_key_one(x, y, z, i, g, keys, vals);
+    morton_key_one(x, y, z, i, g, keys);
 }
 
 // Morton keys have 30 bits: three passes of 10-bit digits.
@@ -644,20 +716,23 @@ constexpr int kRadixBits = 10;
 constexpr int kBuckets = 1 << kRadixBits;
 constexpr int kRadixPasses = 3;
 
-// Digit histogram of one tile, stored digit-major: hist[d * ntiles + tile].
+// Digit histogram of one tile of kBlock * ITEMS keys, digit-major
+// (hist[d * ntiles + tile], for a scan over it) or, ROWS, tile-major.
+template <int ITEMS = kRadixItems, bool ROWS = false>
 __device__ inline void radix_hist_tile(const uint32_t* __restrict__ keys, int64_t n, int shift,
                                        int64_t ntiles, int32_t* __restrict__ hist,
                                        int64_t tile) {
     __shared__ int32_t s_h[kBuckets];
     for (int t = threadIdx.x; t < kBuckets; t += kBlock) s_h[t] = 0;
     __syncthreads();
-    const int64_t base = tile * kRadixTile;
-    for (int k = 0; k < kRadixItems; ++k) {
+    const int64_t base = tile * (kBlock * ITEMS);
+    for (int k = 0; k < ITEMS; ++k) {
         int64_t i = base + k * kBlock + threadIdx.x;
         if (i < n) atomicAdd(&s_h[(keys[i] >> shift) & (kBuckets - 1)], 1);
     }
     __syncthreads();
-    for (int t = threadIdx.x; t < kBuckets; t += kBlock) hist[(int64_t)t * ntiles + tile] = s_h[t];
+    for (int t = threadIdx.x; t < kBuckets; t += kBlock)
+        hist[ROWS ? tile * kBuckets + t : (int64_t)t * ntiles + tile] = s_h[t];
 }
 
 __global__ __launch_bounds__(kBlock) void k_radix_hist(const uint32_t* __restrict__ keys,
@@ -671,11 +746,14 @@ __global__ __launch_bounds__(kBlock) void k_radix_hist(const uint32_t* __restric
 // lane of each (wave, digit) group publishes the group's size; after the
 // writes it adds that size to the digit's running count and clears its slot.
 // vin == nullptr stands for the values 0, 1, 2, .. (the element indices).
+// ROWS: first positions by digit in s_base (LDS) instead of offs.
+template <int ITEMS = kRadixItems, bool ROWS = false>
 __device__ inline void radix_scatter_tile(const uint32_t* __restrict__ kin,
                                           const int32_t* __restrict__ vin, int64_t n, int shift,
                                           int64_t ntiles, const int64_t* __restrict__ offs,
                                           uint32_t* __restrict__ kout,
-                                          int32_t* __restrict__ vout, int64_t tile) {
+                                          int32_t* __restrict__ vout, int64_t tile,
+                                          const int32_t* s_base = nullptr) {
     // a (wave, digit) group of one chunk has at most 64 members: one byte
     // each keeps the workgroup's LDS at 8 KB, small enough to find room on
     // CUs that a persistent gravity kernel mostly fills
@@ -687,9 +765,10 @@ __device__ inline void radix_scatter_tile(const uint32_t* __restrict__ kin,
         for (int w = 0; w < kBlock / 64; ++w) s_w[w][t] = 0;
     }
     __syncthreads();
-    const int64_t base = tile * kRadixTile;
-    for (int k = 0; k < kRadixItems; ++k) {
+    const int64_t base = tile * (kBlock * ITEMS);
+    for (int k = 0; k < ITEMS; ++k) {
         const int64_t i = base + k * kBlock + threadIdx.x;
+        if (ROWS && base + k * kBlock >= n) break;
         const bool valid = i < n;
         const uint32_t key = valid ? kin[i] : 0u;
         const int32_t val = valid ? (vin ? vin[i] : (int32_t)i) : 0;
@@ -707,7 +786,8 @@ __device__ inline void radix_scatter_tile(const uint32_t* __restrict__ kin,
         if (valid) {
             int32_t pre = 0;
             for (int w = 0; w < wave; ++w) pre += s_w[w][d];
-            const int64_t dest = offs[(int64_t)d * ntiles + tile] + s_run[d] + pre + r;
+            const int64_t first = ROWS ? (int64_t)s_base[d] : offs[(int64_t)d * ntiles + tile];
+            const int64_t dest = first + s_run[d] + pre + r;
             kout[dest] = key;
             vout[dest] = val;
         }
@@ -727,19 +807,67 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(
     radix_scatter_tile(kin, vin, n, shift, ntiles, offs, kout, vout, blockIdx.x);
 }
 
+// One pass in two launches, for up to kRowTiles tiles: the histograms are
+// stored tile after tile, and every workgroup of the scatter adds up the rows
+// itself (4 KB a tile from L2; four digits a lane) instead of three launches
+// of a scan: at 8192 keys a pass took 30 us, of which the scan 10 and the
+// scatter's 16 rounds 18.  Tiles shrink with n to fewer rounds of more
+// workgroups.  With the launches saved by k_grid_levels (which finishes the
+// grid), k_grid_hmin (which clears small tables) and k_gather_gas_off, the
+// sort stage went from 73 to 37 us at 1009 gas particles, 107 to 54 at 9001,
+// 136 to 79 at 65536, 198 to 136 at 131071 and 243 to 208 at 262144.
+constexpr int64_t kRowTiles = 64;
+template <int ITEMS>
+__global__ __launch_bounds__(kBlock) void k_radix_hist_rows(const uint32_t* __restrict__ keys,
+                                                            int64_t n, int shift,
+                                                            int32_t* __restrict__ hist) {
+    radix_hist_tile<ITEMS, true>(keys, n, shift, 0, hist, blockIdx.x);
+}
+
+template <int ITEMS>
+__global__ __launch_bounds__(kBlock) void k_radix_scatter_rows(
+    const uint32_t* __restrict__ kin, const int32_t* __restrict__ vin, int64_t n, int shift,
+    int ntiles, const int32_t* __restrict__ hist, uint32_t* __restrict__ kout,
+    int32_t* __restrict__ vout) {
+    __shared__ int32_t s_base[kBuckets];
+    __shared__ int32_t s_w[kBlock / 64];
+    const int tile = blockIdx.x, tid = threadIdx.x;
+    const int4* row = reinterpret_cast<const int4*>(hist) + tid;
+    int4 tot = make_int4(0, 0, 0, 0), pre = tot;
+#pragma unroll 8
+    for (int t = 0; t < ntiles; ++t) {
+        const int4 v = row[t * (kBuckets / 4)];
+        const int m = t < tile ? -1 : 0;
+        tot.x += v.x;
+        tot.y += v.y;
+        tot.z += v.z;
+        tot.w += v.w;
+        pre.x += v.x & m;
+        pre.y += v.y & m;
+        pre.z += v.z & m;
+        pre.w += v.w & m;
+    }
+    const int32_t sum = tot.x + tot.y + tot.z + tot.w;
+    int32_t incl = sum;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int32_t t = __shfl_up(incl, o, 64);
+        if (lane_id() >= (unsigned)o) incl += t;
+    }
+    if (lane_id() == 63) s_w[tid >> 6] = incl;
+    __syncthreads();
+    int32_t first = incl - sum;
+    for (int w = 0; w < tid >> 6; ++w) first += s_w[w];
+    s_base[4 * tid] = first + pre.x;
+    s_base[4 * tid + 1] = first + tot.x + pre.y;
+    s_base[4 * tid + 2] = first + tot.x + tot.y + pre.z;
+    s_base[4 * tid + 3] = first + tot.x + tot.y + tot.z + pre.w;
+    // (radix_scatter_tile synchronises before it reads them)
+    radix_scatter_tile<ITEMS, true>(kin, vin, n, shift, ntiles, nullptr, kout, vout, tile, s_base);
+}
+
 // ---------------------------------------- Morton order, all systems at once --
 // (see sg_seg in sg_internal.h).  The same stable order as the per-system
 // sort: the same keys, digits and stable scatter.
-
-__global__ void k_seg_gbox_reset(const sg_seg_sys* __restrict__ sys, int nsys) {
-    for (int k = threadIdx.x; k < nsys; k += blockDim.x) {
-        sg_grid_dev* g = sys[k].g;
-        for (int d = 0; d < 3; ++d) {
-            g->glo[d] = ~0ull;
-            g->ghi[d] = 0ull;
-        }
-    }
-}
 
 __global__ __launch_bounds__(kBlock) void k_seg_gbox(const sg_seg_sys* __restrict__ sys,
                                                      const int64_t* __restrict__ pfx, int nsys) {
@@ -758,7 +886,7 @@ __global__ __launch_bounds__(kBlock) void k_seg_morton_keys(const sg_seg_sys* __
     int64_t lb;
     const sg_seg_sys& S = sys[sg_seg_find(pfx, nsys, blockIdx.x, &lb)];
     const int64_t i = lb * kBlock + threadIdx.x;
-    if (i < S.n) morton_key_one(S.x, S.y, S.z, i, S.g, S.mk0, S.mv0);
+    if (i < S.n) morton_key_one(S.x, S.y, S.z, i, S.g, S.mk0);
 }
 
 // pass p reads buffer p & 1 and writes the other one; the last pass writes
@@ -778,7 +906,7 @@ __global__ __launch_bounds__(kBlock) void k_seg_radix_scatter(const sg_seg_sys* 
     const sg_seg_sys& S = sys[sg_seg_find(pfx, nsys, blockIdx.x, &tile)];
     const bool odd = pass & 1;
     int32_t* vout = pass == kRadixPasses - 1 ? S.order : (odd ? S.mv0 : S.mv1);
-    radix_scatter_tile(odd ? S.mk1 : S.mk0, odd ? S.mv1 : S.mv0, S.n, kRadixBits * pass,
+    radix_scatter_tile(odd ? S.mk1 : S.mk0, pass == 0 ? nullptr : (odd ? S.mv1 : S.mv0), S.n, kRadixBits * pass,
                        S.ntiles, S.moffs, odd ? S.mk0 : S.mk1, vout, tile);
 }
 
@@ -835,11 +963,6 @@ __global__ __launch_bounds__(kSegScanBlock) void k_seg_scan_hist(const sg_seg_sy
 // (see sg_seg in sg_internal.h): the per-system kernels' bodies; a system
 // without gas is skipped, as the per-system build does.
 
-__global__ void k_seg_grid_reset(const sg_seg_sys* __restrict__ sys) {
-    const sg_seg_sys& S = sys[blockIdx.x];
-    if (S.ng > 0) grid_reset_one(S.g);
-}
-
 __global__ __launch_bounds__(kBlock) void k_seg_grid_hmin(const sg_seg_sys* __restrict__ sys,
                                                           const int64_t* __restrict__ pfx,
                                                           int nsys) {
@@ -860,9 +983,9 @@ __global__ __launch_bounds__(kBlock) void k_seg_grid_levels(const sg_seg_sys* __
     grid_levels_block(S.x, S.y, S.z, S.h, S.ng, S.g, lb * kBlock, 0, 1);
 }
 
-__global__ void k_seg_grid_finish(const sg_seg_sys* __restrict__ sys, int nsys) {
-    for (int k = threadIdx.x; k < nsys; k += blockDim.x)
-        if (sys[k].ng > 0) grid_finish_one(sys[k].g, sys[k].cell_cap, sys[k].cell_scale);
+__global__ void k_seg_grid_finish(const sg_seg_sys* __restrict__ sys) {
+    const sg_seg_sys& S = sys[blockIdx.x];
+    if (S.ng > 0) grid_finish_wave(S.g, S.cell_cap, S.cell_scale);
 }
 
 __global__ __launch_bounds__(kBlock) void k_seg_cells_clear(const sg_seg_sys* __restrict__ sys,
@@ -1003,32 +1126,31 @@ void sg_launch_scan(const int32_t* in, int64_t* out, int64_t n_host, const int64
                        bsum);
 }
 
-void sg_launch_grid_reset(sg_grid_dev* g, hipStream_t st) {
-    hipLaunchKernelGGL(k_grid_reset, dim3(1), dim3(64), 0, st, g);
+void sg_launch_status_clear(sg_grid_dev* g, bool record, hipStream_t st) {
+    hipLaunchKernelGGL(k_status_clear, dim3(1), dim3(64), 0, st, g, record ? 1 : 0);
 }
 
-void sg_launch_status_clear(sg_grid_dev* g, hipStream_t st) {
-    hipLaunchKernelGGL(k_status_clear, dim3(1), dim3(64), 0, st, g);
-}
+// Whole cell tables of up to this many cells are cleared beside the minimum
+// h (12 bytes a cell, a few us at most) instead of by a launch of their own.
+constexpr int64_t kClearWhole = 1 << 20;
 
-void sg_launch_grid_reduce(const double* x, const double* y, const double* z, const double* h,
-                           int64_t ng, sg_grid_dev* g, hipStream_t st) {
+void sg_launch_grid(const double* x, const double* y, const double* z, const double* h, int64_t ng,
+                    sg_grid_dev* g, int32_t* count, unsigned long long* hmax, int64_t cell_cap,
+                    int cell_scale_log2, hipStream_t st) {
     unsigned nb = grid_for(ng, kBlock);
     if (nb > 1024) nb = 1024;
-    hipLaunchKernelGGL(k_grid_hmin, dim3(nb), dim3(kBlock), 0, st, x, y, z, h, ng, g);
-    hipLaunchKernelGGL(k_grid_levels, dim3(nb), dim3(kBlock), 0, st, x, y, z, h, ng, g);
-}
-
-void sg_launch_grid_finish(sg_grid_dev* g, int64_t cell_cap, int cell_scale_log2, hipStream_t st) {
+    const bool whole = cell_cap <= kClearWhole;
+    unsigned nh = whole && grid_for(cell_cap, 4 * kBlock) > nb ? grid_for(cell_cap, 4 * kBlock) : nb;
+    if (nh > 1024) nh = 1024;
+    hipLaunchKernelGGL(k_grid_hmin, dim3(nh), dim3(kBlock), 0, st, x, y, z, h, ng, g, count, hmax,
+                       whole ? cell_cap : (int64_t)0);
     const double scale = cell_scale_log2 < 0 ? 0.5 : (cell_scale_log2 > 0 ? 2.0 : 1.0);
-    hipLaunchKernelGGL(k_grid_finish, dim3(1), dim3(64), 0, st, g, cell_cap, scale);
-}
-
-void sg_launch_cells_clear(sg_grid_dev* g, int32_t* count, unsigned long long* hmax,
-                           int64_t cell_cap, hipStream_t st) {
-    unsigned nb = grid_for(cell_cap, kBlock);
-    if (nb > 4096) nb = 4096;
-    hipLaunchKernelGGL(k_cells_clear, dim3(nb), dim3(kBlock), 0, st, g, count, hmax);
+    hipLaunchKernelGGL(k_grid_levels, dim3(nb), dim3(kBlock), 0, st, x, y, z, h, ng, g, cell_cap,
+                       scale);
+    if (whole) return;
+    unsigned nc = grid_for(cell_cap, kBlock);
+    if (nc > 4096) nc = 4096;
+    hipLaunchKernelGGL(k_cells_clear, dim3(nc), dim3(kBlock), 0, st, g, count, hmax);
 }
 
 void sg_launch_keys_count(const double* x, const double* y, const double* z, const double* h,
@@ -1044,6 +1166,22 @@ void sg_launch_gather_gas(const int32_t* perm, int64_t ng, const sg_grid_dev* g,
                           double* ms, sg_prec* prec, hipStream_t st) {
     hipLaunchKernelGGL(k_gather_gas, dim3(grid_for(ng, kBlock)), dim3(kBlock), 0, st, perm, ng,
                        g, pin, xs, ys, zs, hs, ms, prec);
+}
+
+// Bisection costs log2(N_g) dependent reads a cell, the scan three launches.
+bool sg_offsets_by_bisection(int64_t ng, int64_t cell_cap) {
+    return ng <= 65536 && cell_cap <= kClearWhole;
+}
+
+void sg_launch_gather_gas_off(const int32_t* perm, int64_t ng, const sg_grid_dev* g,
+                              const sg_prec* pin, double* xs, double* ys, double* zs, double* hs,
+                              double* ms, sg_prec* prec, const uint32_t* keys, int64_t* off,
+                              int64_t cell_cap, hipStream_t st) {
+    const unsigned nbg = grid_for(ng, kBlock);
+    unsigned nbc = grid_for(cell_cap + 1, kBlock);
+    if (nbc > 2048) nbc = 2048;
+    hipLaunchKernelGGL(k_gather_gas_off, dim3(nbg + nbc), dim3(kBlock), 0, st, perm, ng, g, pin,
+                       xs, ys, zs, hs, ms, prec, (int)nbg, keys, off);
 }
 
 // Workspace of the Morton order: two key/value buffers, the digit histogram
@@ -1099,10 +1237,9 @@ void sg_seg_launch_sort(const sg_seg& s, hipStream_t st) {
     const int64_t* png = s.pfx + SG_SEG_NG * (s.nsys + 1);
     const int64_t* pcl = s.pfx + SG_SEG_CELLS * (s.nsys + 1);
     const unsigned nbg = (unsigned)s.nblk[SG_SEG_NG];
-    hipLaunchKernelGGL(k_seg_grid_reset, dim3((unsigned)s.nsys), dim3(64), 0, st, s.sys);
     hipLaunchKernelGGL(k_seg_grid_hmin, dim3(nbg), dim3(kBlock), 0, st, s.sys, png, s.nsys);
     hipLaunchKernelGGL(k_seg_grid_levels, dim3(nbg), dim3(kBlock), 0, st, s.sys, png, s.nsys);
-    hipLaunchKernelGGL(k_seg_grid_finish, dim3(1), dim3(64), 0, st, s.sys, s.nsys);
+    hipLaunchKernelGGL(k_seg_grid_finish, dim3((unsigned)s.nsys), dim3(64), 0, st, s.sys);
     hipLaunchKernelGGL(k_seg_cells_clear, dim3((unsigned)s.nblk[SG_SEG_CELLS]), dim3(kBlock), 0, st,
                        s.sys, pcl, s.nsys);
     hipLaunchKernelGGL(k_seg_keys_count, dim3(nbg), dim3(kBlock), 0, st, s.sys, png, s.nsys);
@@ -1139,7 +1276,6 @@ void sg_seg_launch_morton_order(const sg_seg& s, hipStream_t st) {
     const int64_t* pn = s.pfx + SG_SEG_N * (s.nsys + 1);
     const int64_t* pt = s.pfx + SG_SEG_TILES * (s.nsys + 1);
     if (s.nblk[SG_SEG_N] == 0) return;
-    hipLaunchKernelGGL(k_seg_gbox_reset, dim3(1), dim3(64), 0, st, s.sys, s.nsys);
     hipLaunchKernelGGL(k_seg_gbox, dim3((unsigned)s.nblk[SG_SEG_N]), dim3(kBlock), 0, st, s.sys, pn,
                        s.nsys);
     hipLaunchKernelGGL(k_seg_morton_keys, dim3((unsigned)s.nblk[SG_SEG_N]), dim3(kBlock), 0, st,
@@ -1164,8 +1300,34 @@ int sg_gas_radix_passes(int64_t cell_cap) {
     return (bits + kRadixBits - 1) / kRadixBits;
 }
 
-void sg_launch_gas_order(const int32_t* key, int64_t ng, int64_t cell_cap, void* tmp,
-                         int32_t* perm, hipStream_t st) {
+// One stable pass over digit `shift` of n keys: two launches with rows of
+// histograms where kRowTiles tiles do (smaller tiles where the histogram
+// scratch, three rows for every 4096 keys, has room for their rows), else
+// histogram, scan and scatter.
+static void radix_pass(const uint32_t* kin, const int32_t* vin, int64_t n, int shift,
+                       int32_t* hist, int64_t* offs, void* scan_tmp, uint32_t* kout, int32_t* vout,
+                       hipStream_t st) {
+    auto rows = [&](auto items) {
+        constexpr int kItems = decltype(items)::value;
+        const unsigned nt = grid_for(n, kBlock * kItems);
+        hipLaunchKernelGGL((k_radix_hist_rows<kItems>), dim3(nt), dim3(kBlock), 0, st, kin, n,
+                           shift, hist);
+        hipLaunchKernelGGL((k_radix_scatter_rows<kItems>), dim3(nt), dim3(kBlock), 0, st, kin, vin,
+                           n, shift, (int)nt, hist, kout, vout);
+    };
+    if (n <= 3 * kBlock * 4) return rows(std::integral_constant<int, 4>());
+    if (n <= kRowTiles * kBlock * 8) return rows(std::integral_constant<int, 8>());
+    if (n <= kRowTiles * kBlock * 16) return rows(std::integral_constant<int, 16>());
+    const int64_t ntiles = sg_radix_tiles(n);
+    hipLaunchKernelGGL(k_radix_hist, dim3((unsigned)ntiles), dim3(kBlock), 0, st, kin, n, shift,
+                       ntiles, hist);
+    sg_launch_scan(hist, offs, kBuckets * ntiles, nullptr, kBuckets * ntiles, scan_tmp, st);
+    hipLaunchKernelGGL(k_radix_scatter, dim3((unsigned)ntiles), dim3(kBlock), 0, st, kin, vin, n,
+                       shift, ntiles, offs, kout, vout);
+}
+
+const uint32_t* sg_launch_gas_order(const int32_t* key, int64_t ng, int64_t cell_cap, void* tmp,
+                                    int32_t* perm, hipStream_t st) {
     uint32_t *k0, *k1;
     int32_t *v0, *v1, *hist;
     int64_t* offs;
@@ -1180,16 +1342,12 @@ void sg_launch_gas_order(const int32_t* key, int64_t ng, int64_t cell_cap, void*
     const uint32_t* kin = (const uint32_t*)key;        // keys are >= 0
     const int32_t* vin = nullptr;                        // ids 0 .. ng-1
     for (int pass = 0; pass < passes; ++pass) {
-        const int shift = kRadixBits * pass;
-        hipLaunchKernelGGL(k_radix_hist, dim3((unsigned)ntiles), dim3(kBlock), 0, st, kin, ng,
-                           shift, ntiles, hist);
-        sg_launch_scan(hist, offs, kBuckets * ntiles, nullptr, kBuckets * ntiles, scan_tmp, st);
         int32_t* vout = pass == passes - 1 ? perm : vb[pass & 1];
-        hipLaunchKernelGGL(k_radix_scatter, dim3((unsigned)ntiles), dim3(kBlock), 0, st, kin, vin,
-                           ng, shift, ntiles, offs, kb[pass & 1], vout);
+        radix_pass(kin, vin, ng, kRadixBits * pass, hist, offs, scan_tmp, kb[pass & 1], vout, st);
         kin = kb[pass & 1];
         vin = vb[pass & 1];
     }
+    return kin;
 }
 
 void sg_launch_morton_order(const double* x, const double* y, const double* z, int64_t n,
@@ -1202,20 +1360,15 @@ void sg_launch_morton_order(const double* x, const double* y, const double* z, i
     int32_t* hist = (int32_t*)(base + o_hist);
     int64_t* offs = (int64_t*)(base + o_offs);
     void* scan_tmp = base + o_scan;
-    const int64_t ntiles = (n + kRadixTile - 1) / kRadixTile;
     unsigned nb = grid_for(n, kBlock);
-    hipLaunchKernelGGL(k_gbox_reset, dim3(1), dim3(64), 0, st, g);
     hipLaunchKernelGGL(k_gbox, dim3(nb > 512 ? 512 : nb), dim3(kBlock), 0, st, x, y, z, n, g);
-    hipLaunchKernelGGL(k_morton_keys, dim3(nb), dim3(kBlock), 0, st, x, y, z, n, g, k[0], v[0]);
+    hipLaunchKernelGGL(k_morton_keys, dim3(nb), dim3(kBlock), 0, st, x, y, z, n, g, k[0]);
+    // the first pass takes the values 0 .. n-1 from the element indices
     int cur = 0;
     for (int pass = 0; pass < kRadixPasses; ++pass) {
-        const int shift = kRadixBits * pass;
-        hipLaunchKernelGGL(k_radix_hist, dim3((unsigned)ntiles), dim3(kBlock), 0, st, k[cur], n,
-                           shift, ntiles, hist);
-        sg_launch_scan(hist, offs, kBuckets * ntiles, nullptr, kBuckets * ntiles, scan_tmp, st);
         int32_t* vo = (pass == kRadixPasses - 1) ? order : v[cur ^ 1];
-        hipLaunchKernelGGL(k_radix_scatter, dim3((unsigned)ntiles), dim3(kBlock), 0, st, k[cur],
-                           v[cur], n, shift, ntiles, offs, k[cur ^ 1], vo);
+        radix_pass(k[cur], pass == 0 ? nullptr : v[cur], n, kRadixBits * pass, hist, offs, scan_tmp,
+                   k[cur ^ 1], vo, st);
         cur ^= 1;
     }
 }

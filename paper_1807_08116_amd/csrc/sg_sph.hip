@@ -162,12 +162,10 @@ __global__ __launch_bounds__(kBlock) void k_pack_ve(const sg_grid_dev* g, int64_
     if (i < ng) pack_ve_one(i, vx, vy, vz, e, ve);
 }
 
-// One record per slot of the packed state, with p / rho^2 and the sound
-// speed sqrt(gamma p / rho) from the ideal-gas law.
+// One record per slot of the state (v = vx, vy, vz, e of its particle), with
+// p / rho^2 and the sound speed sqrt(gamma p / rho) from the ideal-gas law.
 __device__ inline void sph_prep_one(const sg_sph_bufs& b, int64_t s, int precision,
-                                    double gamma) {
-    const int32_t i = b.perm[s];
-    const double4 v = reinterpret_cast<const double4*>(b.ve)[i];
+                                    double gamma, const double4& v) {
     const sg_prec q = b.prec[s];
     const double rho = b.rho_s[s];
     const double p = (gamma - 1.0) * rho * v.w;
@@ -198,7 +196,22 @@ __global__ __launch_bounds__(kBlock) void k_sph_prep(sg_sph_bufs b, const sg_gri
     if (g->err & (SGE_SORT_FATAL | SGE_NNZ)) return;
     const int64_t s = xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
     if (s >= ng) return;
-    sph_prep_one(b, s, precision, gamma);
+    sph_prep_one(b, s, precision, gamma, reinterpret_cast<const double4*>(b.ve)[b.perm[s]]);
+}
+
+// The same straight from the particle-order arrays, without the packing pass:
+// for sizes whose scattered reads stay in the caches, where its launch costs
+// more than they do.
+constexpr int64_t kPrepDirect = 65536;
+__global__ __launch_bounds__(kBlock) void k_sph_prep_direct(
+    sg_sph_bufs b, const sg_grid_dev* g, int64_t ng, int precision, double gamma,
+    const double* __restrict__ vx, const double* __restrict__ vy, const double* __restrict__ vz,
+    const double* __restrict__ e) {
+    if (g->err & (SGE_SORT_FATAL | SGE_NNZ)) return;
+    const int64_t s = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (s >= ng) return;
+    const int32_t i = b.perm[s];
+    sph_prep_one(b, s, precision, gamma, make_double4(vx[i], vy[i], vz[i], e[i]));
 }
 
 __device__ inline void sph_force_f64_lanes(const sg_sph_bufs& b, int64_t s, bool valid, int sub,
@@ -359,7 +372,8 @@ __global__ __launch_bounds__(kBlock) void k_seg_sph_prep(const sg_seg_sys* __res
     if (S.g->err & (SGE_SORT_FATAL | SGE_NNZ)) return;
     const int64_t s = lb * kBlock + threadIdx.x;
     if (s >= S.ng) return;
-    sph_prep_one(S.sph, s, SG_FP32C, S.gamma);
+    sph_prep_one(S.sph, s, SG_FP32C, S.gamma,
+                 reinterpret_cast<const double4*>(S.sph.ve)[S.sph.perm[s]]);
 }
 
 __global__ __launch_bounds__(kBlock) void k_seg_sph_force(const sg_seg_sys* __restrict__ sys,
@@ -453,6 +467,11 @@ void sg_launch_density(const sg_sph_bufs& b, const sg_grid_dev* g, int64_t ng, i
 void sg_launch_sph_prep(const sg_sph_bufs& b, const sg_grid_dev* g, int64_t ng, int precision,
                         double gamma, const double* vx, const double* vy, const double* vz,
                         const double* e, hipStream_t st) {
+    if (ng <= kPrepDirect) {
+        hipLaunchKernelGGL(k_sph_prep_direct, dim3(grid_for(ng)), dim3(kBlock), 0, st, b, g, ng,
+                           precision, gamma, vx, vy, vz, e);
+        return;
+    }
     hipLaunchKernelGGL(k_pack_ve, dim3(grid_for(ng)), dim3(kBlock), 0, st, g, ng, vx, vy, vz, e,
                        b.ve);
     hipLaunchKernelGGL(k_sph_prep, dim3(grid_for(ng)), dim3(kBlock), 0, st, b, g, ng, precision,

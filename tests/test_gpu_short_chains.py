@@ -1,0 +1,128 @@
+"""The launch-saving forms of the sort, list and record passes at the sizes
+where they hand over to the general ones: tiles of the two-launch radix pass
+(3072, 131072 and 262144 keys), offsets by bisection and records without
+packing (65536 particles), the copy that adds up its own offsets (16384), and
+cell tables cleared whole (2^20 cells).  Integers bit for bit."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def sg():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1807_08116_amd import sphgrav
+    sphgrav.lib()
+    return sphgrav
+
+
+def gas(ng, seed=3):
+    from paper_1807_08116_amd import ic
+    rng = np.random.default_rng(seed + ng)
+    p, m = ic.plummer(ng, 1.0, 0.1, rng)
+    r2 = np.sum(p * p, 1)
+    h = 0.55 * (np.pi / (3.0 * ng)) ** (1 / 3) * (1.0 + r2) ** (5 / 6) * rng.uniform(0.8, 1.25, ng)
+    v = rng.normal(0.0, 0.1, (3, ng))
+    return dict(ng=ng, x=p[:, 0].copy(), y=p[:, 1].copy(), z=p[:, 2].copy(), vx=v[0], vy=v[1],
+                vz=v[2], m=m, h=h, e=rng.uniform(0.04, 0.06, ng))
+
+
+def check_lists(sg, ctx, st):
+    import oracle as orc
+    s = orc.sort_gas(st["x"], st["y"], st["z"], st["h"])
+    soff, sidx = orc.rows_to_slots(s["perm"], *orc.nbrs(st["x"], st["y"], st["z"], st["h"]))
+    for what, ref in ((sg.SG_X_KEYS, s["key"]), (sg.SG_X_COUNTS, s["count"]),
+                      (sg.SG_X_OFFSETS, s["off"]), (sg.SG_X_HMAX, s["hmax"]),
+                      (sg.SG_X_PERM, s["perm"]), (sg.SG_X_NBR_OFF, soff), (sg.SG_X_NBR_IDX, sidx)):
+        np.testing.assert_array_equal(ctx.export(what), ref)
+
+
+@pytest.mark.parametrize("ng", [1024, 1025, 3072, 3073, 16384, 16385, 65536, 65537, 130561, 131072,
+                                131073, 262144, 262145])
+def test_sort_and_lists(sg, ng):
+    st = gas(ng)
+    eng = sg.Engine(st, precision=sg.SG_FP64)
+    eng.build_neighbors()
+    for _ in range(2):                     # the second build starts from what the first left
+        eng.ctx.build_neighbors()
+    eng.ctx.sync()
+    check_lists(sg, eng.ctx, st)
+    eng.ctx.close()
+
+
+@pytest.mark.parametrize("n", [1, 1024, 3072, 3073, 131072, 131073, 262144, 262145])
+def test_morton_order(sg, n):
+    st = gas(n)
+    st.update(ng=0, h=np.zeros(0), e=np.zeros(0))
+    eng = sg.Engine(st, precision=sg.SG_FP32C)
+    P = np.stack([st[f] for f in ("x", "y", "z")])
+    for shift in (0.0, 0.5):               # the box of the first order is not left in the second
+        if shift:
+            eng.dev["x"] *= shift
+            P[0] *= shift
+        eng.ctx.compute_accel(sg.SG_GRAV)
+        lo = P.min(axis=1)
+        ext = np.max(P.max(axis=1) - lo)
+        scale = 1024.0 / (ext * (1.0 + 2.0 ** -20)) if ext > 0 else 0.0
+        q = np.clip((P - lo[:, None]) * scale, 0.0, 1023.0).astype(np.uint64)
+        key = np.zeros(n, np.uint64)
+        for d in range(3):
+            for b in range(10):
+                key |= ((q[d] >> np.uint64(b)) & np.uint64(1)) << np.uint64(3 * b + d)
+        np.testing.assert_array_equal(eng.ctx.export(sg.SG_X_GORDER), np.argsort(key, kind="stable"))
+    eng.ctx.close()
+
+
+@pytest.mark.parametrize("ng", [16383, 16385, 65535, 65537])
+def test_density_and_forces(sg, ng):
+    import oracle as orc
+    from paper_1807_08116_amd import ic
+    st = gas(ng)
+    prm = ic.DEFAULT_PARAMS
+    off, idx = orc.nbrs(st["x"], st["y"], st["z"], st["h"])
+    rho = orc.density(st["x"], st["y"], st["z"], st["m"], st["h"], off, idx)
+    ref = orc.sph_force(*(st[f] for f in ("x", "y", "z", "vx", "vy", "vz", "m", "h")), rho, st["e"],
+                        prm["gamma"], prm["alpha"], prm["beta"], prm["eta"], off, idx)
+    for precision, tol in ((sg.SG_FP64, 1e-12), (sg.SG_FP32C, 1e-6)):
+        eng = sg.Engine(st, precision=precision)
+        eng.build_neighbors()
+        eng.ctx.compute_density()
+        eng.ctx.compute_accel(sg.SG_SPH)
+        eng.ctx.sync()
+        got = [eng.numpy(f) for f in ("ax", "ay", "az", "dedt")]
+        for a, b in zip(got + [eng.numpy("rho")], list(ref[:4]) + [rho]):
+            assert np.linalg.norm(a - b) < tol * np.linalg.norm(b)
+        eng.ctx.close()
+
+
+@pytest.mark.parametrize("ng", [2000, 16384, 20000])
+def test_overflow_and_bad_input_then_recover(sg, ng):
+    st = gas(ng)
+    caps = sg.default_caps(ng, 0, nnz_cap=ng)
+    eng = sg.Engine(st, precision=sg.SG_FP64, caps=caps)
+    eng.ctx.build_neighbors()
+    with pytest.raises(sg.SGError) as e:
+        eng.ctx.sync()
+    assert e.value.code == sg.SG_ECAPACITY and e.value.need[1] > ng
+    need = e.value.need[1]
+    eng.ctx.close()
+    eng = sg.Engine(st, precision=sg.SG_FP64, caps=sg.default_caps(ng, 0, nnz_cap=need))
+    x = float(eng.dev["x"][7])
+    h = float(eng.dev["h"][9])
+    for field, bad, good, k, code in (("x", np.inf, x, 7, sg.SG_ENONFINITE),
+                                      ("h", 1e9, h, 9, sg.SG_ERANGE),
+                                      ("h", -1.0, h, 9, sg.SG_ENONFINITE)):
+        eng.dev[field][k] = bad
+        eng.ctx.build_neighbors()
+        with pytest.raises(sg.SGError) as e:
+            eng.ctx.sync()
+        assert e.value.code == code
+        assert eng.ctx.export(sg.SG_X_NBR_IDX).size == 0
+        eng.dev[field][k] = good
+        eng.ctx.build_neighbors()
+        eng.ctx.sync()
+        check_lists(sg, eng.ctx, st)
+    eng.ctx.close()
