@@ -89,10 +89,10 @@ layout make_layout(const sg_params* p, const sg_caps* c) {
     L.scan = take(sg_scan_tmp_bytes(C > ng + 1 ? C : ng + 1));
     size_t* f64s[] = {&L.xs, &L.ys, &L.zs, &L.hs, &L.ms, &L.rho_s};
     for (size_t* q : f64s) *q = take(8 * ng);
-    L.prec = take(sizeof(sg_prec) * ng);
+    L.prec = take((f32 ? sizeof(sg_prec32) : sizeof(sg_prec)) * ng);
     // FP64 force records, also the time-step rule's; between uses the sort
     // borrows the buffer for its particle-order records (64 of 96 bytes)
-    L.f64 = take(sizeof(sg_frec64) * ng);
+    L.f64 = take((sizeof(sg_frec64) + sizeof(sg_frec64b)) * ng);
     L.f32 = take(f32 ? sizeof(sg_frec32) * ng : 0);
     L.ncnt = take(4 * ng);
     L.nbr_off = take(8 * (ng + 1));
@@ -268,6 +268,7 @@ struct sg_ctx {
         b.rho_s = at<double>(L.rho_s);
         b.prec = at<sg_prec>(L.prec);
         b.f64 = at<sg_frec64>(L.f64);
+        b.f64b = reinterpret_cast<sg_frec64b*>(b.f64 + caps.n_gas_cap);
         b.f32 = at<sg_frec32>(L.f32);
         b.perm = at<int32_t>(L.perm);
         b.nbr_off = at<int64_t>(L.nbr_off);
@@ -381,11 +382,12 @@ sg_status do_build(sg_ctx* c) {
     const uint32_t* sorted =
         sg_launch_gas_order(key, ng, C, c->at<void>(c->L.gsort), c->at<int32_t>(c->L.perm), st);
     if (sg_offsets_by_bisection(ng, C)) {
-        sg_launch_gather_gas_off(b.perm, ng, g, pin, b.xs, b.ys, b.zs, b.hs, b.ms, b.prec, sorted,
-                                 off, C, st);
+        sg_launch_gather_gas_off(b.perm, ng, g, pin, b.xs, b.ys, b.zs, b.hs, b.ms, b.prec,
+                                 c->prm.precision, sorted, off, C, st);
     } else {
         sg_launch_scan(count, off, 0, &g->M, C, scan, st);
-        sg_launch_gather_gas(b.perm, ng, g, pin, b.xs, b.ys, b.zs, b.hs, b.ms, b.prec, st);
+        sg_launch_gather_gas(b.perm, ng, g, pin, b.xs, b.ys, b.zs, b.hs, b.ms, b.prec,
+                             c->prm.precision, st);
     }
     c->end();
     c->begin(SG_ST_NBR);

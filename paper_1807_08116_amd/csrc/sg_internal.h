@@ -63,6 +63,87 @@ __device__ inline int sg_seg_find(const int64_t* __restrict__ p, int nsys, int64
     return lo;
 }
 
+// Records moved by groups of lanes.  A lane that reads or writes a record of
+// its own touches a cache line of its own with every 16 bytes, and the vector
+// memory's address unit takes them one line a cycle: gathers of 64-byte
+// records kept it busy all the time (force pass at 1048576 gas particles).
+// Here the four lanes of a quad move one record per instruction, 16 bytes a
+// lane, so a quad's instruction touches one line, and a 4x4 transpose of
+// 16-byte pieces gives every lane its own record; pairs of lanes move 32-byte
+// records alike.  FP32C passes at that size: force 533 -> 340 us (the vector
+// ALU is busy throughout now), density 285 -> 212.  All lanes of the quad
+// must be active; bases are 64-byte (32-byte) aligned.
+template <int kCtrl>
+__device__ inline uint32_t dpp_quad(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kCtrl, 0xf, 0xf, true);
+}
+// the lower lane's b <-> the upper lane's a
+template <int kCtrl>
+__device__ inline void quad_swap(uint32_t& a, uint32_t& b, bool upper) {
+    const uint32_t xa = dpp_quad<kCtrl>(a), xb = dpp_quad<kCtrl>(b);   // with all lanes active
+    a = upper ? xb : a;
+    b = upper ? b : xa;
+}
+template <int kCtrl>
+__device__ inline void quad_swap(uint4& a, uint4& b, bool upper) {
+    quad_swap<kCtrl>(a.x, b.x, upper);
+    quad_swap<kCtrl>(a.y, b.y, upper);
+    quad_swap<kCtrl>(a.z, b.z, upper);
+    quad_swap<kCtrl>(a.w, b.w, upper);
+}
+// v[p] of lane r <-> v[r] of lane p
+__device__ inline void quad_transpose(uint4 (&v)[4]) {
+    const bool b0 = threadIdx.x & 1, b1 = threadIdx.x & 2;
+    quad_swap<0xb1>(v[0], v[1], b0);
+    quad_swap<0xb1>(v[2], v[3], b0);
+    quad_swap<0x4e>(v[0], v[2], b1);
+    quad_swap<0x4e>(v[1], v[3], b1);
+}
+// Record idx (64 bytes) of every lane.
+__device__ inline void quad_load64(const void* base, int32_t idx, uint4 (&v)[4]) {
+    const char* p = static_cast<const char*>(base) + 16 * (threadIdx.x & 3);
+    const uint32_t i[4] = {dpp_quad<0x00>((uint32_t)idx), dpp_quad<0x55>((uint32_t)idx),
+                           dpp_quad<0xaa>((uint32_t)idx), dpp_quad<0xff>((uint32_t)idx)};
+    for (int k = 0; k < 4; ++k) v[k] = *reinterpret_cast<const uint4*>(p + 64 * (size_t)i[k]);
+    quad_transpose(v);
+}
+// Record idx of every lane with idx >= 0.
+__device__ inline void quad_store64(void* base, int32_t idx, uint4 (&v)[4]) {
+    char* p = static_cast<char*>(base) + 16 * (threadIdx.x & 3);
+    const int32_t i[4] = {(int32_t)dpp_quad<0x00>((uint32_t)idx), (int32_t)dpp_quad<0x55>((uint32_t)idx),
+                          (int32_t)dpp_quad<0xaa>((uint32_t)idx), (int32_t)dpp_quad<0xff>((uint32_t)idx)};
+    quad_transpose(v);
+    for (int k = 0; k < 4; ++k)
+        if (i[k] >= 0) *reinterpret_cast<uint4*>(p + 64 * (size_t)i[k]) = v[k];
+}
+__device__ inline void pair_load32(const void* base, int32_t idx, uint4 (&v)[2]) {
+    const char* p = static_cast<const char*>(base) + 16 * (threadIdx.x & 1);
+    const uint32_t i0 = dpp_quad<0xa0>((uint32_t)idx), i1 = dpp_quad<0xf5>((uint32_t)idx);
+    v[0] = *reinterpret_cast<const uint4*>(p + 32 * (size_t)i0);
+    v[1] = *reinterpret_cast<const uint4*>(p + 32 * (size_t)i1);
+    quad_swap<0xb1>(v[0], v[1], threadIdx.x & 1);
+}
+__device__ inline void pair_store32(void* base, int32_t idx, uint4 (&v)[2]) {
+    char* p = static_cast<char*>(base) + 16 * (threadIdx.x & 1);
+    const int32_t i0 = (int32_t)dpp_quad<0xa0>((uint32_t)idx), i1 = (int32_t)dpp_quad<0xf5>((uint32_t)idx);
+    quad_swap<0xb1>(v[0], v[1], threadIdx.x & 1);
+    if (i0 >= 0) *reinterpret_cast<uint4*>(p + 32 * (size_t)i0) = v[0];
+    if (i1 >= 0) *reinterpret_cast<uint4*>(p + 32 * (size_t)i1) = v[1];
+}
+// A record as its 16-byte pieces and back.
+template <typename R, int K>
+__device__ inline R rec_of(const uint4 (&v)[K]) {
+    static_assert(sizeof(R) == 16 * K, "whole record");
+    R r;
+    __builtin_memcpy(&r, &v, sizeof(R));
+    return r;
+}
+template <typename R, int K>
+__device__ inline void rec_to(const R& r, uint4 (&v)[K]) {
+    static_assert(sizeof(R) == 16 * K, "whole record");
+    __builtin_memcpy(&v, &r, sizeof(R));
+}
+
 struct sg_grid_dev {
     // reduction inputs (order-preserving u64 images of doubles)
     unsigned long long hmin_bits;
@@ -137,14 +218,14 @@ const uint32_t* sg_launch_gas_order(const int32_t* key, int64_t ng, int64_t cell
                          int32_t* perm, hipStream_t st);
 void sg_launch_gather_gas(const int32_t* perm, int64_t ng, const sg_grid_dev* g,
                           const sg_prec* pin, double* xs, double* ys, double* zs, double* hs,
-                          double* ms, sg_prec* prec, hipStream_t st);
+                          double* ms, sg_prec* prec, int precision, hipStream_t st);
 // The gather with the cell offsets from the sorted keys beside it, for sizes
 // where that beats the scan of the counts.
 bool sg_offsets_by_bisection(int64_t ng, int64_t cell_cap);
 void sg_launch_gather_gas_off(const int32_t* perm, int64_t ng, const sg_grid_dev* g,
                               const sg_prec* pin, double* xs, double* ys, double* zs, double* hs,
-                              double* ms, sg_prec* prec, const uint32_t* keys, int64_t* off,
-                              int64_t cell_cap, hipStream_t st);
+                              double* ms, sg_prec* prec, int precision, const uint32_t* keys,
+                              int64_t* off, int64_t cell_cap, hipStream_t st);
 
 // Neighbour lists.
 // Neighbour search: per-target slots of fixed length (sg_nbr_slot_bytes),
@@ -163,11 +244,20 @@ void sg_launch_nbr_finish(sg_grid_dev* g, int64_t ng, const double* xs, const do
 
 // SPH.  Per-particle data in sorted-slot order is packed into one record
 // per particle, so a neighbour gather touches one or two cache lines.
-struct alignas(64) sg_prec {          // positions for the density pass
+struct alignas(64) sg_prec {          // positions for the FP64 density pass
     double x, y, z, h, m, pad[3];
 };
-struct alignas(32) sg_frec64 {        // FP64 force pass
-    double x, y, z, h, m, vx, vy, vz, rho, P, c, pad;   // P = p / rho^2
+struct alignas(32) sg_prec32 {        // the same for the FP32C form
+    double x, y, z;
+    float h, m;
+};
+// FP64 force pass, in two arrays: a particle's 64 bytes, then (after all of
+// them) its 32 bytes (P = p / rho^2).
+struct alignas(64) sg_frec64 {
+    double x, y, z, h, m, vx, vy, vz;
+};
+struct alignas(32) sg_frec64b {
+    double rho, P, c, pad;
 };
 struct alignas(64) sg_frec32 {        // FP32C force pass (FP64 positions)
     double x, y, z;
@@ -176,8 +266,9 @@ struct alignas(64) sg_frec32 {        // FP32C force pass (FP64 positions)
 struct sg_sph_bufs {
     double *xs, *ys, *zs, *hs, *ms;     // sorted SoA (neighbour search, h update)
     double* rho_s;                      // density by slot
-    sg_prec* prec;
+    sg_prec* prec;                      // sg_prec, or (FP32C) sg_prec32 records
     sg_frec64* f64;
+    sg_frec64b* f64b;
     sg_frec32* f32;
     const int32_t* perm;
     const int64_t* nbr_off;

@@ -496,12 +496,12 @@ __device__ inline void keys_count_wave(const double* __restrict__ x, const doubl
                                        sg_prec* __restrict__ pin) {
     int32_t k = -1;
     unsigned long long hb = 0ull;
+    sg_prec rec{};
     if (valid) {
         const double hi = h[i];
         const int l = level_of(hi, g->L0);
         const double p[3] = {x[i], y[i], z[i]};
-        // the particle's record in particle order, for the gather
-        pin[i] = sg_prec{p[0], p[1], p[2], hi, m[i], {0.0, 0.0, 0.0}};
+        rec = sg_prec{p[0], p[1], p[2], hi, m[i], {0.0, 0.0, 0.0}};
         int64_t c[3];
         for (int d = 0; d < 3; ++d) {
             double v = floor((p[d] - g->org[l][d]) * g->invL[l]);
@@ -513,6 +513,10 @@ __device__ inline void keys_count_wave(const double* __restrict__ x, const doubl
         key[i] = k;
         hb = (unsigned long long)__builtin_bit_cast(long long, hi);   // h > 0: orders as bits
     }
+    // the particle's record in particle order, for the gather
+    uint4 v[4];
+    rec_to(rec, v);
+    quad_store64(pin, valid ? (int32_t)i : -1, v);
     bool done = !valid;
     const unsigned long long act = __ballot(valid);
     if (act) {
@@ -557,29 +561,41 @@ __global__ __launch_bounds__(kBlock) void k_keys_count(const double* __restrict_
 // the key pass wrote in particle order (one aligned line per particle)
 // instead of five scattered doubles (five lines): at 1M gas its fetched
 // bytes fell from 625 MB to about 130 MB.
-__device__ inline void gather_one(const int32_t* __restrict__ perm, int64_t s,
+// Every lane of a quad calls this; s >= ng: nothing to gather.
+__device__ inline void gather_one(const int32_t* __restrict__ perm, int64_t s, int64_t ng,
                                   const sg_prec* __restrict__ pin, double* __restrict__ xs,
                                   double* __restrict__ ys, double* __restrict__ zs,
                                   double* __restrict__ hs, double* __restrict__ ms,
-                                  sg_prec* __restrict__ prec) {
-    const sg_prec r = pin[perm[s]];
-    xs[s] = r.x;
-    ys[s] = r.y;
-    zs[s] = r.z;
-    hs[s] = r.h;
-    ms[s] = r.m;
-    prec[s] = r;
+                                  sg_prec* __restrict__ prec, bool f32) {
+    const bool live = s < ng;
+    uint4 v[4];
+    quad_load64(pin, live ? perm[s] : 0, v);
+    const sg_prec r = rec_of<sg_prec>(v);
+    if (live) {
+        xs[s] = r.x;
+        ys[s] = r.y;
+        zs[s] = r.z;
+        hs[s] = r.h;
+        ms[s] = r.m;
+    }
+    const int32_t to = live ? (int32_t)s : -1;
+    if (f32) {
+        uint4 w[2];
+        rec_to(sg_prec32{r.x, r.y, r.z, (float)r.h, (float)r.m}, w);
+        pair_store32(prec, to, w);
+    } else {
+        quad_store64(prec, to, v);
+    }
 }
 
 __global__ __launch_bounds__(kBlock) void k_gather_gas(
     const int32_t* __restrict__ perm, int64_t ng, const sg_grid_dev* g,
     const sg_prec* __restrict__ pin, double* __restrict__ xs, double* __restrict__ ys,
     double* __restrict__ zs, double* __restrict__ hs, double* __restrict__ ms,
-    sg_prec* __restrict__ prec) {
+    sg_prec* __restrict__ prec, int f32) {
     if (g->err & SGE_SORT_FATAL) return;
-    int64_t s = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (s >= ng) return;
-    gather_one(perm, s, pin, xs, ys, zs, hs, ms, prec);
+    gather_one(perm, (int64_t)blockIdx.x * kBlock + threadIdx.x, ng, pin, xs, ys, zs, hs, ms, prec,
+               f32 != 0);
 }
 
 // The same, and in the workgroups after the first nbg the cell offsets, by
@@ -590,12 +606,12 @@ __global__ __launch_bounds__(kBlock) void k_gather_gas_off(
     const int32_t* __restrict__ perm, int64_t ng, const sg_grid_dev* g,
     const sg_prec* __restrict__ pin, double* __restrict__ xs, double* __restrict__ ys,
     double* __restrict__ zs, double* __restrict__ hs, double* __restrict__ ms,
-    sg_prec* __restrict__ prec, int nbg, const uint32_t* __restrict__ keys,
+    sg_prec* __restrict__ prec, int f32, int nbg, const uint32_t* __restrict__ keys,
     int64_t* __restrict__ off) {
     if (g->err & SGE_SORT_FATAL) return;
     if ((int)blockIdx.x < nbg) {
-        const int64_t s = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-        if (s < ng) gather_one(perm, s, pin, xs, ys, zs, hs, ms, prec);
+        gather_one(perm, (int64_t)blockIdx.x * kBlock + threadIdx.x, ng, pin, xs, ys, zs, hs, ms,
+                   prec, f32 != 0);
         return;
     }
     const int64_t M = g->M;
@@ -1098,9 +1114,8 @@ __global__ __launch_bounds__(kBlock) void k_seg_gather_gas(const sg_seg_sys* __r
     if (S.g->err & SGE_SORT_FATAL) return;
     const int64_t s = lb * kBlock + threadIdx.x;
     const sg_sph_bufs& b = S.sph;
-    if (s < S.ng)
-        gather_one(b.perm, s, reinterpret_cast<const sg_prec*>(b.f64), b.xs, b.ys, b.zs, b.hs,
-                   b.ms, b.prec);
+    gather_one(b.perm, s, S.ng, reinterpret_cast<const sg_prec*>(b.f64), b.xs, b.ys, b.zs, b.hs,
+               b.ms, b.prec, true);
 }
 
 inline unsigned grid_for(int64_t n, int per_block) {
@@ -1163,9 +1178,9 @@ void sg_launch_keys_count(const double* x, const double* y, const double* z, con
 
 void sg_launch_gather_gas(const int32_t* perm, int64_t ng, const sg_grid_dev* g,
                           const sg_prec* pin, double* xs, double* ys, double* zs, double* hs,
-                          double* ms, sg_prec* prec, hipStream_t st) {
+                          double* ms, sg_prec* prec, int precision, hipStream_t st) {
     hipLaunchKernelGGL(k_gather_gas, dim3(grid_for(ng, kBlock)), dim3(kBlock), 0, st, perm, ng,
-                       g, pin, xs, ys, zs, hs, ms, prec);
+                       g, pin, xs, ys, zs, hs, ms, prec, precision == SG_FP32C ? 1 : 0);
 }
 
 // Bisection costs log2(N_g) dependent reads a cell, the scan three launches.
@@ -1175,13 +1190,13 @@ bool sg_offsets_by_bisection(int64_t ng, int64_t cell_cap) {
 
 void sg_launch_gather_gas_off(const int32_t* perm, int64_t ng, const sg_grid_dev* g,
                               const sg_prec* pin, double* xs, double* ys, double* zs, double* hs,
-                              double* ms, sg_prec* prec, const uint32_t* keys, int64_t* off,
-                              int64_t cell_cap, hipStream_t st) {
+                              double* ms, sg_prec* prec, int precision, const uint32_t* keys,
+                              int64_t* off, int64_t cell_cap, hipStream_t st) {
     const unsigned nbg = grid_for(ng, kBlock);
     unsigned nbc = grid_for(cell_cap + 1, kBlock);
     if (nbc > 2048) nbc = 2048;
     hipLaunchKernelGGL(k_gather_gas_off, dim3(nbg + nbc), dim3(kBlock), 0, st, perm, ng, g, pin,
-                       xs, ys, zs, hs, ms, prec, (int)nbg, keys, off);
+                       xs, ys, zs, hs, ms, prec, precision == SG_FP32C ? 1 : 0, (int)nbg, keys, off);
 }
 
 // Workspace of the Morton order: two key/value buffers, the digit histogram

@@ -76,21 +76,27 @@ __device__ inline T spline_shape(T xi) {
 
 // Density of target s from lane `sub` of its group; `valid` false for the
 // groups past the end (they still take part in the group exchange).
+// The group walks its row together (lanes past its end repeat the row's
+// entry without adding it): records come by quads or pairs of lanes.
 __device__ inline void density_f64_lanes(const sg_sph_bufs& b, int64_t s, bool valid, int sub,
                                          double* __restrict__ rho_out) {
     double acc = 0.0;
-    sg_prec pi{};
     if (valid) {
-        pi = b.prec[s];
-        if (sub == 0) acc = pi.m / (kPi * pi.h * pi.h * pi.h);   // self term m_i W(0, h_i)
+        const double x = b.xs[s], y = b.ys[s], z = b.zs[s], h = b.hs[s];
+        if (sub == 0) acc = b.ms[s] / (kPi * h * h * h);         // self term m_i W(0, h_i)
         const int64_t e1 = b.nbr_off[s + 1];
-        for (int64_t e = b.nbr_off[s] + sub; e < e1; e += kSphLanes) {
-            const sg_prec pj = b.prec[b.nbr_idx[e]];
-            const double dx = pi.x - pj.x, dy = pi.y - pj.y, dz = pi.z - pj.z;
-            const double r = sqrt(dx * dx + dy * dy + dz * dz);
-            const double hij = 0.5 * (pi.h + pj.h);
-            const double inv = 1.0 / hij;
-            acc += pj.m * spline_shape(r * inv) * (inv * inv * inv) * (1.0 / kPi);
+        for (int64_t e0 = b.nbr_off[s]; e0 < e1; e0 += kSphLanes) {
+            const bool on = e0 + sub < e1;
+            uint4 v[4];
+            quad_load64(b.prec, b.nbr_idx[on ? e0 + sub : e0], v);
+            if (on) {
+                const sg_prec pj = rec_of<sg_prec>(v);
+                const double dx = x - pj.x, dy = y - pj.y, dz = z - pj.z;
+                const double r = sqrt(dx * dx + dy * dy + dz * dz);
+                const double hij = 0.5 * (h + pj.h);
+                const double inv = 1.0 / hij;
+                acc += pj.m * spline_shape(r * inv) * (inv * inv * inv) * (1.0 / kPi);
+            }
         }
     }
     acc = group_sum(acc);
@@ -111,18 +117,22 @@ __device__ inline void density_f32_lanes(const sg_sph_bufs& b, int64_t s, bool v
                                          double* __restrict__ rho_out) {
     kahan acc{0.0f, 0.0f};
     if (valid) {
-        const sg_prec pi = b.prec[s];
-        const float hi = (float)pi.h;
-        if (sub == 0) acc.s = (float)(pi.m / (kPi * pi.h * pi.h * pi.h));
+        const double x = b.xs[s], y = b.ys[s], z = b.zs[s], h = b.hs[s];
+        const float hi = (float)h;
+        if (sub == 0) acc.s = (float)(b.ms[s] / (kPi * h * h * h));
         const int64_t e1 = b.nbr_off[s + 1];
-        for (int64_t e = b.nbr_off[s] + sub; e < e1; e += kSphLanes) {
-            const sg_prec pj = b.prec[b.nbr_idx[e]];
-            const float dx = (float)(pi.x - pj.x), dy = (float)(pi.y - pj.y),
-                        dz = (float)(pi.z - pj.z);
-            const float r = sqrtf(dx * dx + dy * dy + dz * dz);
-            const float hij = 0.5f * (hi + (float)pj.h);
-            const float inv = 1.0f / hij;
-            acc.add((float)pj.m * spline_shape(r * inv) * (inv * inv * inv) * (float)(1.0 / kPi));
+        for (int64_t e0 = b.nbr_off[s]; e0 < e1; e0 += kSphLanes) {
+            const bool on = e0 + sub < e1;
+            uint4 v[2];
+            pair_load32(b.prec, b.nbr_idx[on ? e0 + sub : e0], v);
+            if (on) {
+                const sg_prec32 pj = rec_of<sg_prec32>(v);
+                const float dx = (float)(x - pj.x), dy = (float)(y - pj.y), dz = (float)(z - pj.z);
+                const float r = sqrtf(dx * dx + dy * dy + dz * dz);
+                const float hij = 0.5f * (hi + pj.h);
+                const float inv = 1.0f / hij;
+                acc.add(pj.m * spline_shape(r * inv) * (inv * inv * inv) * (float)(1.0 / kPi));
+            }
         }
     }
     const double rho = group_sum(acc.value());
@@ -164,20 +174,24 @@ __global__ __launch_bounds__(kBlock) void k_pack_ve(const sg_grid_dev* g, int64_
 
 // One record per slot of the state (v = vx, vy, vz, e of its particle), with
 // p / rho^2 and the sound speed sqrt(gamma p / rho) from the ideal-gas law.
-__device__ inline void sph_prep_one(const sg_sph_bufs& b, int64_t s, int precision,
+// Every lane of a quad calls this; live false: nothing is written.
+__device__ inline void sph_prep_one(const sg_sph_bufs& b, int64_t s, bool live, int precision,
                                     double gamma, const double4& v) {
-    const sg_prec q = b.prec[s];
-    const double rho = b.rho_s[s];
+    const int64_t q = live ? s : 0;
+    const double x = b.xs[q], y = b.ys[q], z = b.zs[q], h = b.hs[q], m = b.ms[q];
+    const double rho = b.rho_s[q];
     const double p = (gamma - 1.0) * rho * v.w;
     const double P = p / (rho * rho);
     const double c = sqrt(gamma * p / rho);
+    const int32_t to = live ? (int32_t)s : -1;
+    uint4 w[4];
     if (precision == SG_FP32C) {
         sg_frec32 r;
-        r.x = q.x;
-        r.y = q.y;
-        r.z = q.z;
-        r.h = (float)q.h;
-        r.m = (float)q.m;
+        r.x = x;
+        r.y = y;
+        r.z = z;
+        r.h = (float)h;
+        r.m = (float)m;
         r.vx = (float)v.x;
         r.vy = (float)v.y;
         r.vz = (float)v.z;
@@ -185,18 +199,30 @@ __device__ inline void sph_prep_one(const sg_sph_bufs& b, int64_t s, int precisi
         r.P = (float)P;
         r.c = (float)c;
         r.pad[0] = r.pad[1] = 0.0f;
-        b.f32[s] = r;
+        rec_to(r, w);
+        quad_store64(b.f32, to, w);
     } else {
-        b.f64[s] = sg_frec64{q.x, q.y, q.z, q.h, q.m, v.x, v.y, v.z, rho, P, c, 0.0};
+        rec_to(sg_frec64{x, y, z, h, m, v.x, v.y, v.z}, w);
+        quad_store64(b.f64, to, w);
+        uint4 u[2];
+        rec_to(sg_frec64b{rho, P, c, 0.0}, u);
+        pair_store32(b.f64b, to, u);
     }
+}
+
+__device__ inline void sph_prep_packed(const sg_sph_bufs& b, int64_t s, int64_t ng, int precision,
+                                       double gamma) {
+    const bool live = s < ng;
+    uint4 v[2];
+    pair_load32(b.ve, live ? b.perm[s] : 0, v);
+    sph_prep_one(b, s, live, precision, gamma, rec_of<double4>(v));
 }
 
 __global__ __launch_bounds__(kBlock) void k_sph_prep(sg_sph_bufs b, const sg_grid_dev* g,
                                                      int64_t ng, int precision, double gamma) {
     if (g->err & (SGE_SORT_FATAL | SGE_NNZ)) return;
-    const int64_t s = xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
-    if (s >= ng) return;
-    sph_prep_one(b, s, precision, gamma, reinterpret_cast<const double4*>(b.ve)[b.perm[s]]);
+    sph_prep_packed(b, xcd_block(blockIdx.x, gridDim.x) * kBlock + threadIdx.x, ng, precision,
+                    gamma);
 }
 
 // The same straight from the particle-order arrays, without the packing pass:
@@ -209,9 +235,8 @@ __global__ __launch_bounds__(kBlock) void k_sph_prep_direct(
     const double* __restrict__ e) {
     if (g->err & (SGE_SORT_FATAL | SGE_NNZ)) return;
     const int64_t s = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (s >= ng) return;
-    const int32_t i = b.perm[s];
-    sph_prep_one(b, s, precision, gamma, make_double4(vx[i], vy[i], vz[i], e[i]));
+    const int32_t i = s < ng ? b.perm[s] : 0;
+    sph_prep_one(b, s, s < ng, precision, gamma, make_double4(vx[i], vy[i], vz[i], e[i]));
 }
 
 __device__ inline void sph_force_f64_lanes(const sg_sph_bufs& b, int64_t s, bool valid, int sub,
@@ -222,33 +247,44 @@ __device__ inline void sph_force_f64_lanes(const sg_sph_bufs& b, int64_t s, bool
     double sx = 0, sy = 0, sz = 0, se = 0;
     if (valid) {
         const sg_frec64 a = b.f64[s];
+        const sg_frec64b a2 = b.f64b[s];
         const int64_t e1 = b.nbr_off[s + 1];
-        for (int64_t e = b.nbr_off[s] + sub; e < e1; e += kSphLanes) {
-            const sg_frec64 o = b.f64[b.nbr_idx[e]];
+        for (int64_t e0 = b.nbr_off[s]; e0 < e1; e0 += kSphLanes) {
+            const bool on = e0 + sub < e1;
+            const int32_t j = b.nbr_idx[on ? e0 + sub : e0];
+            uint4 v[4], w[2];
+            quad_load64(b.f64, j, v);
+            pair_load32(b.f64b, j, w);
+            const sg_frec64 o = rec_of<sg_frec64>(v);
+            const sg_frec64b o2 = rec_of<sg_frec64b>(w);
             const double dx = a.x - o.x, dy = a.y - o.y, dz = a.z - o.z;
             const double r2 = dx * dx + dy * dy + dz * dz;
-            if (r2 == 0.0) continue;                       // coincident pair: no gradient
-            const double r = sqrt(r2);
-            const double hij = 0.5 * (a.h + o.h);
-            const double inv = 1.0 / hij;
-            const double q = 2.0 - r * inv;
-            if (q <= 0.0) continue;
-            const double dvx = a.vx - o.vx, dvy = a.vy - o.vy, dvz = a.vz - o.vz;
-            const double rv = dx * dvx + dy * dvy + dz * dvz;
-            double nu = 0.0;
-            if (rv < 0.0) {
-                const double mu = hij * rv / (r2 + eta * hij * hij);
-                nu = mu * (beta * mu - alpha * 0.5 * (a.c + o.c)) / (0.5 * (a.rho + o.rho));
+            // (a coincident pair has no gradient)
+            if (on && r2 != 0.0) {
+                const double r = sqrt(r2);
+                const double hij = 0.5 * (a.h + o.h);
+                const double inv = 1.0 / hij;
+                const double q = 2.0 - r * inv;
+                if (!(q <= 0.0)) {
+                    const double dvx = a.vx - o.vx, dvy = a.vy - o.vy, dvz = a.vz - o.vz;
+                    const double rv = dx * dvx + dy * dvy + dz * dvz;
+                    double nu = 0.0;
+                    if (rv < 0.0) {
+                        const double mu = hij * rv / (r2 + eta * hij * hij);
+                        nu = mu * (beta * mu - alpha * 0.5 * (a2.c + o2.c)) /
+                             (0.5 * (a2.rho + o2.rho));
+                    }
+                    const double Pij = a2.P + o2.P + nu;
+                    // grad W_p = dW_p/dxi * r_ij / (|r_ij| h_ij) = gw * r_ij
+                    const double inv2 = inv * inv;
+                    const double gw = kgrad * q * q * (inv2 * inv2) / r;
+                    const double f = o.m * Pij * gw;
+                    sx -= f * dx;
+                    sy -= f * dy;
+                    sz -= f * dz;
+                    se += f * rv;
+                }
             }
-            const double Pij = a.P + o.P + nu;
-            // grad W_p = dW_p/dxi * r_ij / (|r_ij| h_ij) = gw * r_ij
-            const double inv2 = inv * inv;
-            const double gw = kgrad * q * q * (inv2 * inv2) / r;
-            const double f = o.m * Pij * gw;
-            sx -= f * dx;
-            sy -= f * dy;
-            sz -= f * dz;
-            se += f * rv;
         }
     }
     sx = group_sum(sx);
@@ -285,32 +321,38 @@ __device__ inline void sph_force_f32_lanes(const sg_sph_bufs& b, int64_t s, bool
     if (valid) {
         const sg_frec32 a = b.f32[s];
         const int64_t e1 = b.nbr_off[s + 1];
-        for (int64_t e = b.nbr_off[s] + sub; e < e1; e += kSphLanes) {
-            const sg_frec32 o = b.f32[b.nbr_idx[e]];
+        for (int64_t e0 = b.nbr_off[s]; e0 < e1; e0 += kSphLanes) {
+            const bool on = e0 + sub < e1;
+            uint4 v[4];
+            quad_load64(b.f32, b.nbr_idx[on ? e0 + sub : e0], v);
+            const sg_frec32 o = rec_of<sg_frec32>(v);
             const float dx = (float)(a.x - o.x), dy = (float)(a.y - o.y),
                         dz = (float)(a.z - o.z);
             const float r2 = dx * dx + dy * dy + dz * dz;
-            if (r2 == 0.0f) continue;
-            const float r = sqrtf(r2);
-            const float hij = 0.5f * (a.h + o.h);
-            const float inv = 1.0f / hij;
-            const float q = 2.0f - r * inv;
-            if (q <= 0.0f) continue;
-            const float dvx = a.vx - o.vx, dvy = a.vy - o.vy, dvz = a.vz - o.vz;
-            const float rv = dx * dvx + dy * dvy + dz * dvz;
-            float nu = 0.0f;
-            if (rv < 0.0f) {
-                const float mu = hij * rv / (r2 + eta * hij * hij);
-                nu = mu * (beta * mu - alpha * 0.5f * (a.c + o.c)) / (0.5f * (a.rho + o.rho));
+            if (on && r2 != 0.0f) {
+                const float r = sqrtf(r2);
+                const float hij = 0.5f * (a.h + o.h);
+                const float inv = 1.0f / hij;
+                const float q = 2.0f - r * inv;
+                if (!(q <= 0.0f)) {
+                    const float dvx = a.vx - o.vx, dvy = a.vy - o.vy, dvz = a.vz - o.vz;
+                    const float rv = dx * dvx + dy * dvy + dz * dvz;
+                    float nu = 0.0f;
+                    if (rv < 0.0f) {
+                        const float mu = hij * rv / (r2 + eta * hij * hij);
+                        nu = mu * (beta * mu - alpha * 0.5f * (a.c + o.c)) /
+                             (0.5f * (a.rho + o.rho));
+                    }
+                    const float Pij = a.P + o.P + nu;
+                    const float inv2 = inv * inv;
+                    const float gw = kgrad * q * q * (inv2 * inv2) / r;
+                    const float f = o.m * Pij * gw;
+                    sx.add(-f * dx);
+                    sy.add(-f * dy);
+                    sz.add(-f * dz);
+                    se.add(f * rv);
+                }
             }
-            const float Pij = a.P + o.P + nu;
-            const float inv2 = inv * inv;
-            const float gw = kgrad * q * q * (inv2 * inv2) / r;
-            const float f = o.m * Pij * gw;
-            sx.add(-f * dx);
-            sy.add(-f * dy);
-            sz.add(-f * dz);
-            se.add(f * rv);
         }
     }
     // each lane's compensated sum is exact to FP32 rounding of its terms;
@@ -370,10 +412,7 @@ __global__ __launch_bounds__(kBlock) void k_seg_sph_prep(const sg_seg_sys* __res
     int64_t lb;
     const sg_seg_sys& S = sys[sg_seg_find(pfx, nsys, blockIdx.x, &lb)];
     if (S.g->err & (SGE_SORT_FATAL | SGE_NNZ)) return;
-    const int64_t s = lb * kBlock + threadIdx.x;
-    if (s >= S.ng) return;
-    sph_prep_one(S.sph, s, SG_FP32C, S.gamma,
-                 reinterpret_cast<const double4*>(S.sph.ve)[S.sph.perm[s]]);
+    sph_prep_packed(S.sph, lb * kBlock + threadIdx.x, S.ng, SG_FP32C, S.gamma);
 }
 
 __global__ __launch_bounds__(kBlock) void k_seg_sph_force(const sg_seg_sys* __restrict__ sys,
@@ -407,14 +446,16 @@ __global__ __launch_bounds__(kBlock) void k_cfl(sg_sph_bufs b, const sg_grid_dev
     double dt = __builtin_inf();
     if (s < ng && b.nbr_off[s + 1] > b.nbr_off[s]) {
         const sg_frec64 a = b.f64[s];
+        const double ac = b.f64b[s].c;
         double smin = __builtin_inf(), cmax = 0.0, mumax = 0.0;
         for (int64_t e = b.nbr_off[s]; e < b.nbr_off[s + 1]; ++e) {
-            const sg_frec64 o = b.f64[b.nbr_idx[e]];
+            const int32_t j = b.nbr_idx[e];
+            const sg_frec64 o = b.f64[j];
             const double dx = a.x - o.x, dy = a.y - o.y, dz = a.z - o.z;
             const double r2 = dx * dx + dy * dy + dz * dz;
             const double r = sqrt(r2);
             smin = r < smin ? r : smin;
-            const double cij = 0.5 * (a.c + o.c);
+            const double cij = 0.5 * (ac + b.f64b[j].c);
             cmax = cij > cmax ? cij : cmax;
             const double rv = dx * (a.vx - o.vx) + dy * (a.vy - o.vy) + dz * (a.vz - o.vz);
             if (rv < 0.0) {
