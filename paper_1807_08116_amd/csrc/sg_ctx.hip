@@ -324,12 +324,16 @@ void grav_shape(const sg_ctx* c, int* ipl, int* split) {
 }
 
 // Symmetric gravity launch (each pair once): targets per lane, 0 for the
-// one-sided kernel.
+// one-sided kernel.  More targets amortise a step's LDS reads and rotations
+// over more pairs, fewer give more workgroups and fewer near runs.  With
+// potential, ms with 1 / 2 / 4 targets: FP32C 13000 particles 0.100 / 0.096
+// / 0.140, 100001 3.29 / 2.75 / 2.73, 131072 5.53 / 4.61 / 4.73, 180001
+// 9.99 / 8.50 / 8.28; FP64 13000 0.132 / 0.123 / 0.157, 33001 0.658 / 0.567
+// / 0.583, 40001 0.988 / 0.836 / 0.827, 131072 10.2 / 8.51 / 8.09.
 int sym_lanes(const sg_params& p, int64_t n, int ipl) {
     if (p.grav_variant != 0 || n < kSymMin) return 0;
     if (ipl != 0) return ipl;
-    if (p.precision == SG_FP32C) return n >= 65536 ? 4 : (n >= 24576 ? 2 : 1);
-    return n >= 131072 ? 4 : 2;
+    return n >= (p.precision == SG_FP32C ? 150000 : 40000) ? 4 : 2;
 }
 
 // Tiles per workgroup by the automatic rule; it is also the period at which
