@@ -19,10 +19,22 @@
 // candidate is fetched once per cell instead of once per target.  Any
 // grouping gives the same lists: the union contains each target's own box,
 // and every target keeps only the candidates that pass its predicate, in
-// stream order.  The union box is a pair of DPP reductions per dimension,
-// the stream offsets a DPP scan of the row lengths, and each batch of 64
-// stream positions finds its slots by walking the few non-empty rows that
-// overlap it: the set-up makes no LDS round trips.
+// stream order.  The union of the targets' reaches is a DPP reduction per
+// dimension, its boxes on all levels are computed at once (four lanes a
+// level), the stream offsets are a DPP scan of the row lengths, and the
+// slots of a chunk's stream positions a running maximum over marks that the
+// rows leave where they start.
+//
+// Bound by instruction issue: the scalar unit, which a compute unit's four
+// SIMDs share, as much as the vector ALUs (1190 candidates a target for 48
+// neighbours: a large part of a run's box is out of a given target's reach).
+// So the loop over targets and candidates has one branch per 192 candidates
+// while there is no hit, masks are combined only for batches with one, and
+// candidates are tested by the FP32 pretest below.  Search at 1048576
+// targets, per target: 264 scalar, 66 branch and 377 vector instructions
+// before, 149, 42 and 272 now; with two more wavefronts a SIMD (64 VGPRs),
+// 731 -> 490 us.  (The pretest alone, in a loop with a branch and two mask
+// operations a batch, was slower than the predicate: 820 us.)
 //
 // Each target writes its hits into a slot of its own, kSlot entries long,
 // in a scratch array (no atomics), and counts them.  A scan of the counts
@@ -50,8 +62,14 @@ constexpr int kWaves = kBlock / 64;
 // reads (about 23 instead of 28 vector instructions per 64 pair tests):
 // 1.53 ms with one batch, 1.41 with 2, 1.32 with 4, 1.49 with 8 (113 VGPRs:
 // 4 waves per SIMD).  With the set-up as it is now: 2: 0.98-0.99 ms, 3:
-// 0.94 (63 VGPRs), 4: 0.96, 6: 1.01-1.02.
+// 0.94 (63 VGPRs), 4: 0.96, 6: 1.01-1.02.  With the pretest, stage at
+// 1048576 targets: 2: 0.775, 3: 0.741, 4: 0.728 at 6 wavefronts a SIMD, 3:
+// 0.716 at 8.
 constexpr int kHold = 3;
+// Targets per wavefront from which the pretest is used: it pays for the
+// candidates' conversion from a few targets a run on (stage at 9001 targets
+// with 1 / 2: 47 / 52 us without, 51 / 51 with it; 262144, 2: 427 / 453).
+constexpr int kPreMin = 4;
 
 __device__ inline unsigned rank_below(unsigned long long mask) {
     return __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32),
@@ -84,7 +102,31 @@ __device__ inline bool nbr_pred_f(double xi, double yi, double zi, float hif, do
     return r2 < cut2;
 }
 
-constexpr int64_t kSlot = 96;              // scratch entries per target
+// Pretest of the predicate in FP32, for runs of several targets.  With
+// coordinates x', y', z' from an origin O close to both particles,
+//   (r^2 - (h_i + h_j)^2) / 2 = a_i + a_j - x'_i x'_j - y'_i y'_j
+//                               - z'_i z'_j - h_i h_j,   a = (|x'|^2 - h^2) / 2:
+// four FMAs and a comparison a pair, against three FP64 subtractions, three
+// conversions and six FP32 operations for the predicate itself.  Where the
+// value is within kPreTol (|x'|^2 + h^2) of zero, summed over both particles,
+// the pair is undecided and the predicate decides (a few pairs in a
+// thousand targets).  The tolerance covers, in units of u = 2^-24 and per
+// (|x'|^2 + h^2) of either particle: rounding of the coordinates 2, the
+// predicate's own roundings 5, a 2.5, the four FMAs 4: 13.5 of the 32 that
+// 2^-19 gives; kPreAbs covers what underflows.  A value that is not finite
+// never decides against a pair that the predicate would take: comparisons
+// with NaN leave it undecided.
+constexpr float kPreTol = 0x1p-19f, kPreAbs = 0x1p-118f;
+struct pre_rec {                           // x', y', z', h
+    float x, y, z, h;
+    __device__ inline float q() const {
+        return __builtin_fmaf(x, x, __builtin_fmaf(y, y, z * z));
+    }
+    __device__ inline float tol() const { return kPreTol * __builtin_fmaf(h, h, q()); }
+    __device__ inline float a() const { return 0.5f * __builtin_fmaf(-h, h, q()); }
+};
+
+constexpr int32_t kSlot = 96;              // scratch entries per target
 
 // Cells [lo, hi] (per dimension, clamped to the grid) of level l within
 // R = (h + hmax_l)(1 + 2^-10) of p; false when the level has no such cell.
@@ -166,30 +208,6 @@ __device__ inline int32_t dpp(int32_t old, int32_t v) {
     return __builtin_amdgcn_update_dpp(old, v, kCtrl, kRowMask, 0xf, false);
 }
 
-// minimum over the 64 lanes (uniform result)
-__device__ inline int32_t wave_min(int32_t v) {
-    constexpr int32_t I = INT32_MAX;
-    v = min(v, dpp<0xb1>(I, v));
-    v = min(v, dpp<0x4e>(I, v));
-    v = min(v, dpp<0x141>(I, v));
-    v = min(v, dpp<0x140>(I, v));              // each row of 16: its minimum
-    v = min(v, dpp<0x142, 0xa>(I, v));         // rows 1, 3: with rows 0, 2
-    v = min(v, dpp<0x143, 0xc>(I, v));         // rows 2, 3: with rows 0, 1
-    return __builtin_amdgcn_readlane(v, 63);
-}
-
-// maximum over the 64 lanes (uniform result)
-__device__ inline int32_t wave_max(int32_t v) {
-    constexpr int32_t I = INT32_MIN;
-    v = max(v, dpp<0xb1>(I, v));
-    v = max(v, dpp<0x4e>(I, v));
-    v = max(v, dpp<0x141>(I, v));
-    v = max(v, dpp<0x140>(I, v));
-    v = max(v, dpp<0x142, 0xa>(I, v));
-    v = max(v, dpp<0x143, 0xc>(I, v));
-    return __builtin_amdgcn_readlane(v, 63);
-}
-
 // inclusive prefix sum over the 64 lanes
 __device__ inline int32_t wave_incl_sum(int32_t v) {
     v += dpp<0x111>(0, v);                     // within each row of 16
@@ -199,6 +217,48 @@ __device__ inline int32_t wave_incl_sum(int32_t v) {
     v += dpp<0x142, 0xa>(0, v);                // rows 1, 3: + total of rows 0, 2
     v += dpp<0x143, 0xc>(0, v);                // rows 2, 3: + total of rows 0, 1
     return v;
+}
+
+// inclusive prefix maximum over the 64 lanes, of values >= 0
+__device__ inline int32_t wave_incl_max(int32_t v) {
+    v = max(v, dpp<0x111>(0, v));
+    v = max(v, dpp<0x112>(0, v));
+    v = max(v, dpp<0x114>(0, v));
+    v = max(v, dpp<0x118>(0, v));
+    v = max(v, dpp<0x142, 0xa>(0, v));
+    v = max(v, dpp<0x143, 0xc>(0, v));
+    return v;
+}
+
+// a[i] with a 32-bit byte offset (one address register: slots of 2^29
+// targets, 206 GB of scratch and as much again beside, are out of reach)
+__device__ inline double at32(const double* __restrict__ a, uint32_t i) {
+    return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(a) + (size_t)(i * 8u));
+}
+
+// minimum over each half of the wavefront, in its last lane (31, 63)
+__device__ inline double half_min(double v) {
+    auto step = [&](auto ctrl, auto rows) {
+        constexpr int kCtrl = decltype(ctrl)::value, kRows = decltype(rows)::value;
+        const unsigned long long q = __builtin_bit_cast(unsigned long long, v);
+        const int32_t lo = dpp<kCtrl, kRows>((int32_t)(unsigned)q, (int32_t)(unsigned)q);
+        const int32_t hi = dpp<kCtrl, kRows>((int32_t)(q >> 32), (int32_t)(q >> 32));
+        v = fmin(v, __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+    };
+    step(std::integral_constant<int, 0xb1>{}, std::integral_constant<int, 0xf>{});
+    step(std::integral_constant<int, 0x4e>{}, std::integral_constant<int, 0xf>{});
+    step(std::integral_constant<int, 0x141>{}, std::integral_constant<int, 0xf>{});
+    step(std::integral_constant<int, 0x140>{}, std::integral_constant<int, 0xf>{});   // rows of 16
+    step(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{});   // rows 1, 3
+    return v;
+}
+
+// v of lane l (uniform)
+__device__ inline double lane_value(double v, int l) {
+    const unsigned long long q = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)q, l);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(q >> 32), l);
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 
 // The search of wavefront w (target slots NT w onward); w is uniform.
@@ -213,11 +273,15 @@ __device__ __attribute__((always_inline)) inline void nbr_search_wave(
     const unsigned lane = threadIdx.x & 63;
     const int64_t g0 = (int64_t)w * NT;
     if (g0 >= ng) return;
-    const int64_t s = g0 + lane;
+    // target g0 + (lane & 31) in both halves of the wavefront (the upper one
+    // only helps with the run's reach)
+    static_assert(NT <= 32, "a target a lane, twice");
+    const unsigned tl = lane & 31;
+    const int64_t s = g0 + tl;
     const bool live = lane < (unsigned)NT && s < ng;
     double p[3] = {0.0, 0.0, 0.0}, h = 0.0;
     int32_t k = -1;
-    if (live) {
+    if (tl < (unsigned)NT && s < ng) {
         p[0] = xs[s];
         p[1] = ys[s];
         p[2] = zs[s];
@@ -230,46 +294,93 @@ __device__ __attribute__((always_inline)) inline void nbr_search_wave(
     // the wavefront's targets in LDS: a target pass reads its target's
     // record with broadcast loads (one address instruction) instead of
     // seven lane reads on the vector ALU (search stage at 1M gas 1.147 ->
-    // 1.096 ms); 4 KB per workgroup, which still fits beside the gravity
+    // 1.096 ms); 3-4 KB per workgroup, which still fits beside the gravity
     // kernel's workgroups on a compute unit
+    constexpr bool kPre = NT >= kPreMin;
     struct target_rec { double x, y, z; float h, pad; };
-    __shared__ target_rec tp[kWaves][NT];
-    target_rec* const mytp = tp[threadIdx.x >> 6];
-    if (lane < (unsigned)NT) mytp[lane] = target_rec{p[0], p[1], p[2], hif, 0.0f};
+    struct pre_cut { float maybe, sure; };
+    __shared__ target_rec tp[kPre ? 1 : kWaves][kPre ? 1 : NT];
+    __shared__ pre_rec tq[kPre ? kWaves : 1][kPre ? NT : 1];
+    __shared__ pre_cut tc[kPre ? kWaves : 1][kPre ? NT : 1];
+    target_rec* const mytp = tp[kPre ? 0 : threadIdx.x >> 6];
+    pre_rec* const mytq = tq[kPre ? threadIdx.x >> 6 : 0];
+    pre_cut* const mytc = tc[kPre ? threadIdx.x >> 6 : 0];
+    __shared__ int32_t mark[kWaves][64 * kHold];
+    int32_t* const mymark = mark[threadIdx.x >> 6];
+    if (!kPre && lane < (unsigned)NT) mytp[lane] = target_rec{p[0], p[1], p[2], hif, 0.0f};
     __builtin_amdgcn_wave_barrier();
-    int32_t mine = 0;                          // hits of target g0 + lane so far
+    // end of target g0 + lane's hits, from the wavefront's first slot
+    int32_t* const wslots = slots + g0 * kSlot;
+    int32_t mine = (int32_t)lane * kSlot;
     const int nlev = g->nlev;
     unsigned long long todo = __ballot(live);
     while (todo) {
         const int lead = __builtin_ctzll(todo);
         const int32_t rk = __builtin_amdgcn_readlane(k, lead);
-        const unsigned long long run = __ballot(live && k == rk) & todo;
-        todo &= ~run;
-        const bool inrun = (run >> lane) & 1ull;
-        for (int l = 0; l < nlev; ++l) {
-            if (g->ncell[l] == 0) continue;
-            int32_t lo[3], hi3[3];
-            const bool has = inrun && level_box(g, l, p, h, lo, hi3);
-            // no target of the run reaches level l: skipped before the
-            // reductions (search stage at 1M gas 1.015 -> 0.96-0.97 ms)
-            if (__ballot(has) == 0ull) continue;
-            // union of the run's boxes; wave-uniform, held in scalar
-            // registers so that every loop below is uniform and its
-            // cross-lane reads see all lanes
-            int32_t ulo[3], uhi[3];
-            bool inside = true;
-            for (int d = 0; d < 3; ++d) {
-                ulo[d] = wave_min(has ? lo[d] : INT32_MAX);
-                uhi[d] = wave_max(has ? hi3[d] : -1);
-                inside = inside && ulo[d] >= 0 && ulo[d] <= uhi[d] && uhi[d] < g->dim[l][d];
+        // the slots are in key order: a run is lanes lead .. lead + nrun - 1
+        const unsigned long long eq = __ballot(live && k == rk) >> lead;
+        const int nrun = __builtin_ctzll(~eq);             // (NT < 64: ~eq is not 0)
+        todo &= todo >> lead >> nrun << lead << nrun;
+        const bool inrun = tl - (unsigned)lead < (unsigned)nrun;
+        // the run's reach per dimension, from its first target O: lower end
+        // min (p - O - h (1 + 2^-10)) in lane 31, minus the upper end in 63
+        double O[3], rlo[3], rhi[3];
+        for (int d = 0; d < 3; ++d) {
+            O[d] = lane_value(p[d], lead);
+            const double q = p[d] - O[d];
+            double v = inrun ? (lane < 32 ? q : -q) - h * (1.0 + 0x1p-10) : __builtin_inf();
+            v = half_min(v);
+            rlo[d] = lane_value(v, 31);
+            rhi[d] = -lane_value(v, 63);
+        }
+        if constexpr (kPre) {
+            // pretest: coordinates from O
+            if (inrun && lane < 32) {
+                const pre_rec t{(float)(p[0] - O[0]), (float)(p[1] - O[1]), (float)(p[2] - O[2]), hif};
+                const float m = t.tol() + kPreAbs;
+                mytq[lane] = t;
+                mytc[lane] = pre_cut{m - t.a(), -m - t.a()};
             }
-            // no target of the run reaches level l (the box test also
-            // keeps every row and cell index below inside the level)
-            if (!inside) continue;
-            const int64_t base = g->base[l];
-            const int32_t dx = (int32_t)g->dim[l][0], dy = (int32_t)g->dim[l][1];
+            __builtin_amdgcn_wave_barrier();
+        }
+        // the boxes of cells within reach: lane 4 l + d computes dimension d
+        // of level l (the run's box is the union of its targets' boxes, as
+        // its reach is of theirs)
+        static_assert(SG_MAXLEV <= 16, "four lanes a level");
+        int32_t blo = 0, bhi = 0, bdim = 0;
+        const int lv = (int)(lane >> 2), ld = (int)(lane & 3);
+        bool ok = ld < 3 && lv < nlev && g->ncell[lv < SG_MAXLEV ? lv : 0] != 0;
+        if (ok) {
+            const double inv = g->invL[lv], hl = g->hmaxlev[lv] * (1.0 + 0x1p-10);
+            const double o = (ld == 0 ? O[0] : (ld == 1 ? O[1] : O[2])) - g->org[lv][ld];
+            const double a = (ld == 0 ? rlo[0] : (ld == 1 ? rlo[1] : rlo[2])) - hl;
+            const double b = (ld == 0 ? rhi[0] : (ld == 1 ? rhi[1] : rhi[2])) + hl;
+            bdim = (int32_t)g->dim[lv][ld];
+            // clamped into [-1, 2^30] first, where the conversion is exact
+            // (a NaN becomes -1: an empty box)
+            const int32_t ca = (int32_t)fmin(fmax(floor((o + a) * inv), -1.0), 0x1p30);
+            const int32_t cb = (int32_t)fmin(fmax(floor((o + b) * inv), -1.0), 0x1p30);
+            ok = cb >= 0 && ca < bdim && ca <= cb;
+            blo = max(ca, 0);
+            bhi = min(cb, bdim - 1);
+        }
+        unsigned long long lm = __ballot(ok);
+        lm &= (lm >> 1) & (lm >> 2) & 0x1111111111111111ull;
+        for (; lm; lm &= lm - 1) {
+            // wave-uniform, held in scalar registers so that every loop
+            // below is uniform and its cross-lane reads see all lanes
+            const int lb = __builtin_ctzll(lm);
+            int32_t ulo[3], uhi[3];
+            for (int d = 0; d < 3; ++d) {
+                ulo[d] = __builtin_amdgcn_readlane(blo, lb + d);
+                uhi[d] = __builtin_amdgcn_readlane(bhi, lb + d);
+            }
+            const int32_t dx = __builtin_amdgcn_readlane(bdim, lb);
+            const int32_t dy = __builtin_amdgcn_readlane(bdim, lb + 1);
+            const int64_t base = g->base[lb >> 2];
             const uint32_t ny = (uint32_t)(uhi[1] - ulo[1] + 1);
             const int32_t nrows = (int32_t)((uint32_t)(uhi[2] - ulo[2] + 1) * ny);
+            const float rny = __builtin_amdgcn_rcpf((float)ny);
             for (int32_t r0 = 0; r0 < nrows; r0 += 64) {
                 // rows r0 .. r0+63, one per lane: first slot and length
                 // (offsets clamped to [0, ng] so that a corrupt table can
@@ -278,7 +389,10 @@ __device__ __attribute__((always_inline)) inline void nbr_search_wave(
                 int32_t first = 0, len = 0;
                 const int32_t r = r0 + (int32_t)lane;
                 if (r < nrows) {
-                    const uint32_t rz = (uint32_t)r / ny;
+                    // (exact below 2^20: (r + 1/2) / ny is at least 1 / (2 ny)
+                    // from a whole number)
+                    const uint32_t rz = nrows <= 1 << 20 ? (uint32_t)(((float)r + 0.5f) * rny)
+                                                         : (uint32_t)r / ny;
                     const int32_t cz = ulo[2] + (int32_t)rz, cy = ulo[1] + (int32_t)((uint32_t)r - rz * ny);
                     const int64_t row = base + (int64_t)((cz * dy + cy) * dx);
                     int64_t a = off[row + ulo[0]], b = off[row + uhi[0] + 1];
@@ -292,98 +406,141 @@ __device__ __attribute__((always_inline)) inline void nbr_search_wave(
                 const int32_t incl = wave_incl_sum(len);
                 const int32_t start = incl - len;
                 const int32_t total = __builtin_amdgcn_readlane(incl, 63);
-                // stream positions b .. b+63 -> slots, one per lane: of the
-                // non-empty rows that overlap them (a few; ascending, each
-                // starting where the previous one ends) each lane keeps the
-                // last one that starts at or before its position
+                // a row's slots are its stream positions plus fs, which
+                // never falls along the rows (they ascend)
                 const int32_t fs = first - start;
-                auto locate = [&](int32_t b) -> int32_t {
-                    const int32_t q = b + (int32_t)lane;
-                    int32_t d = 0;
-                    for (unsigned long long m = __ballot(len > 0 && start < b + 64 && incl > b); m;
-                         m &= m - 1) {
-                        const int j = __builtin_ctzll(m);
-                        const int32_t sj = __builtin_amdgcn_readlane(start, j);
-                        const int32_t dj = __builtin_amdgcn_readlane(fs, j);
-                        if (q >= sj) d = dj;
-                    }
-                    return q + d;
-                };
+                int32_t carry = 0;
                 // candidates in chunks of kHold batches of 64, held in
                 // registers while each target of the run tests the whole
                 // chunk (its record read from LDS once per chunk, its hit
                 // count carried in a scalar register)
                 for (int32_t cb0 = 0; cb0 < total; cb0 += 64 * kHold) {
+                    // slots of the chunk's stream positions: each non-empty
+                    // row puts its fs where it starts, and a running maximum
+                    // carries it over the row (against a walk over the rows
+                    // with two lane reads each: the scalar unit, which four
+                    // SIMDs share, was what bounded the search)
+#pragma unroll
+                    for (int k = 0; k < kHold; ++k) mymark[64 * k + lane] = 0;
+                    if (len > 0 && start >= cb0 && start < cb0 + 64 * kHold) mymark[start - cb0] = fs;
+                    __builtin_amdgcn_wave_barrier();
                     int32_t tk[kHold];
-                    bool vk[kHold];
                     unsigned long long vm[kHold];          // lanes holding a candidate
-                    double xk[kHold], yk[kHold], zk[kHold];
-                    float hk[kHold];
+                    double xd[kHold], yd[kHold], zd[kHold], hd[kHold];
                     // every batch's loads are issued before any is used
                     // (h converts to FP32 after the last one); lanes past
                     // the stream load a clamped slot and are masked out
-                    double hd[kHold];
 #pragma unroll
                     for (int k = 0; k < kHold; ++k) {
-                        const int32_t q = cb0 + 64 * k + (int32_t)lane;
-                        vk[k] = q < total;
                         tk[k] = 0;
-                        xk[k] = yk[k] = zk[k] = hd[k] = 0.0;
+                        xd[k] = yd[k] = zd[k] = hd[k] = 0.0;
                         if (cb0 + 64 * k < total) {          // uniform
-                            tk[k] = locate(cb0 + 64 * k);
-                            const int32_t t = min(max(tk[k], 0), (int32_t)(ng - 1));
-                            xk[k] = xs[t];
-                            yk[k] = ys[t];
-                            zk[k] = zs[t];
-                            hd[k] = hs[t];
+                            const int32_t f = max(wave_incl_max(mymark[64 * k + lane]), carry);
+                            carry = __builtin_amdgcn_readlane(f, 63);
+                            tk[k] = cb0 + 64 * k + (int32_t)lane + f;
+                            const uint32_t t = (uint32_t)min(max(tk[k], 0), (int32_t)(ng - 1));
+                            xd[k] = at32(xs, t);
+                            yd[k] = at32(ys, t);
+                            zd[k] = at32(zs, t);
+                            hd[k] = at32(hs, t);
                         }
                         const int32_t nk = total - (cb0 + 64 * k);
                         vm[k] = nk >= 64 ? ~0ull : (nk > 0 ? (1ull << nk) - 1 : 0ull);
                     }
-                    // (an empty statement that takes the loaded values keeps
+                    // (empty statements that take the loaded values keep
                     // the conversions, and their waits, behind the last load)
-                    static_assert(kHold == 3, "the statement below names each held batch");
-                    asm volatile("" : "+v"(hd[0]), "+v"(hd[1]), "+v"(hd[2]));
 #pragma unroll
-                    for (int k = 0; k < kHold; ++k) hk[k] = (float)hd[k];
-                    for (unsigned long long tr = run; tr; tr &= tr - 1) {
-                        const int L = __builtin_ctzll(tr);
+                    for (int k = 0; k < kHold; ++k) asm volatile("" : "+v"(hd[k]));
+                    pre_rec ck[kHold];
+                    float ak[kHold], bk[kHold];
+#pragma unroll
+                    for (int k = 0; k < kHold; ++k) {
+                        ck[k].h = (float)hd[k];
+                        if constexpr (kPre) {
+                            ck[k].x = (float)(xd[k] - O[0]);
+                            ck[k].y = (float)(yd[k] - O[1]);
+                            ck[k].z = (float)(zd[k] - O[2]);
+                            const float m = ck[k].tol();
+                            ak[k] = cb0 + 64 * k + (int32_t)lane < total ? ck[k].a() - m : __builtin_inff();
+                            bk[k] = 2.0f * m;
+                        }
+                    }
+                    for (int L = lead; L < lead + nrun; ++L) {
+                        // target L (uniform) against the chunk: the lanes
+                        // with a hit as a mask a batch
+                        unsigned long long mk[kHold];
                         const int64_t sL = g0 + L;
-                        // target L's data (uniform)
-                        const double xi = mytp[L].x, yi = mytp[L].y, zi = mytp[L].z;
-                        const float hi = mytp[L].h;
+                        if constexpr (kPre) {
+                            const pre_rec qi = mytq[L];
+                            const pre_cut ci = mytc[L];
+                            float t[kHold];
+                            unsigned long long any = 0;
+#pragma unroll
+                            for (int k = 0; k < kHold; ++k) {
+                                t[k] = __builtin_fmaf(-qi.h, ck[k].h,
+                                    __builtin_fmaf(-qi.z, ck[k].z, __builtin_fmaf(-qi.y, ck[k].y,
+                                    __builtin_fmaf(-qi.x, ck[k].x, ak[k]))));
+                                mk[k] = __builtin_amdgcn_ballot_w64(!(t[k] >= ci.maybe));
+                                any |= mk[k];
+                            }
+                            if (!any) continue;
+                            // undecided pairs: the predicate itself
+                            unsigned long long un = 0;
+#pragma unroll
+                            for (int k = 0; k < kHold; ++k)
+                                un |= mk[k] & ~__builtin_amdgcn_ballot_w64(t[k] + bk[k] < ci.sure);
+                            if (un) {
+                                int64_t sq = sL;
+                                asm volatile("" : "+s"(sq));          // (nor for this)
+#pragma unroll
+                                for (int k = 0; k < kHold; ++k) {
+                                    int32_t q = tk[k];
+                                    asm volatile("" : "+v"(q));   // (no addresses kept for this)
+                                    q = min(max(q, 0), (int32_t)(ng - 1));
+                                    const bool pr = nbr_pred(xs[sq], ys[sq], zs[sq], (float)hs[sq],
+                                                             xs[q], ys[q], zs[q], hs[q]);
+                                    mk[k] &= __builtin_amdgcn_ballot_w64(pr) & vm[k];
+                                }
+                            }
+                        } else {
+                            const target_rec ti = mytp[L];
+#pragma unroll
+                            for (int k = 0; k < kHold; ++k) {
+                                mk[k] = 0;
+                                if (cb0 + 64 * k < total)              // uniform
+                                    mk[k] = __builtin_amdgcn_ballot_w64(nbr_pred_f(
+                                        ti.x, ti.y, ti.z, ti.h, xd[k], yd[k], zd[k], ck[k].h)) & vm[k];
+                            }
+                        }
                         int32_t c = __builtin_amdgcn_readlane(mine, L);
-                        int32_t* const row = slots + sL * kSlot;
 #pragma unroll
                         for (int k = 0; k < kHold; ++k) {
-                            if (cb0 + 64 * k >= total) break;  // uniform
-                            // the ballot of the bare comparison is the
-                            // comparison's own lane mask and validity a
-                            // scalar mask; the target itself is looked for
-                            // only in batches with a hit
-                            const bool pr = nbr_pred_f(xi, yi, zi, hi, xk[k], yk[k], zk[k], hk[k]);
-                            unsigned long long mask = __builtin_amdgcn_ballot_w64(pr) & vm[k];
-                            if (mask) {
-                                const bool me = tk[k] == (int32_t)sL;
-                                mask &= ~__builtin_amdgcn_ballot_w64(me);
-                                const uint32_t pos = (uint32_t)c + (uint32_t)rank_below(mask);
-                                if (pr && vk[k] && !me && pos < (uint32_t)kSlot) row[pos] = tk[k];
-                                c += __builtin_popcountll(mask);
-                            }
+                            // the target itself is looked for only in
+                            // batches with a hit
+                            if (mk[k] == 0) continue;
+                            const unsigned long long mask =
+                                mk[k] & ~__builtin_amdgcn_ballot_w64(tk[k] == (int32_t)sL);
+                            // a full slot's last entry takes what does not
+                            // fit: the row is searched again then
+                            const uint32_t pos = min((uint32_t)c + (uint32_t)rank_below(mask),
+                                                     (uint32_t)L * kSlot + (kSlot - 1));
+                            if (__builtin_amdgcn_inverse_ballot_w64(mask)) wslots[pos] = tk[k];
+                            c += __builtin_popcountll(mask);
                         }
                         // lane L's count := c (one lane written, whatever the
                         // execution mask)
+                        c = __builtin_amdgcn_readfirstlane(c);
                         asm volatile("v_writelane_b32 %0, %1, m0" : "+v"(mine) : "s"(c), "{m0}"(L));
                     }
                 }
             }
         }
     }
-    if (live) cnt[s] = mine;
+    if (live) cnt[s] = mine - (int32_t)lane * kSlot;
 }
 
 template <int NT>
-__global__ __launch_bounds__(kBlock) void k_nbr_search(
+__global__ __launch_bounds__(kBlock, NT >= kPreMin ? 8 : 6) void k_nbr_search(
     const sg_grid_dev* __restrict__ g, int64_t ng, const double* __restrict__ xs,
     const double* __restrict__ ys, const double* __restrict__ zs, const double* __restrict__ hs,
     const int64_t* __restrict__ off, const int32_t* __restrict__ perm,
@@ -543,9 +700,8 @@ __global__ void k_nbr_check(sg_grid_dev* g, const int64_t* __restrict__ nbr_off,
 // (see sg_seg in sg_internal.h)
 
 template <int NT>
-__global__ __launch_bounds__(kBlock) void k_seg_nbr_search(const sg_seg_sys* __restrict__ sys,
-                                                           const int64_t* __restrict__ pfx,
-                                                           int nsys) {
+__global__ __launch_bounds__(kBlock, NT >= kPreMin ? 8 : 6) void k_seg_nbr_search(
+    const sg_seg_sys* __restrict__ sys, const int64_t* __restrict__ pfx, int nsys) {
     int64_t lb;
     const sg_seg_sys& S = sys[sg_seg_find(pfx, nsys, blockIdx.x, &lb)];
     const int32_t w = __builtin_amdgcn_readfirstlane((int32_t)(lb * kWaves + (threadIdx.x >> 6)));
@@ -583,17 +739,18 @@ inline unsigned waves_grid(int64_t n) {
 // share the set-up of a run's boxes and each candidate load among its
 // targets, which is what counts once the wavefronts fill the chip.  Stage
 // (search, scan, check, copy) in us with 32 / 16 / 8 / 4 / 2 / 1 targets: 1009
-// targets 153 / 116 / 86 / 61 / 42 / 30; 4096: 179 / 116 / 79 / 61 / 48 / 39;
-// 9001: 217 / 129 / 86 / 72 / 57 / 56; 30011: 191 / 128 / 100 / 98 / 101 /
-// 123; 65536: 204 / 157 / 133 / 139 / 168 / 219; 131071: 222 / 197 / 195 /
-// 218 / 281; 262144: 328 / 307 / 330 / 390; 524288: 541 / 544 / 602; 1048576:
-// 953 / 991 / 1123.
+// targets 112 / 83 / 61 / 44 / 27 / 20; 9001: 170 / 100 / 67 / 58 / 52 / 47;
+// 14000: 192 / 116 / 82 / 68 / 67 / 65; 20000: 202 / 125 / 92 / 81 / 71 / 80;
+// 30011: 161 / 106 / 83 / 77 / 86 / 105; 45000: 146 / 100 / 87 / 91 / 106 /
+// 137; 100000: 163 / 129 / 132 / 151 / 192 / 263; 131071: 166 / 152 / 151 /
+// 178; 262144: 232 / 228 / 251 / 318; 400000: 320 / 315 / 363; 524288: 390 /
+// 400 / 463; 1048576: 696 / 752 / 865.
 int sg_nbr_targets(int64_t ng) {
     if (ng >= 450000) return 32;
-    if (ng >= 150000) return 16;
-    if (ng >= 45000) return 8;
-    if (ng >= 22000) return 4;
-    return ng >= 9500 ? 2 : 1;
+    if (ng >= 120000) return 16;
+    if (ng >= 40000) return 8;
+    if (ng >= 25000) return 4;
+    return ng >= 16000 ? 2 : 1;
 }
 
 namespace {
