@@ -562,10 +562,14 @@ __global__ __launch_bounds__(kBlock, NT >= kPreMin ? 8 : 6) void k_nbr_search(
 // takes targets kCompact w .. kCompact w + kCompact - 1, 64 / kCompact lanes
 // each; a target with more than kSlot hits is searched again by the whole
 // wavefront.
-// Targets per wavefront at 1M gas (about 41 hits each), neighbour stage:
-// 2: 1.23 ms, 4: 1.17-1.19, 8: 1.14-1.16, 16: 1.18, 32: 1.31.
-constexpr int kCompact = 8;
+// Bound by memory once the loads of a whole row are in flight together and
+// the scalar loads of every target's count and offset, one after the other
+// in search of an overflowed slot, are a ballot: 182 -> 97 us at 1048576
+// targets (about 0.5 GB), with 8 / 16 targets a wavefront 120 / 172.
+constexpr int kCompact = 4;
 constexpr int kCompactLanes = 64 / kCompact;
+constexpr int kMove = kSlot / kCompactLanes;      // entries a lane: one pass a row
+static_assert(kMove * kCompactLanes == kSlot, "a slot in one pass");
 
 __device__ __attribute__((always_inline)) inline void nbr_copy_wave(
     const sg_grid_dev* __restrict__ g, int64_t ng, const double* __restrict__ xs,
@@ -577,27 +581,26 @@ __device__ __attribute__((always_inline)) inline void nbr_copy_wave(
     const int64_t s0 = w * kCompact;
     if (s0 >= ng) return;
     const int64_t s = s0 + lane / kCompactLanes;
-    const int64_t c = s < ng ? cnt[s] : 0;
-    if (c <= kSlot) {
-        const int32_t* mine = slots + s * kSlot;
-        const int64_t to = nbr_off[(s < ng ? s : s0) - off0];
-        // four entries in flight per lane, then the rest
-        int64_t k = lane % kCompactLanes;
-        for (; k + 3 * kCompactLanes < c; k += 4 * kCompactLanes) {
-            const int32_t v0 = mine[k], v1 = mine[k + kCompactLanes];
-            const int32_t v2 = mine[k + 2 * kCompactLanes], v3 = mine[k + 3 * kCompactLanes];
-            nbr_idx[to + k] = v0;
-            nbr_idx[to + k + kCompactLanes] = v1;
-            nbr_idx[to + k + 2 * kCompactLanes] = v2;
-            nbr_idx[to + k + 3 * kCompactLanes] = v3;
-        }
-        for (; k < c; k += kCompactLanes) nbr_idx[to + k] = mine[k];
+    const int32_t c = s < ng ? cnt[s] : 0;
+    const unsigned long long over = __ballot(c > kSlot);
+    {
+        const int32_t n = c > kSlot ? 0 : c;
+        const int32_t* const from = slots + s * kSlot;
+        int32_t* const dst = nbr_idx + nbr_off[(s < ng ? s : s0) - off0];
+        const int32_t k = lane % kCompactLanes;
+        int32_t v[kMove];
+#pragma unroll
+        for (int i = 0; i < kMove; ++i)
+            if (k + i * kCompactLanes < n) v[i] = from[k + i * kCompactLanes];
+#pragma unroll
+        for (int i = 0; i < kMove; ++i)
+            if (k + i * kCompactLanes < n) dst[k + i * kCompactLanes] = v[i];
     }
+    if (over == 0) return;
     for (int j = 0; j < kCompact; ++j) {
+        if (!((over >> (j * kCompactLanes)) & 1ull)) continue;
         const int64_t sj = s0 + j;
-        if (sj >= ng) break;
         const int64_t to = nbr_off[sj - off0];
-        if (cnt[sj] <= kSlot) continue;
         int64_t q = 0;
         nbr_scan(g, ng, sj, lane, xs, ys, zs, hs, off,
                  [&](unsigned long long mask, int64_t t, bool ok) {
