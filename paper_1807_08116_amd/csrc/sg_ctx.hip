@@ -377,21 +377,28 @@ sg_status do_build(sg_ctx* c) {
     void* scan = c->at<void>(c->L.scan);
     sg_sph_bufs b = c->sph();
     c->begin(SG_ST_SORT);
+    const bool small = sg_gas_small(c->n, C);
     sg_launch_grid(s.x, s.y, s.z, s.h, ng, g, count, hmax, C, c->prm.cell_scale_log2, st);
-    // the FP64 force records are rebuilt before every use (record builds
-    // precede each force and time-step pass), so the sort borrows their
-    // buffer for the particle-order records the gather reads
-    sg_prec* pin = reinterpret_cast<sg_prec*>(b.f64);
-    sg_launch_keys_count(s.x, s.y, s.z, s.h, s.m, ng, g, key, count, hmax, pin, st);
-    const uint32_t* sorted =
-        sg_launch_gas_order(key, ng, C, c->at<void>(c->L.gsort), c->at<int32_t>(c->L.perm), st);
-    if (sg_offsets_by_bisection(ng, C)) {
-        sg_launch_gather_gas_off(b.perm, ng, g, pin, b.xs, b.ys, b.zs, b.hs, b.ms, b.prec,
-                                 c->prm.precision, sorted, off, C, st);
+    if (small) {
+        sg_launch_gas_small(s.x, s.y, s.z, s.h, s.m, ng, g, C, key, c->at<void>(c->L.gsort), c->at<int32_t>(c->L.perm),
+                            b.xs, b.ys, b.zs, b.hs, b.ms, b.prec, c->prm.precision, off, count,
+                            hmax, st);
     } else {
-        sg_launch_scan(count, off, 0, &g->M, C, scan, st);
-        sg_launch_gather_gas(b.perm, ng, g, pin, b.xs, b.ys, b.zs, b.hs, b.ms, b.prec,
-                             c->prm.precision, st);
+        // the FP64 force records are rebuilt before every use (record builds
+        // precede each force and time-step pass), so the sort borrows their
+        // buffer for the particle-order records the gather reads
+        sg_prec* pin = reinterpret_cast<sg_prec*>(b.f64);
+        sg_launch_keys_count(s.x, s.y, s.z, s.h, s.m, ng, g, key, count, hmax, pin, st);
+        const uint32_t* sorted =
+            sg_launch_gas_order(key, ng, C, c->at<void>(c->L.gsort), c->at<int32_t>(c->L.perm), st);
+        if (sg_offsets_by_bisection(ng, C)) {
+            sg_launch_gather_gas_off(b.perm, ng, g, pin, b.xs, b.ys, b.zs, b.hs, b.ms, b.prec,
+                                     c->prm.precision, sorted, off, C, st);
+        } else {
+            sg_launch_scan(count, off, 0, &g->M, C, scan, st);
+            sg_launch_gather_gas(b.perm, ng, g, pin, b.xs, b.ys, b.zs, b.hs, b.ms, b.prec,
+                                 c->prm.precision, st);
+        }
     }
     c->end();
     c->begin(SG_ST_NBR);

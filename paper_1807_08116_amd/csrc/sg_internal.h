@@ -216,6 +216,15 @@ int sg_gas_radix_passes(int64_t cell_cap);
 // Returns the keys in sorted order (in tmp).
 const uint32_t* sg_launch_gas_order(const int32_t* key, int64_t ng, int64_t cell_cap, void* tmp,
                          int32_t* perm, hipStream_t st);
+// Keys, order, gather, cell offsets, counts and maxima in two launches, for
+// sizes where sg_gas_small says so; n: all particles.
+struct sg_prec;
+bool sg_gas_small(int64_t n, int64_t cell_cap);
+void sg_launch_gas_small(const double* x, const double* y, const double* z, const double* h,
+                         const double* m, int64_t ng, sg_grid_dev* g, int64_t cell_cap,
+                         int32_t* key, void* tmp, int32_t* perm, double* xs, double* ys, double* zs,
+                         double* hs, double* ms, sg_prec* prec, int precision, int64_t* off,
+                         int32_t* count, unsigned long long* hmax, hipStream_t st);
 void sg_launch_gather_gas(const int32_t* perm, int64_t ng, const sg_grid_dev* g,
                           const sg_prec* pin, double* xs, double* ys, double* zs, double* hs,
                           double* ms, sg_prec* prec, int precision, hipStream_t st);

@@ -481,6 +481,23 @@ __global__ __launch_bounds__(kBlock) void k_cells_clear(const sg_grid_dev* g,
     cells_clear_block(g, count, hmax, blockIdx.x, gridDim.x);
 }
 
+// h > 0: orders as bits
+__device__ inline unsigned long long h_bits(double h) {
+    return (unsigned long long)__builtin_bit_cast(long long, h);
+}
+
+// Cell key of a particle of level l.
+__device__ inline int32_t cell_key(const sg_grid_dev* g, int l, const double (&p)[3]) {
+    int64_t c[3];
+    for (int d = 0; d < 3; ++d) {
+        double v = floor((p[d] - g->org[l][d]) * g->invL[l]);
+        double top = (double)(g->dim[l][d] - 1);
+        v = v < 0.0 ? 0.0 : (v > top ? top : v);
+        c[d] = (int64_t)v;
+    }
+    return (int32_t)(g->base[l] + (c[2] * g->dim[l][1] + c[1]) * g->dim[l][0] + c[0]);
+}
+
 // Cell key of gas particle i, its count and the cell's maximum h.  Every
 // lane of the wavefront calls this (valid or not): the lanes that share the
 // key of the first valid lane add their count and maximum h with one
@@ -502,16 +519,9 @@ __device__ inline void keys_count_wave(const double* __restrict__ x, const doubl
         const int l = level_of(hi, g->L0);
         const double p[3] = {x[i], y[i], z[i]};
         rec = sg_prec{p[0], p[1], p[2], hi, m[i], {0.0, 0.0, 0.0}};
-        int64_t c[3];
-        for (int d = 0; d < 3; ++d) {
-            double v = floor((p[d] - g->org[l][d]) * g->invL[l]);
-            double top = (double)(g->dim[l][d] - 1);
-            v = v < 0.0 ? 0.0 : (v > top ? top : v);
-            c[d] = (int64_t)v;
-        }
-        k = (int32_t)(g->base[l] + (c[2] * g->dim[l][1] + c[1]) * g->dim[l][0] + c[0]);
+        k = cell_key(g, l, p);
         key[i] = k;
-        hb = (unsigned long long)__builtin_bit_cast(long long, hi);   // h > 0: orders as bits
+        hb = h_bits(hi);
     }
     // the particle's record in particle order, for the gather
     uint4 v[4];
@@ -554,6 +564,41 @@ __global__ __launch_bounds__(kBlock) void k_keys_count(const double* __restrict_
     keys_count_wave(x, y, z, h, m, i, i < ng, g, key, count, hmax, pin);
 }
 
+// Slot s of the sorted state (every lane of a quad calls this).
+__device__ inline void gather_put(int64_t s, bool live, const sg_prec& r, double* __restrict__ xs,
+                                  double* __restrict__ ys, double* __restrict__ zs,
+                                  double* __restrict__ hs, double* __restrict__ ms,
+                                  sg_prec* __restrict__ prec, bool f32) {
+    if (live) {
+        xs[s] = r.x;
+        ys[s] = r.y;
+        zs[s] = r.z;
+        hs[s] = r.h;
+        ms[s] = r.m;
+    }
+    const int32_t to = live ? (int32_t)s : -1;
+    if (f32) {
+        uint4 w[2];
+        rec_to(sg_prec32{r.x, r.y, r.z, (float)r.h, (float)r.m}, w);
+        pair_store32(prec, to, w);
+    } else {
+        uint4 v[4];
+        rec_to(r, v);
+        quad_store64(prec, to, v);
+    }
+}
+
+// Particles with a key below c, by bisection in the sorted keys.
+__device__ inline int32_t key_rank(const uint32_t* __restrict__ keys, int64_t ng, int64_t c) {
+    int32_t lo = 0, hi = (int32_t)ng;
+    while (lo < hi) {
+        const int32_t mid = (int32_t)(((uint32_t)lo + (uint32_t)hi) >> 1);
+        if ((int64_t)keys[mid] < c) lo = mid + 1;
+        else hi = mid;
+    }
+    return lo;
+}
+
 // The stable order of the gas by cell key (ascending particle id inside a
 // cell) comes from an LSD radix sort of the keys, sg_launch_gas_order;
 // here the gather of the sorted state.  The particles arrive in any order,
@@ -570,22 +615,7 @@ __device__ inline void gather_one(const int32_t* __restrict__ perm, int64_t s, i
     const bool live = s < ng;
     uint4 v[4];
     quad_load64(pin, live ? perm[s] : 0, v);
-    const sg_prec r = rec_of<sg_prec>(v);
-    if (live) {
-        xs[s] = r.x;
-        ys[s] = r.y;
-        zs[s] = r.z;
-        hs[s] = r.h;
-        ms[s] = r.m;
-    }
-    const int32_t to = live ? (int32_t)s : -1;
-    if (f32) {
-        uint4 w[2];
-        rec_to(sg_prec32{r.x, r.y, r.z, (float)r.h, (float)r.m}, w);
-        pair_store32(prec, to, w);
-    } else {
-        quad_store64(prec, to, v);
-    }
+    gather_put(s, live, rec_of<sg_prec>(v), xs, ys, zs, hs, ms, prec, f32);
 }
 
 __global__ __launch_bounds__(kBlock) void k_gather_gas(
@@ -616,15 +646,8 @@ __global__ __launch_bounds__(kBlock) void k_gather_gas_off(
     }
     const int64_t M = g->M;
     for (int64_t c = (int64_t)(blockIdx.x - nbg) * kBlock + threadIdx.x; c <= M;
-         c += (int64_t)(gridDim.x - nbg) * kBlock) {
-        int32_t lo = 0, hi = (int32_t)ng;
-        while (lo < hi) {
-            const int32_t mid = (int32_t)(((uint32_t)lo + (uint32_t)hi) >> 1);
-            if ((int64_t)keys[mid] < c) lo = mid + 1;
-            else hi = mid;
-        }
-        off[c] = lo;
-    }
+         c += (int64_t)(gridDim.x - nbg) * kBlock)
+        off[c] = key_rank(keys, ng, c);
 }
 
 // ------------------------------------------------------ Morton ordering --
@@ -697,6 +720,18 @@ __device__ inline uint32_t spread3(uint32_t v) {   // 10 bits -> every third bit
     return v;
 }
 
+// Key of a point in the cube of side ext (1 + 2^-20) at lo: 10 bits an axis.
+__device__ inline uint32_t morton_key(const double (&p)[3], const double (&lo)[3], double ext) {
+    const double scale = ext > 0.0 ? 1024.0 / (ext * (1.0 + 0x1p-20)) : 0.0;
+    uint32_t c[3];
+    for (int d = 0; d < 3; ++d) {
+        double v = (p[d] - lo[d]) * scale;
+        v = v < 0.0 ? 0.0 : (v > 1023.0 ? 1023.0 : v);
+        c[d] = (uint32_t)v;
+    }
+    return spread3(c[0]) | (spread3(c[1]) << 1) | (spread3(c[2]) << 2);
+}
+
 __device__ inline void morton_key_one(const double* __restrict__ x, const double* __restrict__ y,
                                       const double* __restrict__ z, int64_t i,
                                       const sg_grid_dev* g, uint32_t* __restrict__ keys) {
@@ -706,15 +741,8 @@ __device__ inline void morton_key_one(const double* __restrict__ x, const double
         double e = sg_unord(g->ghi[d]) - lo[d];
         ext = e > ext ? e : ext;
     }
-    const double scale = ext > 0.0 ? 1024.0 / (ext * (1.0 + 0x1p-20)) : 0.0;
     const double p[3] = {x[i], y[i], z[i]};
-    uint32_t c[3];
-    for (int d = 0; d < 3; ++d) {
-        double v = (p[d] - lo[d]) * scale;
-        v = v < 0.0 ? 0.0 : (v > 1023.0 ? 1023.0 : v);
-        c[d] = (uint32_t)v;
-    }
-    keys[i] = spread3(c[0]) | (spread3(c[1]) << 1) | (spread3(c[2]) << 2);
+    keys[i] = morton_key(p, lo, ext);
 }
 
 __global__ __launch_bounds__(kBlock) void k_morton_keys(const double* __restrict__ x,
@@ -758,9 +786,15 @@ __global__ __launch_bounds__(kBlock) void k_radix_hist(const uint32_t* __restric
 }
 
 // Stable scatter: element order inside the tile is preserved within each
-// digit (chunk by chunk, wave by wave, lane by lane).  Per chunk, the first
-// lane of each (wave, digit) group publishes the group's size; after the
-// writes it adds that size to the digit's running count and clears its slot.
+// digit.  A wavefront takes a contiguous quarter of the tile and counts its
+// digits in an LDS column of its own, in order and without a barrier: the
+// count it finds is the rank of an element among its digit's earlier ones in
+// the quarter.  One barrier later the columns of the wavefronts before it
+// are known.  Bound by latency (one load of every element in flight, then
+// ITEMS rounds of ten ballots and an LDS exchange), not by memory; with
+// chunks of kBlock elements shared by the wavefronts, three barriers and a
+// load to wait for in every round, a pass of 8192 keys took 10.7 us where
+// this takes 7.6, one of 131071 13.5 (10.6), one of 1048576 23.8 (20.5).
 // vin == nullptr stands for the values 0, 1, 2, .. (the element indices).
 // ROWS: first positions by digit in s_base (LDS) instead of offs.
 template <int ITEMS = kRadixItems, bool ROWS = false>
@@ -770,49 +804,51 @@ __device__ inline void radix_scatter_tile(const uint32_t* __restrict__ kin,
                                           uint32_t* __restrict__ kout,
                                           int32_t* __restrict__ vout, int64_t tile,
                                           const int32_t* s_base = nullptr) {
-    // a (wave, digit) group of one chunk has at most 64 members: one byte
-    // each keeps the workgroup's LDS at 8 KB, small enough to find room on
-    // CUs that a persistent gravity kernel mostly fills
-    __shared__ int32_t s_run[kBuckets];
-    __shared__ uint8_t s_w[kBlock / 64][kBuckets];
-    const int wave = threadIdx.x >> 6;
-    for (int t = threadIdx.x; t < kBuckets; t += kBlock) {
-        s_run[t] = 0;
-        for (int w = 0; w < kBlock / 64; ++w) s_w[w][t] = 0;
-    }
-    __syncthreads();
-    const int64_t base = tile * (kBlock * ITEMS);
+    // 8 KB of LDS: small enough to find room on CUs that a gravity kernel
+    // mostly fills
+    constexpr int kWaves = kBlock / 64;
+    static_assert(64 * ITEMS < 65536, "counts of a quarter in 16 bits");
+    __shared__ uint16_t s_cnt[kWaves][kBuckets];
+    const int wave = threadIdx.x >> 6, lane = (int)lane_id();
+    const int64_t base = tile * (kBlock * ITEMS) + wave * (64 * ITEMS) + lane;
+    uint32_t key[ITEMS];
+    int32_t val[ITEMS], rank[ITEMS];
+#pragma unroll
     for (int k = 0; k < ITEMS; ++k) {
-        const int64_t i = base + k * kBlock + threadIdx.x;
-        if (ROWS && base + k * kBlock >= n) break;
-        const bool valid = i < n;
-        const uint32_t key = valid ? kin[i] : 0u;
-        const int32_t val = valid ? (vin ? vin[i] : (int32_t)i) : 0;
-        const uint32_t d = (key >> shift) & (kBuckets - 1);
+        const int64_t i = base + 64 * k;
+        key[k] = i < n ? kin[i] : 0u;
+        val[k] = i < n ? (vin ? vin[i] : (int32_t)i) : 0;
+    }
+    uint16_t* const cnt = s_cnt[wave];
+    for (int t = 2 * lane; t < kBuckets; t += 128) cnt[t] = cnt[t + 1] = 0;
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        const bool valid = base + 64 * k < n;
+        const uint32_t d = (key[k] >> shift) & (kBuckets - 1);
         unsigned long long peers = __ballot(valid);
+#pragma unroll
         for (int b = 0; b < kRadixBits; ++b) {
-            unsigned long long bb = __ballot(valid && ((d >> b) & 1u));
+            const unsigned long long bb = __ballot((d >> b) & 1u);
             peers &= ((d >> b) & 1u) ? bb : ~bb;
         }
-        const unsigned r = rank_below(peers);
-        const int cnt = __builtin_popcountll(peers);
-        const bool lead = valid && r == 0;
-        if (lead) s_w[wave][d] = (uint8_t)cnt;
-        __syncthreads();
-        if (valid) {
-            int32_t pre = 0;
-            for (int w = 0; w < wave; ++w) pre += s_w[w][d];
-            const int64_t first = ROWS ? (int64_t)s_base[d] : offs[(int64_t)d * ntiles + tile];
-            const int64_t dest = first + s_run[d] + pre + r;
-            kout[dest] = key;
-            vout[dest] = val;
-        }
-        __syncthreads();
-        if (lead) {
-            atomicAdd(&s_run[d], cnt);
-            s_w[wave][d] = 0;
-        }
-        __syncthreads();
+        const int r = (int)rank_below(peers);
+        const int before = cnt[d];
+        rank[k] = before + r;
+        __builtin_amdgcn_wave_barrier();
+        if (valid && r == 0) cnt[d] = (uint16_t)(before + __builtin_popcountll(peers));
+        __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        if (base + 64 * k >= n) break;                     // (later elements lie further up)
+        const uint32_t d = (key[k] >> shift) & (kBuckets - 1);
+        int32_t pre = rank[k];
+        for (int w = 0; w < wave; ++w) pre += s_cnt[w][d];
+        const int64_t dest = (ROWS ? (int64_t)s_base[d] : offs[(int64_t)d * ntiles + tile]) + pre;
+        kout[dest] = key[k];
+        vout[dest] = val[k];
     }
 }
 
@@ -828,10 +864,13 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(
 // itself (4 KB a tile from L2; four digits a lane) instead of three launches
 // of a scan: at 8192 keys a pass took 30 us, of which the scan 10 and the
 // scatter's 16 rounds 18.  Tiles shrink with n to fewer rounds of more
-// workgroups.  With the launches saved by k_grid_levels (which finishes the
-// grid), k_grid_hmin (which clears small tables) and k_gather_gas_off, the
-// sort stage went from 73 to 37 us at 1009 gas particles, 107 to 54 at 9001,
-// 136 to 79 at 65536, 198 to 136 at 131071 and 243 to 208 at 262144.
+// workgroups.  (Counting a pass's histograms in the scatter before it, by
+// global additions into the destination's tile, saves that launch too, but
+// cost more: a pass of 131071 keys 24.7 us against 10.6 + 4.8.)  With the
+// launches saved by k_grid_levels (which finishes the grid), k_grid_hmin
+// (which clears small tables) and k_gather_gas_off, the sort stage went from
+// 107 to 48 us at 9001 gas particles, 136 to 70 at 65536, 198 to 123 at
+// 131071 and 243 to 184 at 262144.
 constexpr int64_t kRowTiles = 64;
 template <int ITEMS>
 __global__ __launch_bounds__(kBlock) void k_radix_hist_rows(const uint32_t* __restrict__ keys,
@@ -879,6 +918,239 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter_rows(
     s_base[4 * tid + 3] = first + tot.x + tot.y + tot.z + pre.w;
     // (radix_scatter_tile synchronises before it reads them)
     radix_scatter_tile<ITEMS, true>(kin, vin, n, shift, ntiles, nullptr, kout, vout, tile, s_base);
+}
+
+// ------------------------------------------------ a few thousand particles --
+//
+// Keys and all passes of their sort in one launch: a workgroup of 1024 lanes
+// holds up to 4096 keys and indices in LDS.  A pass is radix_scatter_tile's,
+// with sixteen wavefronts' columns of counts summed by the lanes (a digit
+// each) instead of by another launch; bound by latency (barriers, LDS round
+// trips, the ballots of one compute unit).  The general chains take eight
+// launches (Morton order) and five (gas) that cost the host 4-6 us each.
+// Measured: Morton order of 2552 particles 28 us in eight kernels, 22 in
+// one; keys to sorted state of 1009 gas particles 23 us in six, 14 in two
+// (sort stage 34 -> 26 us; 4096: 43 -> 40).  A step of 1009 + 1543 particles
+// went from 148 to 117 us.  (Up to 8192 keys the order takes 39 us instead of
+// 41, but sixteen steps of 4096 + 4096 took anything from 2.9 to 3.6 ms
+// against 3.25: gravity then runs beside the gas sort's one workgroup.)
+constexpr int kSmall = 4096;
+constexpr int kSmallBlock = 1024;
+constexpr int kSmallItems = kSmall / kSmallBlock;
+struct small_lds {
+    uint32_t key[kSmall];
+    uint16_t idx[kSmall];
+    uint16_t cnt[kSmallBlock / 64][kBuckets];
+    int32_t first[kBuckets];
+    int32_t wsum[kSmallBlock / 64];
+};
+static_assert(kBuckets == kSmallBlock, "a lane a digit");
+
+// inclusive prefix sum over the wavefront (every lane active)
+__device__ inline int32_t wave_incl_sum_dpp(int32_t v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr 1, 2, 4, 8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast 15, 31
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+    return v;
+}
+
+// Stable order of L.key / L.idx [0, n) over `passes` digits.
+__device__ inline void small_sort(small_lds& L, int n, int passes) {
+    const int tid = threadIdx.x, w = tid >> 6, lane = (int)lane_id();
+    const int items = (n + kSmallBlock - 1) / kSmallBlock;
+    const int base = w * 64 * items + lane;
+    uint16_t* const cnt = L.cnt[w];
+    for (int pass = 0; pass < passes; ++pass) {
+        const int shift = kRadixBits * pass;
+        uint32_t key[kSmallItems];
+        int32_t idx[kSmallItems], rank[kSmallItems];
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kSmallItems; ++k) {
+            if (k >= items) break;                         // uniform
+            const int i = base + 64 * k;
+            key[k] = i < n ? L.key[i] : 0u;
+            idx[k] = i < n ? L.idx[i] : 0;
+        }
+        for (int t = 2 * lane; t < kBuckets; t += 128) cnt[t] = cnt[t + 1] = 0;
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int k = 0; k < kSmallItems; ++k) {
+            if (k >= items) break;
+            const bool valid = base + 64 * k < n;
+            const uint32_t d = (key[k] >> shift) & (kBuckets - 1);
+            unsigned long long peers = __ballot(valid);
+#pragma unroll
+            for (int b = 0; b < kRadixBits; ++b) {
+                const unsigned long long bb = __ballot((d >> b) & 1u);
+                peers &= ((d >> b) & 1u) ? bb : ~bb;
+            }
+            const int r = (int)rank_below(peers), before = cnt[d];
+            rank[k] = before + r;
+            __builtin_amdgcn_wave_barrier();
+            if (valid && r == 0) cnt[d] = (uint16_t)(before + __builtin_popcountll(peers));
+            __builtin_amdgcn_wave_barrier();
+        }
+        __syncthreads();
+        int32_t sum = 0;                                   // digit tid
+#pragma unroll
+        for (int v = 0; v < kSmallBlock / 64; ++v) {
+            const int32_t c = L.cnt[v][tid];
+            L.cnt[v][tid] = (uint16_t)sum;
+            sum += c;
+        }
+        const int32_t incl = wave_incl_sum_dpp(sum);
+        if (lane == 63) L.wsum[w] = incl;
+        __syncthreads();
+        const int32_t ws = wave_incl_sum_dpp(lane < w ? L.wsum[lane] : 0);   // (w < 64)
+        L.first[tid] = incl - sum + __builtin_amdgcn_readlane(ws, 63);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kSmallItems; ++k) {
+            if (k >= items || base + 64 * k >= n) break;
+            const uint32_t d = (key[k] >> shift) & (kBuckets - 1);
+            const int dest = L.first[d] + cnt[d] + rank[k];
+            L.key[dest] = key[k];
+            L.idx[dest] = (uint16_t)idx[k];
+        }
+    }
+    __syncthreads();
+}
+
+__global__ __launch_bounds__(kSmallBlock) void k_morton_small(const double* __restrict__ x,
+                                                              const double* __restrict__ y,
+                                                              const double* __restrict__ z, int n,
+                                                              sg_grid_dev* g,
+                                                              int32_t* __restrict__ order) {
+    __shared__ small_lds L;
+    __shared__ unsigned long long s_lo[3][kSmallBlock / 64], s_hi[3][kSmallBlock / 64];
+    const int tid = threadIdx.x;
+    unsigned long long mn[3] = {~0ull, ~0ull, ~0ull}, mx[3] = {0, 0, 0};
+    bool bad = false;
+    const int items = (n + kSmallBlock - 1) / kSmallBlock;
+    double p[kSmallItems][3];
+#pragma unroll
+    for (int k = 0; k < kSmallItems; ++k) {
+        if (k >= items) break;                             // uniform
+        const int i = tid + k * kSmallBlock < n ? tid + k * kSmallBlock : 0;
+        p[k][0] = x[i];
+        p[k][1] = y[i];
+        p[k][2] = z[i];
+    }
+#pragma unroll
+    for (int k = 0; k < kSmallItems; ++k) {
+        if (k >= items) break;
+        for (int d = 0; d < 3; ++d) {                      // (a repeated point 0 does no harm)
+            if (!finite_d(p[k][d])) {
+                bad = true;
+                continue;
+            }
+            const unsigned long long o = sg_ord(p[k][d]);
+            mn[d] = o < mn[d] ? o : mn[d];
+            mx[d] = o > mx[d] ? o : mx[d];
+        }
+    }
+    if (bad) atomicOr(&g->err, SGE_GNONFINITE);
+    for (int d = 0; d < 3; ++d) {
+        const unsigned long long a = wave_min_u64(mn[d]), b = wave_max_u64(mx[d]);
+        if (lane_id() == 0) {
+            s_lo[d][tid >> 6] = a;
+            s_hi[d][tid >> 6] = b;
+        }
+    }
+    __syncthreads();
+    double lo[3], ext = 0.0;
+    for (int d = 0; d < 3; ++d) {
+        unsigned long long a = s_lo[d][0], b = s_hi[d][0];
+        for (int k = 1; k < kSmallBlock / 64; ++k) {
+            a = s_lo[d][k] < a ? s_lo[d][k] : a;
+            b = s_hi[d][k] > b ? s_hi[d][k] : b;
+        }
+        lo[d] = sg_unord(a);
+        const double e = sg_unord(b) - lo[d];
+        ext = e > ext ? e : ext;
+    }
+#pragma unroll
+    for (int k = 0; k < kSmallItems; ++k) {
+        if (k >= items) break;
+        const int i = tid + k * kSmallBlock;
+        if (i < n) {
+            L.key[i] = morton_key(p[k], lo, ext);
+            L.idx[i] = (uint16_t)i;
+        }
+    }
+    small_sort(L, n, kRadixPasses);
+    for (int i = tid; i < n; i += kSmallBlock) order[i] = L.idx[i];
+}
+
+// Cell keys, their stable order and the keys in it.
+__global__ __launch_bounds__(kSmallBlock) void k_keys_small(
+    const double* __restrict__ x, const double* __restrict__ y, const double* __restrict__ z,
+    const double* __restrict__ h, int ng, const sg_grid_dev* g, int passes,
+    int32_t* __restrict__ key, uint32_t* __restrict__ sorted, int32_t* __restrict__ perm) {
+    __shared__ small_lds L;
+    if (g->err & SGE_SORT_FATAL) return;
+    const int tid = threadIdx.x;
+    const int items = (ng + kSmallBlock - 1) / kSmallBlock;
+    double p[kSmallItems][3], hi[kSmallItems];
+#pragma unroll
+    for (int k = 0; k < kSmallItems; ++k) {
+        if (k >= items) break;                             // uniform
+        const int i = tid + k * kSmallBlock < ng ? tid + k * kSmallBlock : 0;
+        p[k][0] = x[i];
+        p[k][1] = y[i];
+        p[k][2] = z[i];
+        hi[k] = h[i];
+    }
+#pragma unroll
+    for (int k = 0; k < kSmallItems; ++k) {
+        if (k >= items) break;
+        const int i = tid + k * kSmallBlock;
+        if (i < ng) {
+            const int32_t c = cell_key(g, level_of(hi[k], g->L0), p[k]);
+            key[i] = c;
+            L.key[i] = (uint32_t)c;
+            L.idx[i] = (uint16_t)i;
+        }
+    }
+    small_sort(L, ng, passes);
+    for (int i = tid; i < ng; i += kSmallBlock) {
+        sorted[i] = L.key[i];
+        perm[i] = L.idx[i];
+    }
+}
+
+// k_gather_gas_off from the particle-order arrays, with the counts and
+// maximum h of the cells, which the key pass leaves to it.
+__global__ __launch_bounds__(kBlock) void k_gather_gas_small(
+    const int32_t* __restrict__ perm, int64_t ng, const sg_grid_dev* g,
+    const double* __restrict__ x, const double* __restrict__ y, const double* __restrict__ z,
+    const double* __restrict__ h, const double* __restrict__ m, double* __restrict__ xs,
+    double* __restrict__ ys, double* __restrict__ zs, double* __restrict__ hs,
+    double* __restrict__ ms, sg_prec* __restrict__ prec, int f32, int nbg,
+    const uint32_t* __restrict__ keys, int64_t* __restrict__ off, int32_t* __restrict__ count,
+    unsigned long long* __restrict__ hmax) {
+    if (g->err & SGE_SORT_FATAL) return;
+    if ((int)blockIdx.x < nbg) {
+        const int64_t s = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+        const bool live = s < ng;
+        const int32_t i = live ? perm[s] : 0;
+        const sg_prec r{x[i], y[i], z[i], h[i], m[i], {0.0, 0.0, 0.0}};
+        if (live) {
+            const uint32_t c = keys[s];
+            atomicAdd(&count[c], 1);
+            atomicMax(&hmax[c], h_bits(r.h));
+        }
+        gather_put(s, live, r, xs, ys, zs, hs, ms, prec, f32 != 0);
+        return;
+    }
+    const int64_t M = g->M;
+    for (int64_t c = (int64_t)(blockIdx.x - nbg) * kBlock + threadIdx.x; c <= M;
+         c += (int64_t)(gridDim.x - nbg) * kBlock)
+        off[c] = key_rank(keys, ng, c);
 }
 
 // ---------------------------------------- Morton order, all systems at once --
@@ -1149,6 +1421,29 @@ void sg_launch_status_clear(sg_grid_dev* g, bool record, hipStream_t st) {
 // h (12 bytes a cell, a few us at most) instead of by a launch of their own.
 constexpr int64_t kClearWhole = 1 << 20;
 
+// The one-workgroup kernels take up to kSmall keys, and the gas takes them by
+// the number of all particles: beside a gravity kernel that fills the compute
+// units a workgroup of 1024 lanes waits for its end.
+bool sg_gas_small(int64_t n, int64_t cell_cap) {
+    return n <= kSmall && cell_cap <= kClearWhole;
+}
+
+void sg_launch_gas_small(const double* x, const double* y, const double* z, const double* h,
+                         const double* m, int64_t ng, sg_grid_dev* g, int64_t cell_cap,
+                         int32_t* key, void* tmp, int32_t* perm, double* xs, double* ys, double* zs,
+                         double* hs, double* ms, sg_prec* prec, int precision, int64_t* off,
+                         int32_t* count, unsigned long long* hmax, hipStream_t st) {
+    uint32_t* const sorted = static_cast<uint32_t*>(tmp);
+    hipLaunchKernelGGL(k_keys_small, dim3(1), dim3(kSmallBlock), 0, st, x, y, z, h, (int)ng, g,
+                       sg_gas_radix_passes(cell_cap), key, sorted, perm);
+    const unsigned nbg = grid_for(ng, kBlock);
+    unsigned nbc = grid_for(cell_cap + 1, kBlock);
+    if (nbc > 2048) nbc = 2048;
+    hipLaunchKernelGGL(k_gather_gas_small, dim3(nbg + nbc), dim3(kBlock), 0, st, perm, ng, g, x, y,
+                       z, h, m, xs, ys, zs, hs, ms, prec, precision == SG_FP32C ? 1 : 0, (int)nbg,
+                       sorted, off, count, hmax);
+}
+
 void sg_launch_grid(const double* x, const double* y, const double* z, const double* h, int64_t ng,
                     sg_grid_dev* g, int32_t* count, unsigned long long* hmax, int64_t cell_cap,
                     int cell_scale_log2, hipStream_t st) {
@@ -1376,6 +1671,11 @@ void sg_launch_morton_order(const double* x, const double* y, const double* z, i
     int64_t* offs = (int64_t*)(base + o_offs);
     void* scan_tmp = base + o_scan;
     unsigned nb = grid_for(n, kBlock);
+    if (n <= kSmall) {
+        hipLaunchKernelGGL(k_morton_small, dim3(1), dim3(kSmallBlock), 0, st, x, y, z, (int)n, g,
+                           order);
+        return;
+    }
     hipLaunchKernelGGL(k_gbox, dim3(nb > 512 ? 512 : nb), dim3(kBlock), 0, st, x, y, z, n, g);
     hipLaunchKernelGGL(k_morton_keys, dim3(nb), dim3(kBlock), 0, st, x, y, z, n, g, k[0]);
     // the first pass takes the values 0 .. n-1 from the element indices

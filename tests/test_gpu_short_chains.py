@@ -1,8 +1,9 @@
 """The launch-saving forms of the sort, list and record passes at the sizes
 where they hand over to the general ones: tiles of the two-launch radix pass
-(3072, 131072 and 262144 keys), offsets by bisection and records without
-packing (65536 particles), the copy that adds up its own offsets (16384), and
-cell tables cleared whole (2^20 cells).  Integers bit for bit."""
+(3072, 131072 and 262144 keys), sorts in one workgroup (4096 particles),
+offsets by bisection and records without packing (65536 particles), the copy
+that adds up its own offsets (16384), and cell tables cleared whole (2^20
+cells).  Integers bit for bit."""
 import numpy as np
 import pytest
 
@@ -40,11 +41,15 @@ def check_lists(sg, ctx, st):
         np.testing.assert_array_equal(ctx.export(what), ref)
 
 
-@pytest.mark.parametrize("ng", [1024, 1025, 3072, 3073, 16384, 16385, 65536, 65537, 130561, 131072,
-                                131073, 262144, 262145])
-def test_sort_and_lists(sg, ng):
+@pytest.mark.parametrize("ng,nh", [(1, 0), (63, 0), (1024, 0), (1025, 0), (3072, 0), (3073, 0),
+                                   (4096, 0), (4095, 2), (4097, 0), (2000, 2096), (2000, 2097),
+                                   (16384, 0), (16385, 0), (65536, 0), (65537, 0), (130561, 0), (131072, 0),
+                                   (131073, 0), (262144, 0), (262145, 0)])
+def test_sort_and_lists(sg, ng, nh):
     st = gas(ng)
-    eng = sg.Engine(st, precision=sg.SG_FP64)
+    halo = {f: np.concatenate([st[f], np.random.default_rng(1).normal(0, 1, nh)])
+            for f in ("x", "y", "z", "vx", "vy", "vz", "m")}
+    eng = sg.Engine(dict(st, **halo), precision=sg.SG_FP64)
     eng.build_neighbors()
     for _ in range(2):                     # the second build starts from what the first left
         eng.ctx.build_neighbors()
@@ -53,7 +58,8 @@ def test_sort_and_lists(sg, ng):
     eng.ctx.close()
 
 
-@pytest.mark.parametrize("n", [1, 1024, 3072, 3073, 131072, 131073, 262144, 262145])
+@pytest.mark.parametrize("n", [1, 65, 1024, 3072, 3073, 4095, 4096, 4097, 131072, 131073, 262144,
+                               262145])
 def test_morton_order(sg, n):
     st = gas(n)
     st.update(ng=0, h=np.zeros(0), e=np.zeros(0))
