@@ -388,16 +388,16 @@ sg_status do_build(sg_ctx* c) {
         // precede each force and time-step pass), so the sort borrows their
         // buffer for the particle-order records the gather reads
         sg_prec* pin = reinterpret_cast<sg_prec*>(b.f64);
-        sg_launch_keys_count(s.x, s.y, s.z, s.h, s.m, ng, g, key, count, hmax, pin, st);
+        sg_launch_gas_keys(s.x, s.y, s.z, s.h, s.m, ng, g, key, pin, st);
         const uint32_t* sorted =
             sg_launch_gas_order(key, ng, C, c->at<void>(c->L.gsort), c->at<int32_t>(c->L.perm), st);
         if (sg_offsets_by_bisection(ng, C)) {
             sg_launch_gather_gas_off(b.perm, ng, g, pin, b.xs, b.ys, b.zs, b.hs, b.ms, b.prec,
-                                     c->prm.precision, sorted, off, C, st);
+                                     c->prm.precision, sorted, off, C, count, hmax, st);
         } else {
-            sg_launch_scan(count, off, 0, &g->M, C, scan, st);
             sg_launch_gather_gas(b.perm, ng, g, pin, b.xs, b.ys, b.zs, b.hs, b.ms, b.prec,
-                                 c->prm.precision, st);
+                                 c->prm.precision, sorted, count, hmax, st);
+            sg_launch_scan(count, off, 0, &g->M, C, scan, st);
         }
     }
     c->end();

@@ -202,13 +202,12 @@ void sg_launch_status_clear(sg_grid_dev* g, bool record, hipStream_t st);
 void sg_launch_grid(const double* x, const double* y, const double* z, const double* h, int64_t ng,
                     sg_grid_dev* g, int32_t* count, unsigned long long* hmax, int64_t cell_cap,
                     int cell_scale_log2, hipStream_t st);
-// Cell keys, per-cell counts and max h; also each particle's record
-// (x, y, z, h, m) in particle order into pin [ng] (scratch the gather reads).
+// Cell keys; also each particle's record (x, y, z, h, m) in particle order
+// into pin [ng] (scratch the gather reads).
 struct sg_prec;
-void sg_launch_keys_count(const double* x, const double* y, const double* z, const double* h,
-                          const double* m, int64_t ng, sg_grid_dev* g, int32_t* key,
-                          int32_t* count, unsigned long long* hmax, sg_prec* pin,
-                          hipStream_t st);
+void sg_launch_gas_keys(const double* x, const double* y, const double* z, const double* h,
+                        const double* m, int64_t ng, sg_grid_dev* g, int32_t* key, sg_prec* pin,
+                        hipStream_t st);
 // Stable order of the gas by cell key (ascending id inside a cell): LSD
 // radix sort of the keys with 10-bit digits, enough passes for keys below
 // cell_cap; tmp: sg_morton_tmp_bytes(ng) bytes.
@@ -227,14 +226,16 @@ void sg_launch_gas_small(const double* x, const double* y, const double* z, cons
                          int32_t* count, unsigned long long* hmax, hipStream_t st);
 void sg_launch_gather_gas(const int32_t* perm, int64_t ng, const sg_grid_dev* g,
                           const sg_prec* pin, double* xs, double* ys, double* zs, double* hs,
-                          double* ms, sg_prec* prec, int precision, hipStream_t st);
+                          double* ms, sg_prec* prec, int precision, const uint32_t* keys,
+                          int32_t* count, unsigned long long* hmax, hipStream_t st);
 // The gather with the cell offsets from the sorted keys beside it, for sizes
 // where that beats the scan of the counts.
 bool sg_offsets_by_bisection(int64_t ng, int64_t cell_cap);
 void sg_launch_gather_gas_off(const int32_t* perm, int64_t ng, const sg_grid_dev* g,
                               const sg_prec* pin, double* xs, double* ys, double* zs, double* hs,
                               double* ms, sg_prec* prec, int precision, const uint32_t* keys,
-                              int64_t* off, int64_t cell_cap, hipStream_t st);
+                              int64_t* off, int64_t cell_cap, int32_t* count, unsigned long long* hmax,
+                              hipStream_t st);
 
 // Neighbour lists.
 // Neighbour search: per-target slots of fixed length (sg_nbr_slot_bytes),

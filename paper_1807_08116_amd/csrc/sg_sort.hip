@@ -503,16 +503,14 @@ __device__ inline int32_t cell_key(const sg_grid_dev* g, int l, const double (&p
 // key of the first valid lane add their count and maximum h with one
 // atomic each (clustered or coincident gas puts many particles of a
 // wavefront in one cell); the others add their own.
-__device__ inline void keys_count_wave(const double* __restrict__ x, const double* __restrict__ y,
-                                       const double* __restrict__ z,
-                                       const double* __restrict__ h,
-                                       const double* __restrict__ m, int64_t i, bool valid,
-                                       const sg_grid_dev* g, int32_t* __restrict__ key,
-                                       int32_t* __restrict__ count,
-                                       unsigned long long* __restrict__ hmax,
-                                       sg_prec* __restrict__ pin) {
+// Key and, in particle order, record of particle i (every lane of a quad
+// calls this); returns the key, *hb the bits of h.
+__device__ inline int32_t key_one(const double* __restrict__ x, const double* __restrict__ y,
+                                  const double* __restrict__ z, const double* __restrict__ h,
+                                  const double* __restrict__ m, int64_t i, bool valid,
+                                  const sg_grid_dev* g, int32_t* __restrict__ key,
+                                  sg_prec* __restrict__ pin, unsigned long long* hb = nullptr) {
     int32_t k = -1;
-    unsigned long long hb = 0ull;
     sg_prec rec{};
     if (valid) {
         const double hi = h[i];
@@ -521,12 +519,26 @@ __device__ inline void keys_count_wave(const double* __restrict__ x, const doubl
         rec = sg_prec{p[0], p[1], p[2], hi, m[i], {0.0, 0.0, 0.0}};
         k = cell_key(g, l, p);
         key[i] = k;
-        hb = h_bits(hi);
+        if (hb) *hb = h_bits(hi);
     }
     // the particle's record in particle order, for the gather
     uint4 v[4];
     rec_to(rec, v);
     quad_store64(pin, valid ? (int32_t)i : -1, v);
+    return k;
+}
+
+// The same with the cells' counts and maxima, by atomics (an ensemble's).
+__device__ inline void keys_count_wave(const double* __restrict__ x, const double* __restrict__ y,
+                                       const double* __restrict__ z,
+                                       const double* __restrict__ h,
+                                       const double* __restrict__ m, int64_t i, bool valid,
+                                       const sg_grid_dev* g, int32_t* __restrict__ key,
+                                       int32_t* __restrict__ count,
+                                       unsigned long long* __restrict__ hmax,
+                                       sg_prec* __restrict__ pin) {
+    unsigned long long hb = 0ull;
+    const int32_t k = key_one(x, y, z, h, m, i, valid, g, key, pin, &hb);
     bool done = !valid;
     const unsigned long long act = __ballot(valid);
     if (act) {
@@ -549,19 +561,55 @@ __device__ inline void keys_count_wave(const double* __restrict__ x, const doubl
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_keys_count(const double* __restrict__ x,
-                                                       const double* __restrict__ y,
-                                                       const double* __restrict__ z,
-                                                       const double* __restrict__ h,
-                                                       const double* __restrict__ m,
-                                                       int64_t ng, const sg_grid_dev* g,
-                                                       int32_t* __restrict__ key,
-                                                       int32_t* __restrict__ count,
-                                                       unsigned long long* __restrict__ hmax,
-                                                       sg_prec* __restrict__ pin) {
+// Keys and records; the counts and maxima of the cells are left to the gather
+// (cell_stats), where particles of a cell lie side by side.
+__global__ __launch_bounds__(kBlock) void k_gas_keys(const double* __restrict__ x,
+                                                     const double* __restrict__ y,
+                                                     const double* __restrict__ z,
+                                                     const double* __restrict__ h,
+                                                     const double* __restrict__ m, int64_t ng,
+                                                     const sg_grid_dev* g,
+                                                     int32_t* __restrict__ key,
+                                                     sg_prec* __restrict__ pin) {
     if (g->err & SGE_SORT_FATAL) return;
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    keys_count_wave(x, y, z, h, m, i, i < ng, g, key, count, hmax, pin);
+    key_one(x, y, z, h, m, i, i < ng, g, key, pin);
+}
+
+// Counts and maximum h of the cells from the sorted keys: lanes of a
+// wavefront hold consecutive slots s, so a cell's particles are neighbours
+// and its last lane writes.  Cells that reach into another wavefront's slots
+// add to the cleared tables.  (Atomics per particle from the key pass, in
+// particle order, each went to a line of its own: with them that pass took
+// 117 us at 1048576 particles, without KEYS, and the gather GATHER.)
+__device__ inline void cell_stats(const uint32_t* __restrict__ keys, int64_t s, int64_t ng,
+                                  double h, int32_t* __restrict__ count,
+                                  unsigned long long* __restrict__ hmax) {
+    const int lane = (int)lane_id();
+    const bool live = s < ng;
+    const uint32_t k = live ? keys[s] : ~0u;               // (keys are below 2^31)
+    unsigned long long v = live ? h_bits(h) : 0ull;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t k2 = __shfl_up(k, o, 64);
+        const unsigned long long v2 = __shfl_up(v, o, 64);
+        if (lane >= o && k2 == k && v2 > v) v = v2;
+    }
+    uint32_t prev = __shfl_up(k, 1, 64), next = __shfl_down(k, 1, 64);
+    if (lane == 0) prev = s > 0 && live ? keys[s - 1] : ~0u;
+    if (lane == 63) next = s + 1 < ng ? keys[s + 1] : ~0u;
+    const unsigned long long heads = __ballot(prev != k || lane == 0);
+    const bool cut = __ballot(lane == 0 && prev == k) != 0;    // lane 0 is no first particle
+    if (!live || (next == k && lane != 63)) return;
+    const int first = 63 - __builtin_clzll(heads & (~0ull >> (63 - lane)));
+    const int32_t n = lane - first + 1;
+    if ((first == 0 && cut) || next == k) {
+        atomicAdd(&count[k], n);
+        atomicMax(&hmax[k], v);
+    } else {
+        count[k] = n;
+        hmax[k] = v;
+    }
 }
 
 // Slot s of the sorted state (every lane of a quad calls this).
@@ -611,21 +659,27 @@ __device__ inline void gather_one(const int32_t* __restrict__ perm, int64_t s, i
                                   const sg_prec* __restrict__ pin, double* __restrict__ xs,
                                   double* __restrict__ ys, double* __restrict__ zs,
                                   double* __restrict__ hs, double* __restrict__ ms,
-                                  sg_prec* __restrict__ prec, bool f32) {
+                                  sg_prec* __restrict__ prec, bool f32,
+                                  const uint32_t* __restrict__ keys = nullptr,
+                                  int32_t* __restrict__ count = nullptr,
+                                  unsigned long long* __restrict__ hmax = nullptr) {
     const bool live = s < ng;
     uint4 v[4];
     quad_load64(pin, live ? perm[s] : 0, v);
-    gather_put(s, live, rec_of<sg_prec>(v), xs, ys, zs, hs, ms, prec, f32);
+    const sg_prec r = rec_of<sg_prec>(v);
+    if (count) cell_stats(keys, s, ng, r.h, count, hmax);
+    gather_put(s, live, r, xs, ys, zs, hs, ms, prec, f32);
 }
 
 __global__ __launch_bounds__(kBlock) void k_gather_gas(
     const int32_t* __restrict__ perm, int64_t ng, const sg_grid_dev* g,
     const sg_prec* __restrict__ pin, double* __restrict__ xs, double* __restrict__ ys,
     double* __restrict__ zs, double* __restrict__ hs, double* __restrict__ ms,
-    sg_prec* __restrict__ prec, int f32) {
+    sg_prec* __restrict__ prec, int f32, const uint32_t* __restrict__ keys,
+    int32_t* __restrict__ count, unsigned long long* __restrict__ hmax) {
     if (g->err & SGE_SORT_FATAL) return;
     gather_one(perm, (int64_t)blockIdx.x * kBlock + threadIdx.x, ng, pin, xs, ys, zs, hs, ms, prec,
-               f32 != 0);
+               f32 != 0, keys, count, hmax);
 }
 
 // The same, and in the workgroups after the first nbg the cell offsets, by
@@ -637,11 +691,12 @@ __global__ __launch_bounds__(kBlock) void k_gather_gas_off(
     const sg_prec* __restrict__ pin, double* __restrict__ xs, double* __restrict__ ys,
     double* __restrict__ zs, double* __restrict__ hs, double* __restrict__ ms,
     sg_prec* __restrict__ prec, int f32, int nbg, const uint32_t* __restrict__ keys,
-    int64_t* __restrict__ off) {
+    int64_t* __restrict__ off, int32_t* __restrict__ count,
+    unsigned long long* __restrict__ hmax) {
     if (g->err & SGE_SORT_FATAL) return;
     if ((int)blockIdx.x < nbg) {
         gather_one(perm, (int64_t)blockIdx.x * kBlock + threadIdx.x, ng, pin, xs, ys, zs, hs, ms,
-                   prec, f32 != 0);
+                   prec, f32 != 0, keys, count, hmax);
         return;
     }
     const int64_t M = g->M;
@@ -1123,8 +1178,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_keys_small(
     }
 }
 
-// k_gather_gas_off from the particle-order arrays, with the counts and
-// maximum h of the cells, which the key pass leaves to it.
+// k_gather_gas_off from the particle-order arrays.
 __global__ __launch_bounds__(kBlock) void k_gather_gas_small(
     const int32_t* __restrict__ perm, int64_t ng, const sg_grid_dev* g,
     const double* __restrict__ x, const double* __restrict__ y, const double* __restrict__ z,
@@ -1139,11 +1193,7 @@ __global__ __launch_bounds__(kBlock) void k_gather_gas_small(
         const bool live = s < ng;
         const int32_t i = live ? perm[s] : 0;
         const sg_prec r{x[i], y[i], z[i], h[i], m[i], {0.0, 0.0, 0.0}};
-        if (live) {
-            const uint32_t c = keys[s];
-            atomicAdd(&count[c], 1);
-            atomicMax(&hmax[c], h_bits(r.h));
-        }
+        cell_stats(keys, s, ng, r.h, count, hmax);
         gather_put(s, live, r, xs, ys, zs, hs, ms, prec, f32 != 0);
         return;
     }
@@ -1463,19 +1513,20 @@ void sg_launch_grid(const double* x, const double* y, const double* z, const dou
     hipLaunchKernelGGL(k_cells_clear, dim3(nc), dim3(kBlock), 0, st, g, count, hmax);
 }
 
-void sg_launch_keys_count(const double* x, const double* y, const double* z, const double* h,
-                          const double* m, int64_t ng, sg_grid_dev* g, int32_t* key,
-                          int32_t* count, unsigned long long* hmax, sg_prec* pin,
-                          hipStream_t st) {
-    hipLaunchKernelGGL(k_keys_count, dim3(grid_for(ng, kBlock)), dim3(kBlock), 0, st, x, y, z,
-                       h, m, ng, g, key, count, hmax, pin);
+void sg_launch_gas_keys(const double* x, const double* y, const double* z, const double* h,
+                        const double* m, int64_t ng, sg_grid_dev* g, int32_t* key, sg_prec* pin,
+                        hipStream_t st) {
+    hipLaunchKernelGGL(k_gas_keys, dim3(grid_for(ng, kBlock)), dim3(kBlock), 0, st, x, y, z, h, m,
+                       ng, g, key, pin);
 }
 
 void sg_launch_gather_gas(const int32_t* perm, int64_t ng, const sg_grid_dev* g,
                           const sg_prec* pin, double* xs, double* ys, double* zs, double* hs,
-                          double* ms, sg_prec* prec, int precision, hipStream_t st) {
+                          double* ms, sg_prec* prec, int precision, const uint32_t* keys,
+                          int32_t* count, unsigned long long* hmax, hipStream_t st) {
     hipLaunchKernelGGL(k_gather_gas, dim3(grid_for(ng, kBlock)), dim3(kBlock), 0, st, perm, ng,
-                       g, pin, xs, ys, zs, hs, ms, prec, precision == SG_FP32C ? 1 : 0);
+                       g, pin, xs, ys, zs, hs, ms, prec, precision == SG_FP32C ? 1 : 0, keys, count,
+                       hmax);
 }
 
 // Bisection costs log2(N_g) dependent reads a cell, the scan three launches.
@@ -1486,12 +1537,14 @@ bool sg_offsets_by_bisection(int64_t ng, int64_t cell_cap) {
 void sg_launch_gather_gas_off(const int32_t* perm, int64_t ng, const sg_grid_dev* g,
                               const sg_prec* pin, double* xs, double* ys, double* zs, double* hs,
                               double* ms, sg_prec* prec, int precision, const uint32_t* keys,
-                              int64_t* off, int64_t cell_cap, hipStream_t st) {
+                              int64_t* off, int64_t cell_cap, int32_t* count,
+                              unsigned long long* hmax, hipStream_t st) {
     const unsigned nbg = grid_for(ng, kBlock);
     unsigned nbc = grid_for(cell_cap + 1, kBlock);
     if (nbc > 2048) nbc = 2048;
     hipLaunchKernelGGL(k_gather_gas_off, dim3(nbg + nbc), dim3(kBlock), 0, st, perm, ng, g, pin,
-                       xs, ys, zs, hs, ms, prec, precision == SG_FP32C ? 1 : 0, (int)nbg, keys, off);
+                       xs, ys, zs, hs, ms, prec, precision == SG_FP32C ? 1 : 0, (int)nbg, keys, off,
+                       count, hmax);
 }
 
 // Workspace of the Morton order: two key/value buffers, the digit histogram
