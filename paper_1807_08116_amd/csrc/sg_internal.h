@@ -7,6 +7,7 @@
 #include "sphgrav.h"
 
 #define SG_MAXLEV SG_MAX_LEVELS
+#define SG_BINADES 32
 
 // Device error bits (latched; cleared by sg_create / sg_bind_state).
 enum : uint32_t {
@@ -145,12 +146,12 @@ __device__ inline void rec_to(const R& r, uint4 (&v)[K]) {
 }
 
 struct sg_grid_dev {
-    // reduction inputs (order-preserving u64 images of doubles)
-    unsigned long long hmin_bits;
-    unsigned long long lo[SG_MAXLEV][3];
-    unsigned long long hi[SG_MAXLEV][3];
-    unsigned long long hmax_bits[SG_MAXLEV];
-    unsigned long long cnt[SG_MAXLEV];
+    // reduction inputs by binade of the cell side (its exponent modulo
+    // SG_BINADES), as order-preserving u64 images of doubles
+    struct binade {
+        unsigned long long lo[3], hi[3], hmax, cnt;
+    } bin[SG_BINADES];
+    uint32_t emin, emax;               // smallest and largest exponent
     uint32_t ticket, pad3;             // workgroups that have ended their part
     // finished grid
     double L0;

@@ -179,13 +179,12 @@ __global__ __launch_bounds__(kBlock) void k_scan_down(const int32_t* __restrict_
 
 __device__ inline bool finite_d(double v) { return __builtin_isfinite(v); }
 
-// Smallest power of two >= t (t positive and normal).
-__device__ inline double pow2_ceil(double t) {
-    unsigned long long b = (unsigned long long)__builtin_bit_cast(long long, t);
-    unsigned long long mant = b & 0x000fffffffffffffull;
-    if (mant == 0) return t;
-    unsigned long long e = (b >> 52) & 0x7ff;
-    return __builtin_bit_cast(double, (long long)((e + 1) << 52));
+// Exponent field of the smallest power of two >= h (2 + 2^-9), the cell side
+// that a particle asks for.
+__device__ inline uint32_t side_exponent(double h) {
+    const unsigned long long b =
+        (unsigned long long)__builtin_bit_cast(long long, h * (2.0 + 0x1p-9));
+    return (uint32_t)(b >> 52) + ((b & 0x000fffffffffffffull) ? 1u : 0u);
 }
 
 // First level l with L0 * 2^l >= h (2 + 2^-9); -1 beyond SG_MAXLEV.
@@ -200,19 +199,22 @@ __device__ inline int level_of(double h, double L0) {
     return l;
 }
 
-// The grid's reduction inputs (lane l < SG_MAXLEV of a wavefront: level l).
+// The grid's reduction inputs (lane l < SG_BINADES of a wavefront: binade l).
 // They are reset when a state is bound, and by the pass that consumes them
 // (grid_finish_wave) for the next build, so a build needs no launch for it;
 // the gravity-order box likewise (gbox_reset_lane, after the Morton keys).
 __device__ inline void grid_inputs_reset(sg_grid_dev* g, int l) {
-    if (l == 0) g->hmin_bits = ~0ull;
-    if (l < SG_MAXLEV) {
+    if (l == 0) {
+        g->emin = ~0u;
+        g->emax = 0u;
+    }
+    if (l < SG_BINADES) {
         for (int d = 0; d < 3; ++d) {
-            g->lo[l][d] = ~0ull;
-            g->hi[l][d] = 0ull;
+            g->bin[l].lo[d] = ~0ull;
+            g->bin[l].hi[d] = 0ull;
         }
-        g->hmax_bits[l] = 0ull;
-        g->cnt[l] = 0ull;
+        g->bin[l].hmax = 0ull;
+        g->bin[l].cnt = 0ull;
     }
 }
 
@@ -241,156 +243,157 @@ __global__ void k_status_clear(sg_grid_dev* g, int record) {
     }
 }
 
-// Minimum h and validity of the gas state: a thread's items, then the
-// wavefront and workgroup minimum, one global atomic per workgroup.
-__device__ inline void hmin_item(const double* __restrict__ x, const double* __restrict__ y,
-                                 const double* __restrict__ z, const double* __restrict__ h,
-                                 int64_t i, unsigned long long& mn, bool& bad) {
-    double hi = h[i];
-    if (!(hi > 0.0) || !finite_d(hi) || !finite_d(x[i]) || !finite_d(y[i]) || !finite_d(z[i]))
-        bad = true;
-    else {
-        unsigned long long o = sg_ord(hi);
-        mn = o < mn ? o : mn;
-    }
-}
-
-__device__ inline void hmin_fold(unsigned long long mn, bool bad, sg_grid_dev* g) {
-    __shared__ unsigned long long s_mn[kBlock / 64];
-    mn = wave_min_u64(mn);
-    if (lane_id() == 0) s_mn[threadIdx.x >> 6] = mn;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int k = 1; k < kBlock / 64; ++k) mn = s_mn[k] < mn ? s_mn[k] : mn;
-        if (mn != ~0ull) atomicMin(&g->hmin_bits, mn);
-    }
-    if (bad) atomicOr(&g->err, SGE_NONFINITE);
-}
-
-__global__ __launch_bounds__(kBlock) void k_grid_hmin(const double* __restrict__ x,
-                                                      const double* __restrict__ y,
-                                                      const double* __restrict__ z,
-                                                      const double* __restrict__ h, int64_t ng,
-                                                      sg_grid_dev* g, int32_t* __restrict__ count,
-                                                      unsigned long long* __restrict__ hmax,
-                                                      int64_t nclear) {
-    unsigned long long mn = ~0ull;
-    bool bad = false;
-    const int64_t i0 = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    const int64_t stride = (int64_t)gridDim.x * kBlock;
-    for (int64_t i = i0; i < ng; i += stride) hmin_item(x, y, z, h, i, mn, bad);
-    // small cell tables are cleared whole here, before their size is known
-    for (int64_t k = i0; k < nclear; k += stride) {
-        count[k] = 0;
-        hmax[k] = 0ull;
-    }
-    hmin_fold(mn, bad, g);
-}
-
-// Per-level bounding boxes, maximum h and particle counts.
-// Items base + r * stride + threadIdx.x, r < nround, of a workgroup.
+// Validity of the gas state, and bounds, maximum h and number of its
+// particles by the binade of their cell side: which levels these are follows
+// from the smallest one once all are in (grid_finish_wave), so one pass reads
+// the state.  (A pass for the smallest h first: 21 us more at 1048576 gas
+// particles, 8 at 131071, and a launch.)  Exponents that share an entry of
+// the table differ by SG_BINADES or more, which is an error anyway.
+//
+// Items base + r * stride + threadIdx.x, r < nround, of a workgroup.  One LDS
+// atomic per bound and particle (wavefront reductions per level present cost
+// more), in kCopies copies of the table.  Bound by the workgroups' device
+// atomics at the end, which meet at a few lines: see grid_blocks.
+constexpr int kCopies = 8;
+constexpr int kAhead = 4;                      // items in flight
 __device__ inline void grid_levels_block(const double* __restrict__ x,
                                          const double* __restrict__ y,
                                          const double* __restrict__ z,
                                          const double* __restrict__ h, int64_t ng,
                                          sg_grid_dev* g, int64_t base, int64_t stride,
                                          int64_t nround) {
-    __shared__ unsigned long long s_lo[SG_MAXLEV][3], s_hi[SG_MAXLEV][3];
-    __shared__ unsigned long long s_hmax[SG_MAXLEV], s_cnt[SG_MAXLEV];
-    if (g->err & SGE_NONFINITE) return;   // uniform across the grid
-    for (int t = threadIdx.x; t < SG_MAXLEV; t += kBlock) {
-        for (int d = 0; d < 3; ++d) {
-            s_lo[t][d] = ~0ull;
-            s_hi[t][d] = 0ull;
-        }
-        s_hmax[t] = 0ull;
-        s_cnt[t] = 0ull;
+    __shared__ unsigned long long s_lo[3][SG_BINADES][kCopies], s_hi[3][SG_BINADES][kCopies];
+    __shared__ unsigned long long s_hmax[SG_BINADES][kCopies], s_cnt[SG_BINADES][kCopies];
+    __shared__ uint32_t s_e[2];
+    static_assert(SG_BINADES * kCopies == kBlock, "a lane an entry");
+    const int te = threadIdx.x / kCopies, tc = threadIdx.x % kCopies;
+    for (int d = 0; d < 3; ++d) {
+        s_lo[d][te][tc] = ~0ull;
+        s_hi[d][te][tc] = 0ull;
+    }
+    s_hmax[te][tc] = s_cnt[te][tc] = 0ull;
+    if (threadIdx.x == 0) {
+        s_e[0] = ~0u;
+        s_e[1] = 0u;
     }
     __syncthreads();
-    const double hmin = sg_unord(g->hmin_bits);
-    const double L0 = pow2_ceil(hmin * (2.0 + 0x1p-9));
     bool bad = false;
-    for (int64_t r = 0; r < nround; ++r) {
-        int64_t i = r * stride + base + threadIdx.x;
-        bool valid = i < ng;
-        int lev = -1;
-        double p[3] = {0, 0, 0}, hi = 0;
-        if (valid) {
-            hi = h[i];
-            p[0] = x[i];
-            p[1] = y[i];
-            p[2] = z[i];
-            lev = level_of(hi, L0);
-            if (lev < 0) {
-                bad = true;
-                valid = false;
+    uint32_t mn = ~0u, mx = 0u;
+    for (int64_t r = 0; r < nround; r += kAhead) {
+        double hi[kAhead], p[kAhead][3];
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q) {
+            const int64_t i = (r + q) * stride + base + threadIdx.x;
+            if (r + q >= nround || i >= ng) {
+                hi[q] = -1.0;
+                continue;
             }
+            hi[q] = h[i];
+            p[q][0] = x[i];
+            p[q][1] = y[i];
+            p[q][2] = z[i];
+            if (!(hi[q] > 0.0)) bad = true;
         }
-        // one LDS atomic per bound and particle: a wavefront's particles
-        // arrive in input order and spread over several levels, and seven
-        // wavefront reductions per level present had cost more (sort stage
-        // at 1M gas 0.427 ms with shuffle reductions, 0.408 with DPP ones,
-        // 0.384 with these atomics)
-        if (valid) {
-            for (int d = 0; d < 3; ++d) {
-                atomicMin(&s_lo[lev][d], sg_ord(p[d]));
-                atomicMax(&s_hi[lev][d], sg_ord(p[d]));
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q) {
+            if (!(hi[q] > 0.0)) continue;
+            if (!finite_d(hi[q]) || !finite_d(p[q][0]) || !finite_d(p[q][1]) || !finite_d(p[q][2])) {
+                bad = true;
+                continue;
             }
-            atomicMax(&s_hmax[lev], sg_ord(hi));
-            atomicAdd(&s_cnt[lev], 1ull);
+            const uint32_t e = side_exponent(hi[q]);
+            mn = e < mn ? e : mn;
+            mx = e > mx ? e : mx;
+            const int k = e % SG_BINADES;
+            for (int d = 0; d < 3; ++d) {
+                atomicMin(&s_lo[d][k][tc], sg_ord(p[q][d]));
+                atomicMax(&s_hi[d][k][tc], sg_ord(p[q][d]));
+            }
+            atomicMax(&s_hmax[k][tc], sg_ord(hi[q]));
+            atomicAdd(&s_cnt[k][tc], 1ull);
         }
     }
-    if (bad) atomicOr(&g->err, SGE_LEVELS);
+    if (bad) atomicOr(&g->err, SGE_NONFINITE);
+    if (mn <= mx) {
+        atomicMin(&s_e[0], mn);
+        atomicMax(&s_e[1], mx);
+    }
     __syncthreads();
-    for (int t = threadIdx.x; t < SG_MAXLEV; t += kBlock) {
-        if (s_cnt[t] == 0) continue;
-        for (int d = 0; d < 3; ++d) {
-            atomicMin(&g->lo[t][d], s_lo[t][d]);
-            atomicMax(&g->hi[t][d], s_hi[t][d]);
+    if (threadIdx.x == 0 && s_e[0] <= s_e[1]) {
+        atomicMin(&g->emin, s_e[0]);
+        atomicMax(&g->emax, s_e[1]);
+    }
+    // a lane a value: eight fields of each binade
+    const int k = threadIdx.x / 8, f = threadIdx.x % 8;
+    unsigned long long c = 0;
+    for (int q = 0; q < kCopies; ++q) c += s_cnt[k][q];
+    if (c == 0) return;
+    sg_grid_dev::binade& out = g->bin[k];
+    if (f < 3) {
+        unsigned long long v = ~0ull;
+        for (int q = 0; q < kCopies; ++q) v = s_lo[f][k][q] < v ? s_lo[f][k][q] : v;
+        atomicMin(&out.lo[f], v);
+    } else if (f < 7) {
+        unsigned long long v = 0ull;
+        for (int q = 0; q < kCopies; ++q) {
+            const unsigned long long w = f < 6 ? s_hi[f - 3][k][q] : s_hmax[k][q];
+            v = w > v ? w : v;
         }
-        atomicMax(&g->hmax_bits[t], s_hmax[t]);
-        atomicAdd(&g->cnt[t], s_cnt[t]);
+        atomicMax(f < 6 ? &out.hi[f - 3] : &out.hmax, v);
+    } else {
+        atomicAdd(&out.cnt, c);
     }
 }
 
 // A value that other workgroups wrote by device-scope atomics.
-__device__ inline unsigned long long seen(unsigned long long* p) {
+template <typename T>
+__device__ inline T seen(T* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Cell sides L[l] = L0 2^(l + cell_scale_log2) (powers of two); the level of
-// a particle depends on L0 only.  One wavefront, lane l level l (the levels
-// one after the other on one thread took 7-12 us).
+// a particle depends on L0 only.  One wavefront, lane q < SG_BINADES binade q
+// (all inputs in one round of loads; the levels one after the other on one
+// thread took 7-12 us).
 __device__ inline void grid_finish_wave(sg_grid_dev* g, int64_t cell_cap, double cell_scale) {
-    const int l = threadIdx.x & 63;
-    const uint32_t err = __hip_atomic_load(&g->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const double hmin = sg_unord(seen(&g->hmin_bits));
-    const bool mine = l < SG_MAXLEV;
+    const int q = threadIdx.x & 63;
+    uint32_t err = seen(&g->err);
+    const uint32_t emin = seen(&g->emin), emax = seen(&g->emax);
     unsigned long long np = 0, hb = 0, lo[3] = {0, 0, 0}, hi[3] = {0, 0, 0};
-    if (mine) {
-        np = seen(&g->cnt[l]);
-        hb = seen(&g->hmax_bits[l]);
+    if (q < SG_BINADES) {
+        sg_grid_dev::binade& b = g->bin[q];
+        np = seen(&b.cnt);
+        hb = seen(&b.hmax);
         for (int d = 0; d < 3; ++d) {
-            lo[d] = seen(&g->lo[l][d]);
-            hi[d] = seen(&g->hi[l][d]);
+            lo[d] = seen(&b.lo[d]);
+            hi[d] = seen(&b.hi[d]);
         }
     }
-    grid_inputs_reset(g, l);
+    // (the loads of g->emin come back before any lane resets it)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    grid_inputs_reset(g, q);
+    const int l = (int)(((uint32_t)q - emin) % SG_BINADES);     // the binade's level
+    const bool mine = q < SG_BINADES && l < SG_MAXLEV;
+    if (!(err & SGE_NONFINITE) && emax >= emin + SG_MAXLEV) {
+        err |= SGE_LEVELS;
+        if (q == 0) atomicOr(&g->err, SGE_LEVELS);
+    }
     if (err & (SGE_NONFINITE | SGE_LEVELS)) {
         if (mine) {
             g->ncell[l] = 0;
             g->npart[l] = 0;
         }
-        if (l == 0) {
+        if (q == 0) {
             g->M = 0;
             g->nlev = 0;
         }
         return;
     }
-    const double L0 = pow2_ceil(hmin * (2.0 + 0x1p-9));
+    const double L0 = __builtin_bit_cast(double, (unsigned long long)emin << 52);
     double L = L0 * cell_scale;        // exact: cell_scale is 1/2, 1 or 2
     for (int k = 0; k < l && k < SG_MAXLEV; ++k) L *= 2.0;
     const double inv = 1.0 / L;        // exact: L is a power of two
+    if (!mine) np = 0;
     int64_t nc = np ? 1 : 0, dim[3] = {0, 0, 0};
     double org[3] = {0.0, 0.0, 0.0};
     bool bad = false;
@@ -407,18 +410,23 @@ __device__ inline void grid_finish_wave(sg_grid_dev* g, int64_t cell_cap, double
             }
         }
     }
-    const unsigned long long full = __ballot(np != 0);
     if (__ballot(bad)) nc = 0;
-    int64_t incl = nc;
+    // lane k: level k, for the offsets of the levels
+    const int from = (int)((emin + (uint32_t)q) % SG_BINADES);
+    const int64_t own = __shfl(nc, from, 64);
+    const int any = __shfl((int)(np != 0), from, 64);          // (with all lanes active)
+    const unsigned long long full = __ballot(q < SG_MAXLEV && any != 0);
+    int64_t incl = own;
     for (int o = 1; o < SG_MAXLEV; o <<= 1) {
         const int64_t t = __shfl_up(incl, o, 64);
-        if (l >= o) incl += t;
+        if (q >= o) incl += t;
     }
     const int64_t M = __shfl(incl, SG_MAXLEV - 1, 64);
+    const int64_t base = __shfl(incl - own, l, 64);
     if (mine) {
         g->L[l] = L;
         g->invL[l] = inv;
-        g->base[l] = incl - nc;
+        g->base[l] = base;
         g->hmaxlev[l] = np ? sg_unord(hb) : 0.0;
         g->npart[l] = np;
         g->ncell[l] = nc;
@@ -428,7 +436,7 @@ __device__ inline void grid_finish_wave(sg_grid_dev* g, int64_t cell_cap, double
         }
     }
     const bool none = __ballot(bad) != 0ull || M > 2147483647ll;
-    if (l != 0) return;
+    if (q != 0) return;
     g->L0 = L0;
     g->nlev = full ? 64 - __builtin_clzll(full) : 0;
     g->M = none ? 0 : M;
@@ -448,16 +456,28 @@ __global__ __launch_bounds__(kBlock) void k_grid_levels(const double* __restrict
                                                         const double* __restrict__ z,
                                                         const double* __restrict__ h,
                                                         int64_t ng, sg_grid_dev* g,
-                                                        int64_t cell_cap, double cell_scale) {
+                                                        int64_t cell_cap, double cell_scale,
+                                                        int32_t* __restrict__ count,
+                                                        unsigned long long* __restrict__ hmax,
+                                                        int64_t nclear, unsigned nlev) {
     __shared__ int s_last;
-    const int64_t stride = (int64_t)gridDim.x * kBlock;
+    if (blockIdx.x >= nlev) {
+        // small cell tables are cleared whole here, before their size is known
+        const int64_t step = (int64_t)(gridDim.x - nlev) * kBlock;
+        for (int64_t k = (int64_t)(blockIdx.x - nlev) * kBlock + threadIdx.x; k < nclear; k += step) {
+            count[k] = 0;
+            hmax[k] = 0ull;
+        }
+        return;
+    }
+    const int64_t stride = (int64_t)nlev * kBlock;
     grid_levels_block(x, y, z, h, ng, g, (int64_t)blockIdx.x * kBlock, stride,
                       (ng + stride - 1) / stride);
     // this workgroup's atomics (the only data handed over) have reached
     // memory before it draws its ticket
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (threadIdx.x == 0) s_last = atomicAdd(&g->ticket, 1u) == gridDim.x - 1;
+    if (threadIdx.x == 0) s_last = atomicAdd(&g->ticket, 1u) == nlev - 1;
     __syncthreads();
     if (!s_last || threadIdx.x >= 64) return;
     if (threadIdx.x == 0) atomicExch(&g->ticket, 0u);
@@ -581,7 +601,7 @@ __global__ __launch_bounds__(kBlock) void k_gas_keys(const double* __restrict__ 
 // and its last lane writes.  Cells that reach into another wavefront's slots
 // add to the cleared tables.  (Atomics per particle from the key pass, in
 // particle order, each went to a line of its own: with them that pass took
-// 117 us at 1048576 particles, without KEYS, and the gather GATHER.)
+// 117 us at 1048576 particles, without 22, and the gather 45 instead of 33.)
 __device__ inline void cell_stats(const uint32_t* __restrict__ keys, int64_t s, int64_t ng,
                                   double h, int32_t* __restrict__ count,
                                   unsigned long long* __restrict__ hmax) {
@@ -922,8 +942,8 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(
 // workgroups.  (Counting a pass's histograms in the scatter before it, by
 // global additions into the destination's tile, saves that launch too, but
 // cost more: a pass of 131071 keys 24.7 us against 10.6 + 4.8.)  With the
-// launches saved by k_grid_levels (which finishes the grid), k_grid_hmin
-// (which clears small tables) and k_gather_gas_off, the sort stage went from
+// launches saved by k_grid_levels (which finishes the grid and clears small
+// tables) and k_gather_gas_off, the sort stage went from
 // 107 to 48 us at 9001 gas particles, 136 to 70 at 65536, 198 to 123 at
 // 131071 and 243 to 184 at 262144.
 constexpr int64_t kRowTiles = 64;
@@ -1301,18 +1321,6 @@ __global__ __launch_bounds__(kSegScanBlock) void k_seg_scan_hist(const sg_seg_sy
 // (see sg_seg in sg_internal.h): the per-system kernels' bodies; a system
 // without gas is skipped, as the per-system build does.
 
-__global__ __launch_bounds__(kBlock) void k_seg_grid_hmin(const sg_seg_sys* __restrict__ sys,
-                                                          const int64_t* __restrict__ pfx,
-                                                          int nsys) {
-    int64_t lb;
-    const sg_seg_sys& S = sys[sg_seg_find(pfx, nsys, blockIdx.x, &lb)];
-    unsigned long long mn = ~0ull;
-    bool bad = false;
-    const int64_t i = lb * kBlock + threadIdx.x;
-    if (i < S.ng) hmin_item(S.x, S.y, S.z, S.h, i, mn, bad);
-    hmin_fold(mn, bad, S.g);
-}
-
 __global__ __launch_bounds__(kBlock) void k_seg_grid_levels(const sg_seg_sys* __restrict__ sys,
                                                             const int64_t* __restrict__ pfx,
                                                             int nsys) {
@@ -1467,8 +1475,8 @@ void sg_launch_status_clear(sg_grid_dev* g, bool record, hipStream_t st) {
     hipLaunchKernelGGL(k_status_clear, dim3(1), dim3(64), 0, st, g, record ? 1 : 0);
 }
 
-// Whole cell tables of up to this many cells are cleared beside the minimum
-// h (12 bytes a cell, a few us at most) instead of by a launch of their own.
+// Whole cell tables of up to this many cells are cleared beside the level
+// bounds (12 bytes a cell, a few us at most) instead of by a launch of their own.
 constexpr int64_t kClearWhole = 1 << 20;
 
 // The one-workgroup kernels take up to kSmall keys, and the gas takes them by
@@ -1494,19 +1502,26 @@ void sg_launch_gas_small(const double* x, const double* y, const double* z, cons
                        sorted, off, count, hmax);
 }
 
+// Workgroups of k_grid_levels: each ends with eight device atomics a level on
+// the same few lines, one after the other.  Sort stage in us with at most
+// 1024 / 256 / 128 / 64 of them: 65536 particles 66 / 66 / 60 / 57; 131071 114
+// / 99 / 93 / 90; 262144 170 / 128 / 123 / 123; 1048576 286 / 249 / 253 / 272.
+static unsigned grid_blocks(int64_t ng) {
+    const unsigned few = grid_for(ng, kBlock), many = grid_for(ng, 16 * kBlock);
+    const unsigned lo = few < 64 ? few : 64, hi = many < 256 ? many : 256;
+    return lo > hi ? lo : hi;
+}
+
 void sg_launch_grid(const double* x, const double* y, const double* z, const double* h, int64_t ng,
                     sg_grid_dev* g, int32_t* count, unsigned long long* hmax, int64_t cell_cap,
                     int cell_scale_log2, hipStream_t st) {
-    unsigned nb = grid_for(ng, kBlock);
-    if (nb > 1024) nb = 1024;
+    const unsigned nb = grid_blocks(ng);
     const bool whole = cell_cap <= kClearWhole;
-    unsigned nh = whole && grid_for(cell_cap, 4 * kBlock) > nb ? grid_for(cell_cap, 4 * kBlock) : nb;
-    if (nh > 1024) nh = 1024;
-    hipLaunchKernelGGL(k_grid_hmin, dim3(nh), dim3(kBlock), 0, st, x, y, z, h, ng, g, count, hmax,
-                       whole ? cell_cap : (int64_t)0);
+    unsigned ncl = whole ? grid_for(cell_cap, 4 * kBlock) : 0;
+    if (ncl > 512) ncl = 512;
     const double scale = cell_scale_log2 < 0 ? 0.5 : (cell_scale_log2 > 0 ? 2.0 : 1.0);
-    hipLaunchKernelGGL(k_grid_levels, dim3(nb), dim3(kBlock), 0, st, x, y, z, h, ng, g, cell_cap,
-                       scale);
+    hipLaunchKernelGGL(k_grid_levels, dim3(nb + ncl), dim3(kBlock), 0, st, x, y, z, h, ng, g,
+                       cell_cap, scale, count, hmax, cell_cap, nb);
     if (whole) return;
     unsigned nc = grid_for(cell_cap, kBlock);
     if (nc > 4096) nc = 4096;
@@ -1600,7 +1615,6 @@ void sg_seg_launch_sort(const sg_seg& s, hipStream_t st) {
     const int64_t* png = s.pfx + SG_SEG_NG * (s.nsys + 1);
     const int64_t* pcl = s.pfx + SG_SEG_CELLS * (s.nsys + 1);
     const unsigned nbg = (unsigned)s.nblk[SG_SEG_NG];
-    hipLaunchKernelGGL(k_seg_grid_hmin, dim3(nbg), dim3(kBlock), 0, st, s.sys, png, s.nsys);
     hipLaunchKernelGGL(k_seg_grid_levels, dim3(nbg), dim3(kBlock), 0, st, s.sys, png, s.nsys);
     hipLaunchKernelGGL(k_seg_grid_finish, dim3((unsigned)s.nsys), dim3(64), 0, st, s.sys);
     hipLaunchKernelGGL(k_seg_cells_clear, dim3((unsigned)s.nblk[SG_SEG_CELLS]), dim3(kBlock), 0, st,

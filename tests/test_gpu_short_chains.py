@@ -132,3 +132,31 @@ def test_overflow_and_bad_input_then_recover(sg, ng):
         eng.ctx.sync()
         check_lists(sg, eng.ctx, st)
     eng.ctx.close()
+
+
+# The levels come from the exponents of 2 h and up, kept modulo 32: sixteen
+# in a row are a grid, more are refused, also where two share an entry.  One
+# particle a level, placed as far out as its h goes, so that every level has
+# few cells; all others in the lowest.
+@pytest.mark.parametrize("ng", [900, 5000])
+@pytest.mark.parametrize("top,scale,ok", [(15, 1.0, True), (15, 2.0 ** -20, True),
+                                          (15, 2.0 ** 25, True),
+                                          (16, 1.0, False), (32, 2.0 ** -10, False),
+                                          (45, 2.0 ** -20, False)])
+def test_level_range(sg, ng, top, scale, ok):
+    st = gas(ng)
+    rng = np.random.default_rng(top)
+    side = 2.0 ** np.concatenate([np.arange(16), [top], np.zeros(ng - 17)])
+    st["h"] = 0.125 * side * rng.uniform(0.51, 0.99, ng) * scale
+    for f in ("x", "y", "z"):
+        st[f] = st[f] * side * scale
+    eng = sg.Engine(st, precision=sg.SG_FP64)
+    if ok:
+        eng.build_neighbors()
+        check_lists(sg, eng.ctx, st)
+    else:
+        eng.ctx.build_neighbors()
+        with pytest.raises(sg.SGError) as err:
+            eng.ctx.sync()
+        assert err.value.code == sg.SG_ERANGE
+    eng.ctx.close()
