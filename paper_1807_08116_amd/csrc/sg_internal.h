@@ -189,10 +189,12 @@ __host__ __device__ inline double sg_unord(unsigned long long m) {
 // ---- launchers (each defined in the translation unit of its kernels) ----
 // Scans: exclusive prefix sums of int32 counts into int64 offsets, with
 // out[n] = total.  n is read from *n_dev when n_dev != nullptr (device-side
-// sizes), else n_host; cap bounds the launch.
+// sizes), else n_host; cap bounds the launch.  chk: in holds the numbers of
+// neighbours; their total becomes chk->nnz and is checked against nnz_cap.
 size_t sg_scan_tmp_bytes(int64_t cap);
 void sg_launch_scan(const int32_t* in, int64_t* out, int64_t n_host, const int64_t* n_dev,
-                    int64_t cap, void* tmp, hipStream_t st);
+                    int64_t cap, void* tmp, hipStream_t st,
+                    sg_grid_dev* chk = nullptr, int64_t nnz_cap = 0);
 
 // Gas sort chain.
 // Clear the error word; record: also the grid record and the reduction

@@ -693,12 +693,6 @@ __device__ inline void nbr_check_one(sg_grid_dev* g, const int64_t* __restrict__
     }
 }
 
-__global__ void k_nbr_check(sg_grid_dev* g, const int64_t* __restrict__ nbr_off, int64_t ng,
-                            int64_t nnz_cap) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    nbr_check_one(g, nbr_off, ng, nnz_cap);
-}
-
 // ----------------------------------------------------- all systems at once --
 // (see sg_seg in sg_internal.h)
 
@@ -820,8 +814,7 @@ void sg_launch_nbr_finish(sg_grid_dev* g, int64_t ng, const double* xs, const do
                            off, cnt, slots, nnz_cap, nbr_off, nbr_idx);
         return;
     }
-    sg_launch_scan(cnt, nbr_off, ng, nullptr, ng, scan, st);
-    hipLaunchKernelGGL(k_nbr_check, dim3(1), dim3(64), 0, st, g, nbr_off, ng, nnz_cap);
+    sg_launch_scan(cnt, nbr_off, ng, nullptr, ng, scan, st, g, nnz_cap);
     hipLaunchKernelGGL(k_nbr_compact, dim3(nb), dim3(kBlock), 0, st, g, ng, xs, ys, zs, hs, off,
                        cnt, slots, nbr_off, nbr_idx);
 }

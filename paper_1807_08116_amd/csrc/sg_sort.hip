@@ -57,6 +57,24 @@ __device__ inline unsigned rank_below(unsigned long long mask) {
                                      __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
 }
 
+// The number of list entries, against the capacity.
+__device__ inline void nbr_check_total(sg_grid_dev* g, int64_t nnz, int64_t nnz_cap) {
+    if (g->err & SGE_SORT_FATAL) {
+        g->nnz = 0;
+        return;
+    }
+    g->nnz = nnz;
+    if (nnz > nnz_cap) {
+        atomicOr(&g->err, SGE_NNZ);
+        g->need_nnz = nnz;
+    }
+}
+
+__global__ void k_nbr_check(sg_grid_dev* g, const int64_t* __restrict__ nbr_off, int64_t ng,
+                            int64_t nnz_cap) {
+    if (threadIdx.x == 0) nbr_check_total(g, nbr_off[ng], nnz_cap);
+}
+
 // ------------------------------------------------------------------ scan --
 constexpr int kScanItems = 8;
 constexpr int kScanTile = kBlock * kScanItems;
@@ -137,11 +155,11 @@ __global__ __launch_bounds__(256) void k_scan_bsums(int64_t* __restrict__ bsum, 
     scan_bsums_block(bsum, scan_n(n_host, n_dev, cap), out);
 }
 
-__device__ inline void scan_down_tile(const int32_t* __restrict__ in, int64_t* __restrict__ out,
-                                      int64_t n, int64_t tile,
-                                      const int64_t* __restrict__ bsum) {
+// before: sum of the tiles before this one; returns this tile's sum.
+__device__ inline int64_t scan_down_tile(const int32_t* __restrict__ in, int64_t* __restrict__ out,
+                                         int64_t n, int64_t tile, int64_t before) {
     const int64_t base = tile * kScanTile;
-    if (base >= n) return;
+    if (base >= n) return 0;
     const int64_t i0 = base + (int64_t)threadIdx.x * kScanItems;
     int64_t v[kScanItems];
     int64_t tsum = 0;
@@ -160,11 +178,14 @@ __device__ inline void scan_down_tile(const int32_t* __restrict__ in, int64_t* _
     __syncthreads();
     int64_t wbase = 0;
     for (int w = 0; w < (int)(threadIdx.x >> 6); ++w) wbase += wtot[w];
-    int64_t run = bsum[tile] + wbase + incl - tsum;
+    int64_t run = before + wbase + incl - tsum;
     for (int k = 0; k < kScanItems; ++k) {
         if (i0 + k < n) out[i0 + k] = run;
         run += v[k];
     }
+    int64_t total = 0;
+    for (int w = 0; w < kBlock / 64; ++w) total += wtot[w];
+    return total;
 }
 
 __global__ __launch_bounds__(kBlock) void k_scan_down(const int32_t* __restrict__ in,
@@ -172,7 +193,33 @@ __global__ __launch_bounds__(kBlock) void k_scan_down(const int32_t* __restrict_
                                                       const int64_t* __restrict__ n_dev,
                                                       int64_t cap,
                                                       const int64_t* __restrict__ bsum) {
-    scan_down_tile(in, out, scan_n(n_host, n_dev, cap), blockIdx.x, bsum);
+    scan_down_tile(in, out, scan_n(n_host, n_dev, cap), blockIdx.x, bsum[blockIdx.x]);
+}
+
+// The same without k_scan_bsums, for up to kScanOwn tiles: a workgroup adds
+// up the sums of the tiles before it itself (8 KB from L2 at most), and the
+// last one knows the total.  chk: the total is that of the neighbour lists,
+// whose check needs no launch of its own then.
+constexpr int64_t kScanOwn = 1024;
+__global__ __launch_bounds__(kBlock) void k_scan_down_own(
+    const int32_t* __restrict__ in, int64_t* __restrict__ out, int64_t n_host,
+    const int64_t* __restrict__ n_dev, int64_t cap, const int64_t* __restrict__ bsum,
+    sg_grid_dev* chk, int64_t nnz_cap) {
+    const int64_t n = scan_n(n_host, n_dev, cap), tile = blockIdx.x;
+    const int64_t tiles = n > 0 ? (n + kScanTile - 1) / kScanTile : 1;
+    if (tile >= tiles) return;
+    __shared__ int64_t s_b[kBlock / 64];
+    int64_t b = 0;
+    for (int64_t k = threadIdx.x; k < tile; k += kBlock) b += bsum[k];
+    b = (int64_t)wave_sum_u64((unsigned long long)b);
+    if (lane_id() == 0) s_b[threadIdx.x >> 6] = b;
+    __syncthreads();
+    b = 0;
+    for (int w = 0; w < kBlock / 64; ++w) b += s_b[w];
+    const int64_t total = b + scan_down_tile(in, out, n, tile, b);
+    if (tile != tiles - 1 || threadIdx.x != 0) return;
+    out[n] = total;
+    if (chk) nbr_check_total(chk, total, nnz_cap);
 }
 
 // ------------------------------------------------------------ grid rule --
@@ -1401,7 +1448,7 @@ __global__ __launch_bounds__(kBlock) void k_seg_scan_down(const sg_seg_sys* __re
     int64_t* out;
     int64_t n;
     seg_scan_args(S, which, &in, &out, &n);
-    scan_down_tile(in, out, n, tile, (const int64_t*)S.scan);
+    scan_down_tile(in, out, n, tile, ((const int64_t*)S.scan)[tile]);
 }
 
 // Cell-key radix pass `pass` of every system (the per-system buffers'
@@ -1461,14 +1508,23 @@ size_t sg_scan_tmp_bytes(int64_t cap) {
     return sizeof(int64_t) * (size_t)((cap + kScanTile - 1) / kScanTile + 1);
 }
 
+// Both ways: three launches of 4.5-5 us each and an idle chip in the middle
+// one, against two; the sums of 1024 tiles (2097152 entries) cost a workgroup
+// less than a launch.
 void sg_launch_scan(const int32_t* in, int64_t* out, int64_t n_host, const int64_t* n_dev,
-                    int64_t cap, void* tmp, hipStream_t st) {
+                    int64_t cap, void* tmp, hipStream_t st, sg_grid_dev* chk, int64_t nnz_cap) {
     const unsigned nb = grid_for(cap, kScanTile);
     int64_t* bsum = (int64_t*)tmp;
     hipLaunchKernelGGL(k_scan_reduce, dim3(nb), dim3(kBlock), 0, st, in, n_host, n_dev, cap, bsum);
+    if (nb <= kScanOwn) {
+        hipLaunchKernelGGL(k_scan_down_own, dim3(nb), dim3(kBlock), 0, st, in, out, n_host, n_dev,
+                           cap, bsum, chk, nnz_cap);
+        return;
+    }
     hipLaunchKernelGGL(k_scan_bsums, dim3(1), dim3(256), 0, st, bsum, n_host, n_dev, cap, out);
     hipLaunchKernelGGL(k_scan_down, dim3(nb), dim3(kBlock), 0, st, in, out, n_host, n_dev, cap,
                        bsum);
+    if (chk) hipLaunchKernelGGL(k_nbr_check, dim3(1), dim3(64), 0, st, chk, out, n_host, nnz_cap);
 }
 
 void sg_launch_status_clear(sg_grid_dev* g, bool record, hipStream_t st) {
