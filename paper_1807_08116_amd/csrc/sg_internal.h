@@ -64,6 +64,14 @@ __device__ inline int sg_seg_find(const int64_t* __restrict__ p, int nsys, int64
     return lo;
 }
 
+// Between a wavefront's LDS accesses that meet across lanes: the hardware
+// keeps their order, this makes the compiler keep it too (no instruction).
+__device__ inline void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Records moved by groups of lanes.  A lane that reads or writes a record of
 // its own touches a cache line of its own with every 16 bytes, and the vector
 // memory's address unit takes them one line a cycle: gathers of 64-byte

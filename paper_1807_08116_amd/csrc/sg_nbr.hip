@@ -308,7 +308,7 @@ __device__ __attribute__((always_inline)) inline void nbr_search_wave(
     __shared__ int32_t mark[kWaves][64 * kHold];
     int32_t* const mymark = mark[threadIdx.x >> 6];
     if (!kPre && lane < (unsigned)NT) mytp[lane] = target_rec{p[0], p[1], p[2], hif, 0.0f};
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     // end of target g0 + lane's hits, from the wavefront's first slot
     int32_t* const wslots = slots + g0 * kSlot;
     int32_t mine = (int32_t)lane * kSlot;
@@ -341,7 +341,7 @@ __device__ __attribute__((always_inline)) inline void nbr_search_wave(
                 mytq[lane] = t;
                 mytc[lane] = pre_cut{m - t.a(), -m - t.a()};
             }
-            __builtin_amdgcn_wave_barrier();
+            wave_sync();
         }
         // the boxes of cells within reach: lane 4 l + d computes dimension d
         // of level l (the run's box is the union of its targets' boxes, as
@@ -423,7 +423,7 @@ __device__ __attribute__((always_inline)) inline void nbr_search_wave(
 #pragma unroll
                     for (int k = 0; k < kHold; ++k) mymark[64 * k + lane] = 0;
                     if (len > 0 && start >= cb0 && start < cb0 + 64 * kHold) mymark[start - cb0] = fs;
-                    __builtin_amdgcn_wave_barrier();
+                    wave_sync();
                     int32_t tk[kHold];
                     unsigned long long vm[kHold];          // lanes holding a candidate
                     double xd[kHold], yd[kHold], zd[kHold], hd[kHold];

@@ -943,7 +943,7 @@ __device__ inline void radix_scatter_tile(const uint32_t* __restrict__ kin,
     }
     uint16_t* const cnt = s_cnt[wave];
     for (int t = 2 * lane; t < kBuckets; t += 128) cnt[t] = cnt[t + 1] = 0;
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
 #pragma unroll
     for (int k = 0; k < ITEMS; ++k) {
         const bool valid = base + 64 * k < n;
@@ -957,9 +957,9 @@ __device__ inline void radix_scatter_tile(const uint32_t* __restrict__ kin,
         const int r = (int)rank_below(peers);
         const int before = cnt[d];
         rank[k] = before + r;
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
         if (valid && r == 0) cnt[d] = (uint16_t)(before + __builtin_popcountll(peers));
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
     }
     __syncthreads();
 #pragma unroll
@@ -1098,7 +1098,7 @@ __device__ inline void small_sort(small_lds& L, int n, int passes) {
             idx[k] = i < n ? L.idx[i] : 0;
         }
         for (int t = 2 * lane; t < kBuckets; t += 128) cnt[t] = cnt[t + 1] = 0;
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
 #pragma unroll
         for (int k = 0; k < kSmallItems; ++k) {
             if (k >= items) break;
@@ -1112,9 +1112,9 @@ __device__ inline void small_sort(small_lds& L, int n, int passes) {
             }
             const int r = (int)rank_below(peers), before = cnt[d];
             rank[k] = before + r;
-            __builtin_amdgcn_wave_barrier();
+            wave_sync();
             if (valid && r == 0) cnt[d] = (uint16_t)(before + __builtin_popcountll(peers));
-            __builtin_amdgcn_wave_barrier();
+            wave_sync();
         }
         __syncthreads();
         int32_t sum = 0;                                   // digit tid

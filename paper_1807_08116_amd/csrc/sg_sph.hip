@@ -74,12 +74,56 @@ __device__ inline T spline_shape(T xi) {
     return t > T(0) ? T(0.25) * t * t * t : T(0);
 }
 
+// quad_load64 and pair_load32 with the exchange through LDS (`buf`, the
+// wavefront's own) instead of selects: the passes below are bound by issue,
+// and the selects were 68 of the force pass's 220 vector instructions a step.
+// Lane c of a quad loads piece c ^ k of the k-th lane's record, so that both
+// the stores and the reads meet every bank once.  Stage at 131071 gas
+// particles with the record build, selects -> LDS: FP32C force 65 -> 54 us,
+// density 30 -> 29; FP64 75 -> 72, 41 -> 36 (1048576: 428 -> 396, 235 -> 235,
+// 550 -> 546, 300 -> 289).
+constexpr int kStage64 = 64 * 4, kStage32 = 64 * 2;
+__device__ inline void stage_load64(const void* base, int32_t idx, uint4* buf, uint4 (&v)[4]) {
+    const uint4* p = static_cast<const uint4*>(base);
+    const int c = threadIdx.x & 3, lane = threadIdx.x & 63, q = lane >> 2;
+    const uint32_t i0 = dpp_quad<0x00>((uint32_t)idx), i1 = dpp_quad<0x55>((uint32_t)idx),
+                   i2 = dpp_quad<0xaa>((uint32_t)idx), i3 = dpp_quad<0xff>((uint32_t)idx);
+    const uint4 t0 = p[4 * (size_t)i0 + c], t1 = p[4 * (size_t)i1 + (c ^ 1)],
+                t2 = p[4 * (size_t)i2 + (c ^ 2)], t3 = p[4 * (size_t)i3 + (c ^ 3)];
+    buf[lane] = t0;
+    buf[lane + 64] = t1;
+    buf[lane + 128] = t2;
+    buf[lane + 192] = t3;
+    wave_sync();
+    const uint4* r = buf + 64 * c + 4 * q;
+    v[0] = r[c];
+    v[1] = r[c ^ 1];
+    v[2] = r[c ^ 2];
+    v[3] = r[c ^ 3];
+    wave_sync();
+}
+__device__ inline void stage_load32(const void* base, int32_t idx, uint4* buf, uint4 (&v)[2]) {
+    const uint4* p = static_cast<const uint4*>(base);
+    const int c = threadIdx.x & 1, lane = threadIdx.x & 63, q = lane >> 1;
+    const uint32_t i0 = dpp_quad<0xa0>((uint32_t)idx), i1 = dpp_quad<0xf5>((uint32_t)idx);
+    const uint4 t0 = p[2 * (size_t)i0 + c], t1 = p[2 * (size_t)i1 + (c ^ 1)];
+    buf[lane] = t0;
+    buf[lane + 64] = t1;
+    wave_sync();
+    const uint4* r = buf + 64 * c + 2 * q;
+    v[0] = r[c];
+    v[1] = r[c ^ 1];
+    wave_sync();
+}
+
 // Density of target s from lane `sub` of its group; `valid` false for the
 // groups past the end (they still take part in the group exchange).
 // The group walks its row together (lanes past its end repeat the row's
 // entry without adding it): records come by quads or pairs of lanes.
 __device__ inline void density_f64_lanes(const sg_sph_bufs& b, int64_t s, bool valid, int sub,
                                          double* __restrict__ rho_out) {
+    __shared__ uint4 stage[kBlock / 64][kStage64];
+    uint4* const buf = stage[threadIdx.x >> 6];
     double acc = 0.0;
     if (valid) {
         const double x = b.xs[s], y = b.ys[s], z = b.zs[s], h = b.hs[s];
@@ -88,7 +132,7 @@ __device__ inline void density_f64_lanes(const sg_sph_bufs& b, int64_t s, bool v
         for (int64_t e0 = b.nbr_off[s]; e0 < e1; e0 += kSphLanes) {
             const bool on = e0 + sub < e1;
             uint4 v[4];
-            quad_load64(b.prec, b.nbr_idx[on ? e0 + sub : e0], v);
+            stage_load64(b.prec, b.nbr_idx[on ? e0 + sub : e0], buf, v);
             if (on) {
                 const sg_prec pj = rec_of<sg_prec>(v);
                 const double dx = x - pj.x, dy = y - pj.y, dz = z - pj.z;
@@ -115,6 +159,8 @@ __global__ __launch_bounds__(kBlock) void k_density_f64(sg_sph_bufs b, const sg_
 
 __device__ inline void density_f32_lanes(const sg_sph_bufs& b, int64_t s, bool valid, int sub,
                                          double* __restrict__ rho_out) {
+    __shared__ uint4 stage[kBlock / 64][kStage32];
+    uint4* const buf = stage[threadIdx.x >> 6];
     kahan acc{0.0f, 0.0f};
     if (valid) {
         const double x = b.xs[s], y = b.ys[s], z = b.zs[s], h = b.hs[s];
@@ -124,7 +170,7 @@ __device__ inline void density_f32_lanes(const sg_sph_bufs& b, int64_t s, bool v
         for (int64_t e0 = b.nbr_off[s]; e0 < e1; e0 += kSphLanes) {
             const bool on = e0 + sub < e1;
             uint4 v[2];
-            pair_load32(b.prec, b.nbr_idx[on ? e0 + sub : e0], v);
+            stage_load32(b.prec, b.nbr_idx[on ? e0 + sub : e0], buf, v);
             if (on) {
                 const sg_prec32 pj = rec_of<sg_prec32>(v);
                 const float dx = (float)(x - pj.x), dy = (float)(y - pj.y), dz = (float)(z - pj.z);
@@ -243,6 +289,8 @@ __device__ inline void sph_force_f64_lanes(const sg_sph_bufs& b, int64_t s, bool
                                            double alpha, double beta, double eta,
                                            double* __restrict__ asx, double* __restrict__ asy,
                                            double* __restrict__ asz, double* __restrict__ dedt) {
+    __shared__ uint4 stage[kBlock / 64][kStage64];
+    uint4* const buf = stage[threadIdx.x >> 6];
     const double kgrad = -45.0 / (64.0 * kPi);
     double sx = 0, sy = 0, sz = 0, se = 0;
     if (valid) {
@@ -253,8 +301,8 @@ __device__ inline void sph_force_f64_lanes(const sg_sph_bufs& b, int64_t s, bool
             const bool on = e0 + sub < e1;
             const int32_t j = b.nbr_idx[on ? e0 + sub : e0];
             uint4 v[4], w[2];
-            quad_load64(b.f64, j, v);
-            pair_load32(b.f64b, j, w);
+            stage_load64(b.f64, j, buf, v);
+            stage_load32(b.f64b, j, buf, w);
             const sg_frec64 o = rec_of<sg_frec64>(v);
             const sg_frec64b o2 = rec_of<sg_frec64b>(w);
             const double dx = a.x - o.x, dy = a.y - o.y, dz = a.z - o.z;
@@ -316,6 +364,8 @@ __device__ inline void sph_force_f32_lanes(const sg_sph_bufs& b, int64_t s, bool
                                            float alpha, float beta, float eta,
                                            double* __restrict__ asx, double* __restrict__ asy,
                                            double* __restrict__ asz, double* __restrict__ dedt) {
+    __shared__ uint4 stage[kBlock / 64][kStage64];
+    uint4* const buf = stage[threadIdx.x >> 6];
     const float kgrad = (float)(-45.0 / (64.0 * kPi));
     kahan sx{0, 0}, sy{0, 0}, sz{0, 0}, se{0, 0};
     if (valid) {
@@ -324,7 +374,7 @@ __device__ inline void sph_force_f32_lanes(const sg_sph_bufs& b, int64_t s, bool
         for (int64_t e0 = b.nbr_off[s]; e0 < e1; e0 += kSphLanes) {
             const bool on = e0 + sub < e1;
             uint4 v[4];
-            quad_load64(b.f32, b.nbr_idx[on ? e0 + sub : e0], v);
+            stage_load64(b.f32, b.nbr_idx[on ? e0 + sub : e0], buf, v);
             const sg_frec32 o = rec_of<sg_frec32>(v);
             const float dx = (float)(a.x - o.x), dy = (float)(a.y - o.y),
                         dz = (float)(a.z - o.z);
