@@ -43,21 +43,23 @@ def pass_bytes(stage, precision_form, ng, nnz, ncell):
     array the stage must read or write, counted once (per gas particle, per
     neighbour pair, per cell)."""
     if stage == "sort":
-        # keys: x,y,z,h,m in (40 B), key out (4), count and max-h atomics
-        # (12), the particle's 64-byte record out (for the gather); radix
+        # keys: x,y,z,h,m in (40 B), key out (4), count and max h (12), the
+        # particle's 64-byte record out (for the gather); radix
         # passes: the first reads keys (histogram and scatter, 8 B) and
         # writes key and id (8), each later one reads and writes both
         # (4 + 16); gather: perm and the record in (68), sorted copies and
-        # the density records out (104); cells: count, max h, offset (24)
+        # the density records out (40 + 64, FP32C 40 + 32); cells: count,
+        # max h, offset (24)
         p = radix_passes(8 * ng + 4096)      # the binding's default cell capacity
-        return (120 + 16 + 20 * (p - 1) + 172) * ng + 24 * ncell
+        gather = 172 if precision_form == "fp64" else 140
+        return (120 + 16 + 20 * (p - 1) + gather) * ng + 24 * ncell
     if stage == "nbr":         # own x,y,z,h; count + offset; one int32 per pair
         return 44 * ng + 4 * nnz
-    if stage == "density":     # offset, record (64 B), rho out; one index per pair
-        return 80 * ng + 4 * nnz
+    if stage == "density":     # offset, record (64 or 32 B), rho out; one index per pair
+        return (80 if precision_form == "fp64" else 48) * ng + 4 * nnz
     if stage == "sph":         # v, e packed (32 B in, 32 out), EOS + record build
         #                        (reads the pack), then offsets, records, 4 outputs
-        return (400 if precision_form == "fp64" else 336) * ng + 4 * nnz
+        return (376 if precision_form == "fp64" else 312) * ng + 4 * nnz
     raise ValueError(stage)
 
 

@@ -18,7 +18,8 @@ thread_local char g_create_msg[256] = "null context";
 
 // grav_variant 0 (automatic) resolved per precision form: FP64 -> 4
 // (expanded far field, FP64-seeded rsqrt: 8 % faster than the difference
-// form at 2M particles); FP32C has one kernel (1).
+// form at 2M particles); FP32C has one one-sided
+// kernel (1).
 constexpr int kAutoVariantFP64 = 4;
 inline int resolved_variant(const sg_params& p) {
     if (p.precision == SG_FP32C) return 1;
@@ -1028,7 +1029,7 @@ sg_status sg_export(sg_ctx* c, int32_t what, void* dst, int64_t cap_bytes, int64
             info.L0 = g.L0;
             info.nlev = g.nlev;
             for (int l = 0; l < SG_MAXLEV; ++l) {
-                info.L[l] = g.L[l];
+                info.L[l] = g.invL[l] != 0.0 ? 1.0 / g.invL[l] : 0.0;
                 info.base[l] = g.base[l];
                 info.ncell[l] = g.ncell[l];
                 info.npart[l] = (int64_t)g.npart[l];

@@ -7,7 +7,7 @@
 #include "sphgrav.h"
 
 #define SG_MAXLEV SG_MAX_LEVELS
-#define SG_BINADES 32
+#define SG_BINADES SG_MAXLEV
 
 // Device error bits (latched; cleared by sg_create / sg_bind_state).
 enum : uint32_t {
@@ -160,26 +160,26 @@ struct sg_grid_dev {
         unsigned long long lo[3], hi[3], hmax, cnt;
     } bin[SG_BINADES];
     uint32_t emin, emax;               // smallest and largest exponent
-    uint32_t ticket, pad3;             // workgroups that have ended their part
-    // finished grid
+    uint32_t ticket;                   // workgroups that have ended their part
+    int32_t nlev;                      // (finished grid)
+    // gravity preparation: whether the symmetric kernel may run (else the
+    // one-sided one), and the scales (powers of two) of its fixed-point sums
+    int32_t grav_sym;
+    uint32_t err;                      // status
+    double grav_S, grav_Sp;
+    // finished grid (the cell side of level l is 1 / invL[l])
     double L0;
-    double L[SG_MAXLEV], invL[SG_MAXLEV];
+    double invL[SG_MAXLEV];
     double org[SG_MAXLEV][3];
     int64_t dim[SG_MAXLEV][3];
     int64_t base[SG_MAXLEV];
     int64_t ncell[SG_MAXLEV];
     unsigned long long npart[SG_MAXLEV];
     double hmaxlev[SG_MAXLEV];
-    int32_t nlev, pad0;
     int64_t M;
     // gravity-order bounding box over all N (order-preserving u64 images)
     unsigned long long glo[3], ghi[3];
-    // gravity preparation: scales (powers of two) of the fixed-point sums of
-    // the symmetric kernel, and whether it may run (else the one-sided one)
-    double grav_S, grav_Sp;
-    int32_t grav_sym, pad2;
     // status
-    uint32_t err, pad1;
     int64_t need_cells, need_nnz;
     int64_t nnz;
 };

@@ -301,7 +301,7 @@ __global__ void k_status_clear(sg_grid_dev* g, int record) {
 // atomic per bound and particle (wavefront reductions per level present cost
 // more), in kCopies copies of the table.  Bound by the workgroups' device
 // atomics at the end, which meet at a few lines: see grid_blocks.
-constexpr int kCopies = 8;
+constexpr int kCopies = 16;
 constexpr int kAhead = 4;                      // items in flight
 __device__ inline void grid_levels_block(const double* __restrict__ x,
                                          const double* __restrict__ y,
@@ -372,6 +372,7 @@ __device__ inline void grid_levels_block(const double* __restrict__ x,
     }
     // a lane a value: eight fields of each binade
     const int k = threadIdx.x / 8, f = threadIdx.x % 8;
+    if (k >= SG_BINADES) return;
     unsigned long long c = 0;
     for (int q = 0; q < kCopies; ++q) c += s_cnt[k][q];
     if (c == 0) return;
@@ -471,7 +472,6 @@ __device__ inline void grid_finish_wave(sg_grid_dev* g, int64_t cell_cap, double
     const int64_t M = __shfl(incl, SG_MAXLEV - 1, 64);
     const int64_t base = __shfl(incl - own, l, 64);
     if (mine) {
-        g->L[l] = L;
         g->invL[l] = inv;
         g->base[l] = base;
         g->hmaxlev[l] = np ? sg_unord(hb) : 0.0;

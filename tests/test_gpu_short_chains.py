@@ -134,7 +134,7 @@ def test_overflow_and_bad_input_then_recover(sg, ng):
     eng.ctx.close()
 
 
-# The levels come from the exponents of 2 h and up, kept modulo 32: sixteen
+# The levels come from the exponents of 2 h and up, kept modulo 16: sixteen
 # in a row are a grid, more are refused, also where two share an entry.  One
 # particle a level, placed as far out as its h goes, so that every level has
 # few cells; all others in the lowest.
