@@ -1092,9 +1092,10 @@ struct sg_ens {
     sg_ens_sys* d_sys;
     sg_ens_task* d_tasks;
     sg_sym_task* d_sym;
-    int32_t* d_counter;          // of the one-sided launch
+    int32_t* d_counter;          // [2]: one-sided, symmetric
     int32_t ntasks, nsym;
     int nblocks, ipl, tile;
+    int sym_blocks;              // workgroups of the symmetric launch
     double eps, G;
     sg_seg seg;                  // segmented launches over all systems
     char msg[256];
@@ -1130,7 +1131,7 @@ ens_offsets ens_layout(int32_t nsys, int64_t ntasks, int64_t nsym) {
     o.sym = at;
     at += al(sizeof(sg_sym_task) * (size_t)(nsym > 0 ? nsym : 1));
     o.counter = at;
-    at += al(sizeof(int32_t));
+    at += al(2 * sizeof(int32_t));
     o.seg = at;
     at += al(sizeof(sg_seg_sys) * (size_t)nsys);
     o.pfx = at;
@@ -1173,7 +1174,7 @@ sg_status ens_grav_launch(sg_ens* e, bool pot, hipStream_t st) {
     c0->st = st;
     c0->begin(SG_ST_GRAV);
     sg_launch_grav_ensemble_sym(e->d_sys, e->d_sym, e->nsym, e->d_counter, pot ? 1 : 0, e->eps,
-                                e->ipl, st);
+                                e->ipl, e->sym_blocks, st);
     sg_launch_grav_ensemble(e->d_sys, e->d_tasks, e->ntasks, e->d_counter, pot ? 1 : 0, e->eps,
                             e->G, e->ipl, e->tile, e->nblocks, st);
     if (e->nsym > 0) sg_seg_launch_grav_finish(e->seg, pot ? 1 : 0, e->G, e->eps, st);
@@ -1530,7 +1531,9 @@ sg_status sg_ensemble_create(sg_ctx* const* ctxs, int32_t nsys, void* d_ws, size
     (void)hipGetLastError();
     e->nblocks = per_cu * (cus > 0 ? cus : 256);
     if (e->nblocks > e->ntasks) e->nblocks = e->ntasks;
+    e->sym_blocks = sg_grav_sym_blocks_per_cu(ipl) * (cus > 0 ? cus : 256);
     (void)hipGetLastError();
+    if (e->sym_blocks > e->nsym) e->sym_blocks = e->nsym;
     if (hipMemcpyAsync(e->d_sys, sys.data(), sizeof(sg_ens_sys) * sys.size(), hipMemcpyHostToDevice,
                        e->st) != hipSuccess ||
         hipMemcpyAsync(e->d_tasks, tk.data(), sizeof(sg_ens_task) * tk.size(),

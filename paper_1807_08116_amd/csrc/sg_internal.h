@@ -378,12 +378,13 @@ struct sg_sym_task {
 };
 void sg_grav_sorted_ptrs(void* sorted, int64_t n, const double** xs, const double** ys,
                          const double** zs, const double** ms, const void** sbox);
-// The symmetric launch over its tasks (first it resets the task counter of
-// the one-sided launch, which follows it and takes the systems that the
-// symmetric kernel does not serve).
+// The symmetric launch over its tasks (it resets both task counters first:
+// d_counter[0] belongs to the one-sided launch, which follows it and takes
+// the systems that the symmetric kernel does not serve).
 void sg_launch_grav_ensemble_sym(const sg_ens_sys* d_sys, const sg_sym_task* d_tasks,
                                  int32_t ntasks, int32_t* d_counter, int with_pot, double eps,
-                                 int t, hipStream_t st);
+                                 int t, int nblocks, hipStream_t st);
+int sg_grav_sym_blocks_per_cu(int t);
 void sg_launch_grav_ensemble(const sg_ens_sys* d_sys, const sg_ens_task* d_tasks, int32_t ntasks,
                              int32_t* d_counter, int with_pot, double eps, double G, int ipl,
                              int tile, int nblocks, hipStream_t st);
