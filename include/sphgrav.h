@@ -92,10 +92,12 @@ typedef enum {
  *   symmetric kernel, which meets each pair once and credits both particles
  *   (grav_ipl = targets per lane, grav_split = parts of a block's source
  *   list, grav_tile unused; its sums are fixed-point, so results do not
- *   depend on grav_split), and below, or where those sums cannot hold the
+ *   depend on grav_split; a particle whose acceleration these would hold too
+ *   coarsely, such as one that outweighs all others, gets a plain FP64 sum
+ *   over all others instead), and below, or where those sums cannot hold the
  *   input (extent / eps beyond 2^19 in the FP64 form, 2^30 in FP32C, or
- *   magnitudes near the ends of the floating-point range), FP64 variant 4 or
- *   FP32C variant 1.  FP64 form: 1 = pair differences, reciprocal
+ *   below 2^-30; no mass; magnitudes near the ends of the floating-point
+ *   range), FP64 variant 4 or FP32C variant 1.  FP64 form: 1 = pair differences, reciprocal
  *   square root seeded in FP32 and refined in FP64 (needs eps^2 >=
  *   1.2e-38), 2 = pair differences, seeded in FP64 (both refined to FP64
  *   rounding level); 3 (FP32 seed, needs eps^2 >= 1.2e-38) and 4 (FP64
