@@ -96,8 +96,11 @@ typedef enum {
  *   coarsely, such as one that outweighs all others, gets a plain FP64 sum
  *   over all others instead), and below, or where those sums cannot hold the
  *   input (extent / eps beyond 2^19 in the FP64 form, 2^30 in FP32C, or
- *   below 2^-30; no mass; magnitudes near the ends of the floating-point
- *   range), FP64 variant 4 or FP32C variant 1.  FP64 form: 1 = pair differences, reciprocal
+ *   below 2^-30; no mass; extent or eps from 1e100 on or eps up to 1e-100
+ *   in the FP64 form, extent or eps from 1e12 on in FP32C; masses near the
+ *   ends of the floating-point range), FP64 variant 4 or FP32C variant 1.
+ *   (These too lose the terms of pairs whose r^-3 leaves the form's normal
+ *   range, FP32C from 4e12 on, FP64 from 4e102 on: choose units within.)  FP64 form: 1 = pair differences, reciprocal
  *   square root seeded in FP32 and refined in FP64 (needs eps^2 >=
  *   1.2e-38), 2 = pair differences, seeded in FP64 (both refined to FP64
  *   rounding level); 3 (FP32 seed, needs eps^2 >= 1.2e-38) and 4 (FP64

@@ -92,3 +92,43 @@ def test_ensemble_heavy_particles(sg):
         np.testing.assert_array_equal(np.stack([e.numpy(f) for f in ("ax", "ay", "az")], 1), a)
         np.testing.assert_array_equal(e.numpy("pot"), phi)
     ens.close()
+
+
+def test_short_lengths_fp64(sg):
+    """Separations whose r^-3 is no FP64 number although m r^-3 is: closest
+    pairs at 1e-104 in a system of 1e-101.  All lengths and masses are a
+    power of two times those of an ordinary system, so its accelerations,
+    scaled, are the reference (the two differ by the kernel that serves them:
+    the forms' 1e-12)."""
+    rng = np.random.default_rng(3)
+    n, eps = 13312, 0.001                 # whole tiles of the one-sided kernel
+    p = rng.uniform(-0.5, 0.5, (n, 3))
+    z = np.zeros(n)
+    ls, ms = 2.0 ** -335, 2.0 ** -200
+
+    def state(k, q):
+        return dict(ng=0, x=k * p[:, 0], y=k * p[:, 1], z=k * p[:, 2], vx=z, vy=z, vz=z,
+                    m=np.full(n, q / n), h=np.zeros(0), e=np.zeros(0))
+
+    ref, rphi = evaluate(sg, state(1.0, 1.0), 0, eps=eps)
+    got, phi = evaluate(sg, state(ls, ms), 0, eps=eps * ls)
+    assert np.isfinite(got).all() and np.isfinite(phi).all()
+    assert np.linalg.norm(got * (ls / ms) * ls - ref) < 1e-12 * np.linalg.norm(ref)
+    assert np.linalg.norm(phi * (ls / ms) - rphi) < 1e-12 * np.linalg.norm(rphi)
+
+
+@pytest.mark.parametrize("precision,scale,eps", [(0, 1e101, 1e98), (1, 3e12, 1e9)])
+def test_long_lengths(sg, precision, scale, eps):
+    """Extents at which r^-3 leaves the normal range: the one-sided kernel's
+    answers, which are numbers there."""
+    rng = np.random.default_rng(5)
+    n = 12500
+    p = scale * rng.uniform(-0.5, 0.5, (n, 3))
+    z = np.zeros(n)
+    st = dict(ng=0, x=p[:, 0].copy(), y=p[:, 1].copy(), z=p[:, 2].copy(), vx=z, vy=z, vz=z,
+              m=np.full(n, 1.0 / n), h=np.zeros(0), e=np.zeros(0))
+    got = evaluate(sg, st, precision, eps=eps, grav_ipl=1)
+    ref = evaluate(sg, st, precision, eps=eps, grav_ipl=1, grav_variant=1 if precision else 4)
+    assert np.isfinite(ref[0]).all() and (np.abs(ref[0]).max(axis=1) > 0.0).all()
+    np.testing.assert_array_equal(got[0], ref[0])
+    np.testing.assert_array_equal(got[1], ref[1])
