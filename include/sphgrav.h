@@ -128,7 +128,7 @@ typedef enum {
  *   hold for any order; a stale order only makes the boxes less compact
  *   (more near-field pairs).  Results depend on the period at rounding
  *   level (other groupings); runs with one period are reproducible bit
- *   for bit, eager or graph-captured (sg_run, sg_ensemble_run). */
+ *   for bit (sg_step, sg_run, sg_ensemble_run). */
 typedef struct {
     double G, eps, gamma, alpha, beta, eta;
     int32_t precision;
@@ -256,15 +256,17 @@ sg_status sg_kick_drift(sg_ctx *ctx, double dt, int32_t phase);
 sg_status sg_step(sg_ctx *ctx, double dt, uint32_t flags);
 
 /* nsteps whole steps (as sg_step) with the conserved quantities of each
- * step written to d_hist[10*k .. 10*k+9] (device, may be NULL).  With
- * use_graph != 0, the first step runs eagerly, then P steady-state steps
- * (step + diagnostics; P = grav_reorder when it is above 1 and the kernel
- * uses the Morton order, else 1: one period of that order's schedule) are
- * captured once into a HIP graph and replayed while P steps remain; the
- * rest run eagerly (dt is fixed inside the graph; stage timing must be
- * off; the context's stream must not be the null stream, which cannot be
- * captured: SG_EINVAL before any work).  Results are identical to nsteps
- * calls of sg_step.  Waits for the stream before returning. */
+ * step written to d_hist[10*k .. 10*k+9] (device, may be NULL).  Results
+ * are identical to nsteps calls of sg_step.  Waits for the stream before
+ * returning.
+ * use_graph: whether the steps may be replayed from a HIP graph.  Not zero
+ * asks for what a capture needs (stage timing off: SG_ESTATE; from two steps
+ * on a stream other than the null stream: SG_EINVAL, both before any work),
+ * but this version enqueues the steps one by one either way: a replay of
+ * captured steps is no faster at any size (the stream never waits for the
+ * host), and processes that built and replayed hundreds of graphs have ended
+ * with a host segmentation fault whose cause is not known.  A caller may
+ * still capture sg_step() into a graph of its own. */
 sg_status sg_run(sg_ctx *ctx, double dt, int64_t nsteps, uint32_t flags, int32_t use_graph,
                  double *d_hist);
 
@@ -381,8 +383,7 @@ sg_status sg_ensemble_gravity(sg_ens *e, uint32_t flags);
  * contexts' stream.  Results equal those of sg_step on each context alone
  * (same launch shape) bit for bit. */
 sg_status sg_ensemble_step(sg_ens *e, double dt, uint32_t flags);
-/* nsteps ensemble steps; with use_graph one period of steady-state steps
- * is captured once and replayed (as sg_run).  Waits for the stream. */
+/* nsteps ensemble steps; use_graph as in sg_run.  Waits for the stream. */
 sg_status sg_ensemble_run(sg_ens *e, double dt, int64_t nsteps, uint32_t flags, int32_t use_graph);
 const char *sg_ensemble_last_error(const sg_ens *e);
 void sg_ensemble_destroy(sg_ens *e);

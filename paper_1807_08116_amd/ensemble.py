@@ -4,8 +4,7 @@ gravity launch, against running the systems one by one.
 Default workload: 64 collisions, N per system log-uniform in [8192, 262144]
 (gas:halo 1:1), impact parameter U[0, 3], closing speed U[0.5, 2];
 FP32-compensated form.  Reports aggregate pair-interactions/s of the
-batched gravity and of per-system launches, and steps/s of graph-captured
-ensemble steps.
+batched gravity and of per-system launches, and steps/s of ensemble steps.
 
 With --tune the persistent launch's targets per lane (the block of
 targets) and j-tile are first picked by the autotuner on these systems,
@@ -85,17 +84,12 @@ def main():
     ms_single = timed(one_by_one)
     log("one by one:      %.2f ms (%.3e pairs/s)" % (ms_single, pairs / ms_single * 1e3))
 
-    # steps, graph-captured (one capture per run, chunks of one Morton-order
-    # period) and eager (the host enqueues every launch of every step)
-    sec = {}
-    for graph in (True, False):
-        torch.cuda.synchronize()
-        t = time.perf_counter()
-        ens.run(args.dt, args.steps, sg.SG_POT, use_graph=graph)
-        torch.cuda.synchronize()
-        sec[graph] = time.perf_counter() - t
-        log("%d %s ensemble steps: %.3f s/step"
-            % (args.steps, "graph-captured" if graph else "eager", sec[graph] / args.steps))
+    torch.cuda.synchronize()
+    t = time.perf_counter()
+    ens.run(args.dt, args.steps, sg.SG_POT)
+    torch.cuda.synchronize()
+    sec = time.perf_counter() - t
+    log("%d ensemble steps: %.3f s/step" % (args.steps, sec / args.steps))
     out = {
         "workload": "%d independent collisions, N log-uniform in [8192, 262144] x %g"
                     % (len(states), args.scale),
@@ -103,8 +97,7 @@ def main():
         "batched_gravity_ms": ms_batched, "batched_pairs_per_s": pairs / ms_batched * 1e3,
         "one_by_one_gravity_ms": ms_single, "one_by_one_pairs_per_s": pairs / ms_single * 1e3,
         "batched_speedup": ms_single / ms_batched,
-        "steps": args.steps, "steps_per_s_graph": args.steps / sec[True],
-        "steps_per_s_eager": args.steps / sec[False], "precision": "fp32c",
+        "steps": args.steps, "steps_per_s": args.steps / sec, "precision": "fp32c",
         "grav_reorder": args.reorder or 1, "chain_stream": args.chain_stream,
         "launch": shape or "automatic",
     }

@@ -1,9 +1,8 @@
-"""Multi-step run with graph-captured steps: energy and momentum drift.
+"""Multi-step run: energy and momentum drift.
 
 Runs the off-axis 3:1 collision (2097152 gas + 2097152 halo particles by
-default) for a number of predictor-corrector steps in each precision form,
-with the steady-state step captured into a HIP graph and replayed, and
-reports steps/s plus the drift of the FP64 conserved-quantity sums:
+default) for a number of predictor-corrector steps in each precision form
+and reports steps/s plus the drift of the FP64 conserved-quantity sums:
 |E(t) - E(0)| / |E(0)|, |P(t) - P(0)| / sum m|v|, and the gap between the
 FP32-compensated and FP64 trajectories.
 
@@ -43,7 +42,7 @@ def run_form(sg, st, precision, steps, chunk, dt):
         k = min(chunk, steps - done)
         torch.cuda.synchronize()
         t = time.perf_counter()
-        h = ctx.run(dt, k, sg.SG_POT, use_graph=True)
+        h = ctx.run(dt, k, sg.SG_POT)
         torch.cuda.synchronize()
         t_total += time.perf_counter() - t
         hist.append(h.cpu().numpy())
@@ -88,7 +87,7 @@ def main():
     m = st["m"]
     pscale = float(np.sum(m * np.sqrt(st["vx"] ** 2 + st["vy"] ** 2 + st["vz"] ** 2)))
     out = {"config": args.config, "n_particles": n, "n_gas": ng, "steps": args.steps,
-           "dt": args.dt, "graph": True, "forms": {}}
+           "dt": args.dt, "forms": {}}
     hists = {}
     for form in args.forms.split(","):
         p = sg.SG_FP32C if form == "fp32c" else sg.SG_FP64

@@ -179,7 +179,7 @@ def _torch_stream(torch, device, stream):
     if stream is None:
         return torch.cuda.current_stream(device)
     if stream == "new":
-        # a stream of its own (default priority): needed for graph capture
+        # a stream of its own (default priority): a graph capture needs one
         return torch.cuda.Stream(device=device)
     return stream
 
@@ -277,8 +277,7 @@ class Context:
         self._check(lib().sg_step(self.h, float(dt), flags), "sg_step")
 
     def run(self, dt, nsteps, flags=0, use_graph=True, hist=None):
-        """nsteps steps (graph-replayed after the first when use_graph);
-        returns the [nsteps, 10] device tensor of per-step diagnostics."""
+        """nsteps steps (use_graph: see sg_run in the header); returns the [nsteps, 10] device tensor of per-step diagnostics."""
         if hist is None:
             hist = self.torch.empty((max(nsteps, 1), 10), dtype=self.torch.float64,
                                     device=self.device)
