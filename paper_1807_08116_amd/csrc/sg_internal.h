@@ -140,8 +140,8 @@ __device__ inline void pair_store32(void* base, int32_t idx, uint4 (&v)[2]) {
     if (i1 >= 0) *reinterpret_cast<uint4*>(p + 32 * (size_t)i1) = v[1];
 }
 // A record as its 16-byte pieces and back.
-template <typename R, int K>
-__device__ inline R rec_of(const uint4 (&v)[K]) {
+template <typename R, typename P, int K>
+__device__ inline R rec_of(const P (&v)[K]) {
     static_assert(sizeof(R) == 16 * K, "whole record");
     R r;
     __builtin_memcpy(&r, &v, sizeof(R));
