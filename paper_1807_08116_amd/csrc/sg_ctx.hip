@@ -915,7 +915,7 @@ sg_status sg_cfl_dt(sg_ctx* c, double C, double* d_dt) {
         return c->fail(SG_ESTATE, "time step needs neighbours, density and accelerations");
     sg_sph_bufs b = c->sph();
     // sound speeds and velocities of the current state, FP64, slot order
-    sg_launch_sph_prep(b, c->grid(), c->ng, SG_FP64, c->prm.gamma, c->s.vx, c->s.vy, c->s.vz,
+    sg_launch_sph_prep(b, c->grid(), c->ng, kPrepCfl, c->prm.gamma, c->s.vx, c->s.vy, c->s.vz,
                        c->s.e, c->st);
     sg_launch_cfl(b, c->grid(), c->ng, c->prm.alpha, c->prm.beta, c->prm.eta, C, c->s.ax, c->s.ay,
                   c->s.az, c->s.dedt, d_dt, c->st);

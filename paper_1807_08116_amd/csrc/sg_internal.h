@@ -301,6 +301,9 @@ struct sg_sph_bufs {
 };
 void sg_launch_density(const sg_sph_bufs& b, const sg_grid_dev* g, int64_t ng, int precision,
                        double* rho_out, hipStream_t st);
+// precision: SG_FP64 or SG_FP32C, or kPrepCfl for the time-step rule's records
+// (those of the FP64 pass with the sound speed as their mass, no second part).
+constexpr int kPrepCfl = 2;
 void sg_launch_sph_prep(const sg_sph_bufs& b, const sg_grid_dev* g, int64_t ng, int precision,
                         double gamma, const double* vx, const double* vy, const double* vz,
                         const double* e, hipStream_t st);

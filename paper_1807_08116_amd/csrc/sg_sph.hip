@@ -288,6 +288,9 @@ __device__ inline void sph_prep_one(const sg_sph_bufs& b, int64_t s, bool live, 
         r.pad[0] = r.pad[1] = 0.0f;
         rec_to(r, w);
         quad_store64(b.f32, to, w);
+    } else if (precision == kPrepCfl) {
+        rec_to(sg_frec64{x, y, z, h, c, v.x, v.y, v.z}, w);
+        quad_store64(b.f64, to, w);
     } else {
         rec_to(sg_frec64{x, y, z, h, m, v.x, v.y, v.z}, w);
         quad_store64(b.f64, to, w);
@@ -526,7 +529,8 @@ __global__ __launch_bounds__(kBlock) void k_seg_sph_force(const sg_seg_sys* __re
 // Step control of Sec. 2.2.  CFL bound of Eq. (dt-stability) per gas slot,
 // reduced to the minimum over slots with at least one neighbour: positive
 // doubles order like their bit patterns, so an integer atomic min is exact
-// and order-independent.
+// and order-independent.  The records (kPrepCfl) hold the sound speed in the
+// place of the mass, which this pass does not need: a line a neighbour.
 __global__ void k_cfl_init(unsigned long long* out) {
     if (threadIdx.x == 0 && blockIdx.x == 0) *out = 0x7ff0000000000000ull;   // +inf
 }
@@ -543,7 +547,6 @@ __global__ __launch_bounds__(kBlock) void k_cfl(sg_sph_bufs b, const sg_grid_dev
     double dt = __builtin_inf();
     if (s < ng && b.nbr_off[s + 1] > b.nbr_off[s]) {
         const sg_frec64 a = b.f64[s];
-        const double ac = b.f64b[s].c;
         double smin = __builtin_inf(), cmax = 0.0, mumax = 0.0;
         for (int64_t e = b.nbr_off[s]; e < b.nbr_off[s + 1]; ++e) {
             const int32_t j = b.nbr_idx[e];
@@ -552,7 +555,7 @@ __global__ __launch_bounds__(kBlock) void k_cfl(sg_sph_bufs b, const sg_grid_dev
             const double r2 = dx * dx + dy * dy + dz * dz;
             const double r = sqrt(r2);
             smin = r < smin ? r : smin;
-            const double cij = 0.5 * (ac + b.f64b[j].c);
+            const double cij = 0.5 * (a.m + o.m);
             cmax = cij > cmax ? cij : cmax;
             const double rv = dx * (a.vx - o.vx) + dy * (a.vy - o.vy) + dz * (a.vz - o.vz);
             if (rv < 0.0) {

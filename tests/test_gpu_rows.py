@@ -62,3 +62,39 @@ def test_row_lengths(sg, precision):
             continue
         assert np.linalg.norm(a - b) < tol * np.linalg.norm(b), k
         assert np.linalg.norm(got[4][s] - ref[3][s]) < tol * np.linalg.norm(ref[3][s]), k
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("ng", [700, 65537])
+def test_time_step_between_forces(sg, precision, ng):
+    """The time-step rule's records share the force pass's memory and hold the
+    sound speed where those have the mass: its value against the oracle's rule
+    on the same state, and forces before and after it alike, bit for bit."""
+    import oracle as orc
+    from paper_1807_08116_amd import ic
+    prm = ic.DEFAULT_PARAMS
+    rng = np.random.default_rng(ng)
+    x, y, z = rng.uniform(0.0, 1.0, (3, ng))
+    v = rng.normal(0.0, 0.1, (3, ng))
+    h = ng ** (-1 / 3) * rng.uniform(0.8, 1.2, ng)
+    m, e = rng.uniform(0.5, 1.5, ng) / ng, rng.uniform(0.02, 0.06, ng)
+    st = dict(ng=ng, x=x, y=y, z=z, vx=v[0], vy=v[1], vz=v[2], m=m, h=h, e=e)
+    eng = sg.Engine(st, precision=precision)
+    eng.build_neighbors()
+    eng.ctx.compute_density()
+    eng.ctx.compute_accel(sg.SG_SPH | sg.SG_GRAV)
+    dt = float(eng.ctx.cfl_dt(0.3))
+    eng.ctx.sync()
+    F = ("ax", "ay", "az", "dedt", "rho")
+    before = {f: eng.numpy(f).copy() for f in F}
+    rho = before["rho"]
+    c = np.sqrt(prm["gamma"] * (prm["gamma"] - 1.0) * e)
+    off, idx = orc.nbrs(x, y, z, h)
+    ref = orc.cfl_dt(x, y, z, v[0], v[1], v[2], h, c, before["ax"], before["ay"], before["az"],
+                     before["dedt"], 0.3, prm["alpha"], prm["beta"], prm["eta"], off, idx)
+    assert abs(dt - ref) < 1e-12 * ref
+    eng.ctx.compute_accel(sg.SG_SPH | sg.SG_GRAV)
+    eng.ctx.sync()
+    for f in F:
+        np.testing.assert_array_equal(eng.numpy(f), before[f], err_msg=f)
+    eng.ctx.close()
