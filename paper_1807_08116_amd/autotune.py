@@ -4,19 +4,22 @@ Tuned knobs (none changes results beyond summation order; the parity tests
 cover every value):
 
 * gravity: targets per lane (a workgroup of 256 lanes owns 256 * ipl
-  targets: the "block" of targets), sources per LDS tile (the j-tile: 128,
-  256 or 512), source-range splits and, in the FP64 form, the kernel
-  variant (difference or expanded far field, FP32- or FP64-seeded rsqrt);
+  targets: the "block" of targets), source-range splits and the kernel
+  variant: from 12288 particles on the pairwise kernel against the one-sided
+  ones, below (and where a one-sided kernel won) also its sources per LDS
+  tile (the j-tile: 128, 256 or 512), which the pairwise kernel does not use;
 * neighbour grid: the cell size, as a power-of-two scale of the default
   rule (cell_scale_log2 in {-1, 0, 1});
 * ensembles: targets per lane and j-tile of the persistent launch.
 
 Each candidate is timed on the caller's particle set with the library's own
 stage timing (HIP events around the kernels).  The gravity search is a
-coordinate search (targets per lane, then tile, then splits, then variant),
-each step keeping the best value so far.  Results are cached in a JSON file
-keyed by what was tuned, the precision form and the particle count rounded
-up to a power of two.
+coordinate search, each step keeping the best value so far; a value replaces
+the automatic choice only when it is faster by more than two timings of one
+launch differ.  Results are cached in a JSON file keyed by what was tuned, the
+precision form and the particle count rounded up to a power of two, with the
+version of the kernels' launch rules that they were measured on: entries of
+another version are not looked up.
 
 Usage: python -m paper_1807_08116_amd.autotune [--config c2] [--scale 1.0]
            [--forms fp32c,fp64] [--reps 2]
@@ -32,23 +35,35 @@ CACHE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "autotune_cache
 IPLS = (1, 2, 4)
 TILES = (128, 256, 512)
 CELL_SCALES = (-1, 0, 1)
+SYM_MIN = 12288          # smallest N of the pairwise gravity kernel (grav_variant 0)
+SYM_SPLITS = (16, 32, 64)
+KERNELS = 2              # version of the launch rules; 1: one-sided kernels at every size
+MARGIN = 0.99            # a launch's timings repeat to about half a per cent
+AUTO = dict(grav_ipl=0, grav_tile=0, grav_split=0, grav_variant=0)
 
 
 def _fill_split(n, ipl):
-    """Splits that give about 8192 workgroups (the library's automatic rule)."""
+    """Splits that give about 8192 workgroups (the one-sided kernels' automatic rule)."""
     blocks = max(1, (n + 256 * ipl - 1) // (256 * ipl))
     return max(1, min(64, (8192 + blocks - 1) // blocks))
+
+
+def _one_sided(precision):
+    from . import sphgrav as sg
+    return (1, 2, 3, 4) if precision == sg.SG_FP64 else (1,)
 
 
 def candidates(precision, n):
     """Every gravity parameter set the search may visit (for validation)."""
     from . import sphgrav as sg
     out = []
-    variants = (1, 2, 3, 4) if precision == sg.SG_FP64 else (0,)
+    if n >= SYM_MIN:
+        out += [dict(AUTO, grav_ipl=ipl, grav_split=split) for ipl in (0,) + IPLS
+                for split in (0,) + SYM_SPLITS]
     for ipl in IPLS:
         for tile in TILES:
             for split in sorted({1, 2, 4, _fill_split(n, ipl)}):
-                for v in variants:
+                for v in _one_sided(precision):
                     out.append(dict(grav_ipl=ipl, grav_tile=tile, grav_split=split, grav_variant=v))
     return out
 
@@ -69,7 +84,7 @@ def load_cache(path=CACHE):
 
 def _store(path, key, entry):
     cache = load_cache(path)
-    cache[key] = entry
+    cache[key] = dict(entry, kernels=KERNELS)
     with open(path, "w") as f:
         json.dump(cache, f, indent=1)
 
@@ -95,31 +110,39 @@ def time_gravity(st, precision, params, reps=2):
 
 def tune_gravity(st, precision, reps=2, path=CACHE, verbose=False):
     """Coordinate search over (ipl, tile, split, variant); returns the best dict."""
-    from . import sphgrav as sg
     n = len(st["x"])
-    best = dict(grav_ipl=0, grav_tile=0, grav_split=0, grav_variant=0)
+    best = dict(AUTO)
     best_ms = time_gravity(st, precision, best, reps)
     rows = [dict(best, ms=best_ms)]
 
-    def try_axis(name, values):
+    def try_all(cands):
         nonlocal best, best_ms
-        for v in values:
-            cand = dict(best, **{name: v})
+        for cand in cands:
             if cand == best:
                 continue
             ms = time_gravity(st, precision, cand, reps)
             rows.append(dict(cand, ms=ms))
             if verbose:
                 print("  %s: %.3f ms" % (cand, ms), file=sys.stderr, flush=True)
-            if ms < best_ms:
+            if ms < MARGIN * best_ms:
                 best, best_ms = cand, ms
 
-    try_axis("grav_ipl", IPLS)
-    try_axis("grav_tile", TILES)
-    ipl = best["grav_ipl"] or 2
-    try_axis("grav_split", sorted({1, 2, 4, _fill_split(n, ipl)}))
-    if precision == sg.SG_FP64:
-        try_axis("grav_variant", (1, 2, 3, 4))
+    def axis(name, values):
+        return [dict(best, **{name: v}) for v in values]
+
+    try_all(axis("grav_ipl", IPLS))
+    if n >= SYM_MIN:
+        # the pairwise kernel has no tiles; the one-sided ones start from
+        # their own automatic shape
+        try_all(axis("grav_split", SYM_SPLITS))
+        try_all([dict(AUTO, grav_variant=v) for v in _one_sided(precision)])
+        if best["grav_variant"] != 0:
+            try_all(axis("grav_tile", TILES))
+    else:
+        try_all(axis("grav_tile", TILES))
+        try_all(axis("grav_split", sorted({1, 2, 4, _fill_split(n, best["grav_ipl"] or 2)})))
+        if len(_one_sided(precision)) > 1:
+            try_all(axis("grav_variant", _one_sided(precision)))
     _store(path, _key("grav", precision, n), dict(best=best, ms=best_ms, n=n, tried=rows))
     return best
 
@@ -162,8 +185,10 @@ def tune_ensemble(states, reps=2, path=CACHE, verbose=False):
     import torch
     from . import sphgrav as sg
     rows = []
+    # only systems below the pairwise kernel's sizes have tiles
+    tiles = TILES if any(len(s["x"]) < SYM_MIN for s in states) else (512,)
     for ipl in IPLS:
-        for tile in TILES:
+        for tile in tiles:
             ens = sg.Ensemble(states, grav_ipl=ipl, grav_tile=tile)
             ens.gravity(sg.SG_GRAV | sg.SG_POT)                 # warm-up
             torch.cuda.synchronize()
@@ -191,7 +216,7 @@ def tune_ensemble(states, reps=2, path=CACHE, verbose=False):
 def lookup(kind, precision, n, path=CACHE):
     """Cached best parameters ('grav', 'cells' or 'ens') for this size bucket, or None."""
     e = load_cache(path).get(_key(kind, precision, n))
-    return None if e is None else e["best"]
+    return None if e is None or e.get("kernels") != KERNELS else e["best"]
 
 
 def main():
