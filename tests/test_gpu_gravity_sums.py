@@ -132,3 +132,38 @@ def test_long_lengths(sg, precision, scale, eps):
     assert np.isfinite(ref[0]).all() and (np.abs(ref[0]).max(axis=1) > 0.0).all()
     np.testing.assert_array_equal(got[0], ref[0])
     np.testing.assert_array_equal(got[1], ref[1])
+
+
+def tiles_and_period(n, t):
+    """The launch rule: tiles of the longest source list, and tiles between two
+    roundings of the target-side sums."""
+    nb = -(-n // (256 * t))
+    tiles = t * (1 + nb // 2)
+    s = min(max(-(-16384 // nb), tiles // 32), 128)
+    return tiles, -(-tiles // s) if s < tiles else 1
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("n,ipl", [(66000, 1), (100001, 4)])
+def test_parts_with_longer_periods(sg, orc, precision, n, ipl):
+    """Sizes whose target-side sums span several tiles: parts that do not end
+    with a period are rounded up to one, so every cut gives the same bits."""
+    tiles, period = tiles_and_period(n, ipl)
+    splits = (1, 3, 7, 64)
+    assert period > 1 and any(-(-tiles // s) % period for s in splits)
+    rng = np.random.default_rng(n)
+    p = rng.normal(0.0, 1.0, (n, 3))
+    z = np.zeros(n)
+    st = dict(ng=0, x=p[:, 0].copy(), y=p[:, 1].copy(), z=p[:, 2].copy(), vx=z, vy=z, vz=z,
+              m=rng.uniform(0.5, 1.5, n) / n, h=np.zeros(0), e=np.zeros(0))
+    ref, rphi = evaluate(sg, st, precision, grav_ipl=ipl)
+    t = np.arange(0, n, 331)
+    gx, gy, gz, gp = orc.gravity(st["x"], st["y"], st["z"], st["m"], 1.0, 0.01, targets=t)
+    a = np.stack([gx, gy, gz], 1)
+    tol = (1e-12, 1e-6)[precision]
+    assert np.linalg.norm(ref[t] - a) < tol * np.linalg.norm(a)
+    assert np.linalg.norm(rphi[t] - gp) < tol * np.linalg.norm(gp)
+    for split in splits:
+        got, phi = evaluate(sg, st, precision, grav_ipl=ipl, grav_split=split)
+        np.testing.assert_array_equal(got, ref)
+        np.testing.assert_array_equal(phi, rphi)
