@@ -194,7 +194,7 @@ sg_status sg_create(const sg_params *prm, const sg_caps *caps, void *d_workspace
  * threads) race.
  * SG_ECAPACITY, with a message, when sg_workspace_bytes(prm, caps) exceeds
  * SG_STATIC_WS_BYTES (64 MiB: with the Python binding's default
- * capacities, up to 11939 gas + 11939 halo particles); SG_EINVAL as
+ * capacities, up to 12048 gas + 12048 halo particles); SG_EINVAL as
  * sg_create for bad parameters.  Steps run the gravity and the
  * neighbour/SPH chain one after the other on `stream` (no auxiliary
  * stream).  Every other entry point works on the context as on one from
@@ -340,11 +340,14 @@ sg_status sg_status_sync(sg_ctx *ctx, int64_t need[2]);
 
 /* Ensembles of independent systems (one bound context each, all SG_FP32C,
  * the same G, eps, grav_reorder and stream; SG_EINVAL otherwise).
- * Gravity of all systems runs as ONE persistent launch: workgroups take
- * (system, block of 256 * grav_ipl targets) tasks, largest systems first,
- * from a device counter until none is left; grav_ipl and grav_tile are
- * those of the first context, 0 selecting 2 targets per lane and 512
- * sources per tile for this launch.  Every other per-particle stage of a
+ * Gravity of all systems runs as two persistent launches, one after the
+ * other: the pairwise kernel over the systems that it serves (as in
+ * grav_variant above), then the one-sided kernel over the others; in each,
+ * workgroups take (system, block of 256 * grav_ipl targets) tasks, in the
+ * pairwise one a part of the block's source list, largest systems first,
+ * from a device counter until none is left.  grav_ipl and grav_tile (of the
+ * one-sided kernel) are those of the first context, 0 selecting 2 targets per
+ * lane and 512 sources per tile for these launches.  Every other per-particle stage of a
  * step (the predictor's SPH pass, the combination of the SPH and gravity
  * parts, predictor and corrector, the Morton order and sorted copies of the
  * gravity inputs, and the corrector's grid, sort, neighbour lists, density

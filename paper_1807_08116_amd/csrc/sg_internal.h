@@ -22,10 +22,6 @@ enum : uint32_t {
 };
 #define SGE_SORT_FATAL (SGE_LEVELS | SGE_CELLS | SGE_NONFINITE | SGE_GRID)
 
-// Grid of smoothing-length levels plus the device status word.  Lives in
-// the workspace; written only by device code: the level fields by the
-// neighbour build, the gravity-order box (glo, ghi) by the gravity
-// preparation, the status word by both (atomic OR).
 // Workgroups of a launch are dealt to the 8 XCDs of the chip round-robin,
 // and each XCD has its own L2.  Kernels whose neighbouring targets share
 // data (neighbour gathers over slot-ordered particles) remap the block
@@ -153,6 +149,11 @@ __device__ inline void rec_to(const R& r, uint4 (&v)[K]) {
     __builtin_memcpy(&v, &r, sizeof(R));
 }
 
+// Grid of smoothing-length levels plus the device status word.  Lives in
+// the workspace; written only by device code: the level fields by the
+// neighbour build, the gravity-order box (glo, ghi) and the choice and scales
+// of the pairwise gravity by the gravity preparation, the status word by both
+// (atomic OR).
 struct sg_grid_dev {
     // reduction inputs by binade of the cell side (its exponent modulo
     // SG_BINADES), as order-preserving u64 images of doubles
@@ -183,6 +184,19 @@ struct sg_grid_dev {
     int64_t need_cells, need_nnz;
     int64_t nnz;
 };
+
+// The number of list entries, against the capacity.
+__device__ inline void nbr_check_total(sg_grid_dev* g, int64_t nnz, int64_t nnz_cap) {
+    if (g->err & SGE_SORT_FATAL) {
+        g->nnz = 0;
+        return;
+    }
+    g->nnz = nnz;
+    if (nnz > nnz_cap) {
+        atomicOr(&g->err, SGE_NNZ);
+        g->need_nnz = nnz;
+    }
+}
 
 // Order-preserving map of doubles onto u64 (for integer atomic min/max).
 __host__ __device__ inline unsigned long long sg_ord(double v) {

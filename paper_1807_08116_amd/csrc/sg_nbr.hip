@@ -657,11 +657,7 @@ __global__ __launch_bounds__(kBlock) void k_nbr_compact_own(
     // the last workgroup knows the total
     if (blockIdx.x == gridDim.x - 1 && tid == 0) {
         nbr_off[ng] = end;
-        g->nnz = end;
-        if (end > nnz_cap) {
-            atomicOr(&g->err, SGE_NNZ);
-            g->need_nnz = end;
-        }
+        nbr_check_total(g, end, nnz_cap);
     }
     if (end > nnz_cap) return;                     // rows past the capacity are not written
     nbr_copy_wave(g, ng, xs, ys, zs, hs, off, cnt, slots, s_off, first, nbr_idx,
@@ -677,20 +673,6 @@ __global__ __launch_bounds__(kBlock) void k_nbr_compact(
     if (g->err & (SGE_SORT_FATAL | SGE_NNZ)) return;
     const int64_t w = (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6);
     nbr_copy_wave(g, ng, xs, ys, zs, hs, off, cnt, slots, nbr_off, 0, nbr_idx, w);
-}
-
-__device__ inline void nbr_check_one(sg_grid_dev* g, const int64_t* __restrict__ nbr_off,
-                                     int64_t ng, int64_t nnz_cap) {
-    if (g->err & SGE_SORT_FATAL) {
-        g->nnz = 0;
-        return;
-    }
-    const int64_t nnz = nbr_off[ng];
-    g->nnz = nnz;
-    if (nnz > nnz_cap) {
-        atomicOr(&g->err, SGE_NNZ);
-        g->need_nnz = nnz;
-    }
 }
 
 // ----------------------------------------------------- all systems at once --
@@ -709,7 +691,8 @@ __global__ __launch_bounds__(kBlock, NT >= kPreMin ? 8 : 6) void k_seg_nbr_searc
 
 __global__ void k_seg_nbr_check(const sg_seg_sys* __restrict__ sys, int nsys) {
     for (int k = threadIdx.x; k < nsys; k += blockDim.x)
-        if (sys[k].ng > 0) nbr_check_one(sys[k].g, sys[k].sph.nbr_off, sys[k].ng, sys[k].nnz_cap);
+        if (sys[k].ng > 0)
+            nbr_check_total(sys[k].g, sys[k].sph.nbr_off[sys[k].ng], sys[k].nnz_cap);
 }
 
 __global__ __launch_bounds__(kBlock) void k_seg_nbr_compact(const sg_seg_sys* __restrict__ sys,

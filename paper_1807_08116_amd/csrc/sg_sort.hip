@@ -17,8 +17,8 @@ constexpr int kBlock = 256;
 __device__ inline unsigned lane_id() { return threadIdx.x & 63; }
 
 // 64-bit minimum and maximum over the 64 lanes by DPP row operations on the
-// two 32-bit halves, with no chain of shuffles through LDS (h minimum,
-// Morton box, equal-key runs of the key pass).  Every lane must be active;
+// two 32-bit halves, with no chain of shuffles through LDS (Morton box,
+// equal-key runs of an ensemble's key pass).  Every lane must be active;
 // the result is uniform.  Controls: quad_perm
 // [1,0,3,2] 0xb1, [2,3,0,1] 0x4e, row_half_mirror 0x141, row_mirror 0x140,
 // row_bcast:15 0x142 (lane 15 of each row into the next row), row_bcast:31
@@ -55,19 +55,6 @@ __device__ inline unsigned long long wave_sum_u64(unsigned long long v) {
 __device__ inline unsigned rank_below(unsigned long long mask) {
     return __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32),
                                      __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
-}
-
-// The number of list entries, against the capacity.
-__device__ inline void nbr_check_total(sg_grid_dev* g, int64_t nnz, int64_t nnz_cap) {
-    if (g->err & SGE_SORT_FATAL) {
-        g->nnz = 0;
-        return;
-    }
-    g->nnz = nnz;
-    if (nnz > nnz_cap) {
-        atomicOr(&g->err, SGE_NNZ);
-        g->need_nnz = nnz;
-    }
 }
 
 __global__ void k_nbr_check(sg_grid_dev* g, const int64_t* __restrict__ nbr_off, int64_t ng,
@@ -249,7 +236,8 @@ __device__ inline int level_of(double h, double L0) {
 // The grid's reduction inputs (lane l < SG_BINADES of a wavefront: binade l).
 // They are reset when a state is bound, and by the pass that consumes them
 // (grid_finish_wave) for the next build, so a build needs no launch for it;
-// the gravity-order box likewise (gbox_reset_lane, after the Morton keys).
+// the gravity-order box likewise (by the gather in Morton order, in
+// sg_grav.hip, after the Morton keys).
 __device__ inline void grid_inputs_reset(sg_grid_dev* g, int l) {
     if (l == 0) {
         g->emin = ~0u;
@@ -565,11 +553,6 @@ __device__ inline int32_t cell_key(const sg_grid_dev* g, int l, const double (&p
     return (int32_t)(g->base[l] + (c[2] * g->dim[l][1] + c[1]) * g->dim[l][0] + c[0]);
 }
 
-// Cell key of gas particle i, its count and the cell's maximum h.  Every
-// lane of the wavefront calls this (valid or not): the lanes that share the
-// key of the first valid lane add their count and maximum h with one
-// atomic each (clustered or coincident gas puts many particles of a
-// wavefront in one cell); the others add their own.
 // Key and, in particle order, record of particle i (every lane of a quad
 // calls this); returns the key, *hb the bits of h.
 __device__ inline int32_t key_one(const double* __restrict__ x, const double* __restrict__ y,
@@ -595,7 +578,11 @@ __device__ inline int32_t key_one(const double* __restrict__ x, const double* __
     return k;
 }
 
-// The same with the cells' counts and maxima, by atomics (an ensemble's).
+// The same with the cell's count and maximum h, by atomics (an ensemble's).
+// Every lane of the wavefront calls this (valid or not): the lanes that share
+// the key of the first valid lane add their count and maximum h with one
+// atomic each (clustered or coincident gas puts many particles of a
+// wavefront in one cell); the others add their own.
 __device__ inline void keys_count_wave(const double* __restrict__ x, const double* __restrict__ y,
                                        const double* __restrict__ z,
                                        const double* __restrict__ h,

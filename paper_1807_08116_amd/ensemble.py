@@ -1,5 +1,5 @@
-"""Batched ensemble: independent two-system collisions in one persistent
-gravity launch, against running the systems one by one.
+"""Batched ensemble: independent two-system collisions in persistent gravity
+launches over all systems, against running the systems one by one.
 
 Default workload: 64 collisions, N per system log-uniform in [8192, 262144]
 (gas:halo 1:1), impact parameter U[0, 3], closing speed U[0.5, 2];

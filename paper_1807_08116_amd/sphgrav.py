@@ -442,7 +442,7 @@ class Engine:
 
 class Ensemble:
     """Independent systems (one Engine each, FP32C, one shared stream) whose
-    gravity runs as one persistent launch."""
+    gravity runs as persistent launches over all of them."""
 
     def __init__(self, states, device="cuda", chain_stream=None, **kw):
         import torch
