@@ -26,11 +26,41 @@ import numpy as np
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-FLOPS_PER_PAIR = 22          # 20 for the acceleration, +2 for the potential
+FLOPS_PER_PAIR = 22          # a credited pair: 20 for the acceleration, +2 for the potential
 PEAK = {"fp32": 157.3, "fp64": 78.6}  # TFLOP/s, MI355X vector peaks
 HBM_PEAK = 8000.0            # GB/s
 DT = 1e-3
 HBM_ROUNDS = 5               # rounds of the HBM-bound passes timed on their own
+
+
+def executed_flops(precision_form, n, variant=0):
+    """Operations of one gravity launch with the potential, as the chosen
+    kernel's far-field pair loop executes them (an FMA counts 2, the reciprocal
+    square root 2; the FP64 refinement's 2 multiplies and 3 FMAs count), and
+    what they are per pair.  The pairwise kernel meets each unordered pair once
+    and credits both particles, so this is less than FLOPS_PER_PAIR for each of
+    the n^2 ordered pairs."""
+    from paper_1807_08116_amd import autotune
+    refine = 8 if precision_form == "fp64" else 0
+    r2, root, cube, credit = 7, 2 + refine, 2, 8 + 2      # 4 FMAs and the potential's a side
+    if variant == 0 and n >= autotune.SYM_MIN:
+        per = r2 + root + cube + 2 * credit
+        return per * 0.5 * float(n) * float(n), "%d for each of N^2/2 pairs" % per
+    per = 22 + refine - 1 if variant in (1, 2) else r2 + root + cube + credit
+    return per * float(n) * float(n), "%d for each of N^2 ordered pairs" % per
+
+
+def alu_roofline(precision_form, n, variant, grav_s):
+    flops, what = executed_flops(precision_form, n, variant)
+    achieved, peak = flops / grav_s / 1e12, PEAK["fp32" if precision_form == "fp32c" else "fp64"]
+    return {"bound": "alu", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
+            "frac": achieved / peak,
+            "kernel": "gravity pair kernel (%s), executed operations: %s, %.1f ms/launch"
+                      % (precision_form, what, 1e3 * grav_s),
+            "credited": {"flops_per_ordered_pair": FLOPS_PER_PAIR, "unit": "TFLOP/s",
+                         "rate": FLOPS_PER_PAIR * float(n) * float(n) / grav_s / 1e12,
+                         "note": "not a utilisation: both particles of a pair are credited with "
+                                 "operations that may be executed once"}}
 
 
 def radix_passes(cell_cap):
@@ -293,8 +323,6 @@ def main():
     sec = res[head]["sec"]
     gms, glaunch = res[head]["prof"]["grav"]
     grav_s = gms / 1e3 / max(glaunch, 1)
-    achieved = FLOPS_PER_PAIR * float(n) * float(n) / grav_s / 1e12
-    peak = PEAK["fp32" if head == "fp32c" else "fp64"]
     out = {
         "metric": "force-steps/s at 2M particles, FP32-compensated vs FP64, at 1e-6 accel err",
         "value": args.steps / sec,
@@ -312,11 +340,8 @@ def main():
                                "%d gas + %d halo particles, one predictor-corrector step "
                                "+ FP64 energy/momentum sums" % (args.config, ng, n - ng),
                    "n_particles": n, "n_gas": ng, "precision_form": head, "seed": ic.SEED_BASE + int(args.config[1:])},
-        "roofline": {"bound": "alu", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
-                     "frac": achieved / peak,
-                     "traffic": recorded_traffic(head) if args.config == "c2" else None,
-                     "kernel": "gravity pair kernel (%s), %d flops/pair x N^2 per launch, "
-                               "%.1f ms/launch" % (head, FLOPS_PER_PAIR, 1e3 * grav_s)},
+        "roofline": dict(alu_roofline(head, n, args.variant if head == "fp64" else 0, grav_s),
+                         traffic=recorded_traffic(head) if args.config == "c2" else None),
         "cpu_baseline": cpu,
         "accel_err_vs_oracle": errs,
         "pairs_per_s": float(n) * n / grav_s,
@@ -348,11 +373,7 @@ def main():
         out["fp32c_vs_fp64_speedup"] = res["fp64"]["sec"] / res["fp32c"]["sec"]
     if "fp64" in res and head != "fp64":
         ms64, n64 = res["fp64"]["prof"]["grav"]
-        s64 = ms64 / 1e3 / max(n64, 1)
-        a64 = FLOPS_PER_PAIR * float(n) * float(n) / s64 / 1e12
-        out["roofline_fp64"] = {"bound": "alu", "achieved": a64, "peak": PEAK["fp64"],
-                                "unit": "TFLOP/s", "frac": a64 / PEAK["fp64"],
-                                "kernel": "gravity pair kernel (fp64), %.1f ms/launch" % (1e3 * s64)}
+        out["roofline_fp64"] = alu_roofline("fp64", n, args.variant, ms64 / 1e3 / max(n64, 1))
     if args.calib_copy:
         a = torch.empty(1 << 28, dtype=torch.float32, device="cuda")
         b = torch.empty_like(a)
